@@ -17,6 +17,7 @@
 //     reduces across lanes (and rescales) only when some score exceeds the reference by more than 2^8.
 // Work items are the group kernel's (RowItem x K/V head), pulled from a queue by persistent workgroups of 4 waves;
 // wave w takes the item's blocks w, w+4, ...; the four (m, l, O) are combined through LDS at the end.
+#include <algorithm>
 #include <mutex>
 
 #include "tile_body.h"
@@ -289,23 +290,21 @@ __global__ __launch_bounds__(64 * kSlimWaves, 5) void group_slim_kernel(AttnPara
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   __shared__ int s_next;
   const uint32_t Hk = (uint32_t)p.num_kv_heads;
-  const uint32_t n = (uint32_t)(p.n_row_items - p.n_vec_items) * Hk;
-  for (;;) {
-    if (threadIdx.x == 0) s_next = atomicAdd(&p.counters[kCtrGroupQueue], 1);
-    __syncthreads();
-    const uint32_t idx = (uint32_t)s_next;
-    __syncthreads();  // s_next is rewritten at the top of the next round
-    if (idx >= n) break;
+  const uint32_t n = (uint32_t)(p.n_row_items - p.group_first) * Hk;
+  const bool queued = n > gridDim.x;
+  for (uint32_t idx = blockIdx.x; idx < n;) {
     const uint32_t item = idx / Hk;
-    const RowItem it = p.row_items[(uint32_t)p.n_vec_items + item];  // the group kernels' items follow the vector kernel's
+    const RowItem it = p.row_items[(uint32_t)p.group_first + item];
     slim_body(p, it, (int)(idx - item * Hk), lds);
-    __syncthreads();  // the combine reads every wave's slice
+    if (!queued) return;
+    idx = queue_pull(&p.counters[kCtrGroupQueue], gridDim.x, &s_next);  // its barriers end the combine's use of LDS
   }
+  if (!queued) return;
   queue_leave(p.counters, kCtrGroupQueue, 1, -1, kCtrGroupLeft);
 }
 
 hipError_t launch_group_slim(const AttnParams& p, int head_dim, int slots, hipStream_t st) {
-  const int n_items = p.n_row_items - p.n_vec_items;
+  const int n_items = p.n_row_items - p.group_first;
   if (n_items <= 0) return hipSuccess;
   if (head_dim != kSD || p.group < 2 || p.group > 16 || !p.counters || slots < 1) return hipErrorInvalidValue;
   if ((uint64_t)n_items * (uint64_t)p.num_kv_heads > 0x7fffffffull) return hipErrorInvalidValue;
@@ -322,7 +321,7 @@ hipError_t launch_group_slim(const AttnParams& p, int head_dim, int slots, hipSt
       asked[dev] = true;
     }
   }
-  hipLaunchKernelGGL(group_slim_kernel, dim3((uint32_t)slots), dim3(64 * kSlimWaves), kSlimLdsBytes, st, p);
+  hipLaunchKernelGGL(group_slim_kernel, dim3((uint32_t)std::min<int64_t>(slots, (int64_t)n_items * p.num_kv_heads)), dim3(64 * kSlimWaves), kSlimLdsBytes, st, p);
   return hipGetLastError();
 }
 

@@ -1,4 +1,6 @@
 // Row kernel (decode rows, and spans row by row when asked) and the split-KV merge.
+#include <algorithm>
+
 #include "row_body.h"
 
 namespace ic {
@@ -19,7 +21,7 @@ __global__ __launch_bounds__(kRowWaves * 64) void row_attn_kernel(AttnParams p) 
 }
 
 // Persistent launch of the same body: `slots` workgroups (one per CU) pull (item, head) pairs from a
-// queue with an atomic counter (counters[8], zeroed by the descriptor upload).  Measured on MI355X:
+// queue with an atomic counter (zeroed by the descriptor upload).  Measured on MI355X:
 // 256 resident workgroups read 6.65 TB/s, 4 % more than one workgroup per work item, because no
 // workgroup launch or drain sits between two items.
 template <int D, int PF>
@@ -28,17 +30,15 @@ __global__ __launch_bounds__(kRowWaves * 64) void row_persist_kernel(AttnParams 
   __shared__ int s_next;
   const int H = p.num_heads;
   const uint32_t n_r = (uint32_t)p.n_vec_items * (uint32_t)H;
-  for (;;) {
-    if (threadIdx.x == 0) s_next = atomicAdd(&p.counters[8], 1);
-    __syncthreads();
-    const uint32_t idx = (uint32_t)s_next;
-    __syncthreads();  // s_next is rewritten at the top of the next round
-    if (idx >= n_r) break;
+  const bool queued = n_r > gridDim.x;
+  for (uint32_t idx = blockIdx.x; idx < n_r;) {
     const uint32_t item = idx / (uint32_t)H;  // head fastest: neighbours read adjacent tiles of a block
     const RowItem it = p.row_items[item];
     row_body<D, PF, true>(p, it, (int)(idx - item * (uint32_t)H), lds);
-    __syncthreads();  // the body leaves LDS in use until every wave is through
+    if (!queued) return;
+    idx = queue_pull(&p.counters[kCtrRowQueue], gridDim.x, &s_next);
   }
+  if (!queued) return;
   queue_leave(p.counters, kCtrRowQueue, 1, -1, kCtrRowLeft);
 }
 
@@ -101,24 +101,22 @@ __global__ __launch_bounds__(kRowWaves * 64, (D <= 128 ? 6 : 5)) void row_persis
   __shared__ int s_next;
   const int H = p.num_heads;
   const uint32_t n_r = (uint32_t)p.n_vec_items * (uint32_t)H;
-  for (;;) {
-    if (threadIdx.x == 0) s_next = atomicAdd(&p.counters[8], 1);
-    __syncthreads();
-    const uint32_t idx = (uint32_t)s_next;
-    __syncthreads();
-    if (idx >= n_r) break;
+  const bool queued = n_r > gridDim.x;
+  for (uint32_t idx = blockIdx.x; idx < n_r;) {
     const uint32_t item = idx / (uint32_t)H;
     const RowItem it = p.row_items[item];
     row_body<D, 0, true, (D > 128)>(p, it, (int)(idx - item * (uint32_t)H), lds);
-    __syncthreads();
+    if (!queued) return;
+    idx = queue_pull(&p.counters[kCtrRowQueue], gridDim.x, &s_next);
   }
+  if (!queued) return;
   queue_leave(p.counters, kCtrRowQueue, 1, -1, kCtrRowLeft);
 }
 
 hipError_t launch_row_persist(const AttnParams& p, int head_dim, int slots, hipStream_t st) {
   if (p.n_vec_items <= 0) return hipSuccess;
   if (!p.counters || slots < 1) return hipErrorInvalidValue;
-  const dim3 g((uint32_t)slots), b(kRowWaves * 64);
+  const dim3 g((uint32_t)std::min<uint64_t>((uint64_t)slots, (uint64_t)p.n_vec_items * p.num_heads)), b(kRowWaves * 64);
   switch (head_dim) {
     case 64: hipLaunchKernelGGL((row_persist_kernel<64, 1>), g, b, 0, st, p); break;
     case 128: hipLaunchKernelGGL((row_persist_kernel<128, 1>), g, b, 0, st, p); break;
@@ -131,7 +129,7 @@ hipError_t launch_row_persist(const AttnParams& p, int head_dim, int slots, hipS
 hipError_t launch_row_persist_slim(const AttnParams& p, int head_dim, int slots, hipStream_t st) {
   if (p.n_vec_items <= 0) return hipSuccess;
   if (!p.counters || slots < 1) return hipErrorInvalidValue;
-  const dim3 g((uint32_t)slots), b(kRowWaves * 64);
+  const dim3 g((uint32_t)std::min<uint64_t>((uint64_t)slots, (uint64_t)p.n_vec_items * p.num_heads)), b(kRowWaves * 64);
   switch (head_dim) {
     case 64: hipLaunchKernelGGL(row_persist_slim_kernel<64>, g, b, 0, st, p); break;
     case 128: hipLaunchKernelGGL(row_persist_slim_kernel<128>, g, b, 0, st, p); break;

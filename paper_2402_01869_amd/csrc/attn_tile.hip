@@ -1,7 +1,9 @@
 // Tile kernels: recomputation spans on the matrix cores.  head_dim <= 128: 32 query rows per wave (tile_body.h);
-// head_dim 256: 16 rows per wave (tile16_body.h).  Either way a workgroup is 8 waves, two per SIMD.
-#include "tile_body.h"
-#include "tile16_body.h"
+// head_dim 256: 16 rows per wave (tile16_body.h).  Either way a workgroup is 8 waves, two per SIMD.  The rows of a span
+// that see fewer than 64 keys are units of their own (few_body.h), handed out after the tile items.
+#include <algorithm>
+
+#include "few_body.h"
 
 namespace ic {
 
@@ -29,11 +31,34 @@ struct Impl<D, true> {
   }
 };
 
+// Few-key units of a launch: pairs of query heads per few item.
+__host__ __device__ inline uint32_t few_units(const AttnParams& p) { return (uint32_t)p.n_few_items * (uint32_t)((p.num_heads + 1) / 2); }
+
+// Workgroups (of one XCD where each has its queue) that hand out everything in one round; XCD 0 has the most to do.
+__host__ __device__ inline uint32_t tile_round(const AttnParams& p) {
+  const uint32_t n_th = (uint32_t)p.num_heads >> p.tile_g_shift;
+  if (n_th < 8u) return (uint32_t)p.n_tile_items * n_th + few_units(p);
+  return (uint32_t)p.n_tile_items * ((n_th + 7u) / 8u) + (few_units(p) + 7u) / 8u;
+}
+
+template <int D>
+__device__ __forceinline__ void run_few(const AttnParams& p, uint32_t unit, uint16_t* lds) {
+  static_assert(fewp::few_lds_bytes<D>() <= Impl<D>::kLdsBytes && Impl<D>::kThreads == 512, "few-key units run in the tile kernels");
+  const uint32_t pairs = (uint32_t)(p.num_heads + 1) / 2u;
+  const uint32_t f = unit / pairs;
+  fewp::few_body<D>(p, p.few_items[f], (int)(unit - f * pairs), lds);
+}
+
 template <int D>
 __global__ __launch_bounds__(Impl<D>::kThreads, 2) void tile_attn_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[Impl<D>::kLdsBytes / 2];
   const int n_th = p.num_heads >> p.tile_g_shift;  // head groups, each served by one workgroup per item
   const uint32_t wg = blockIdx.x;
+  const uint32_t n_tile = (uint32_t)p.n_tile_items * (uint32_t)n_th;
+  if (wg >= n_tile) {
+    run_few<D>(p, wg - n_tile, lds);
+    return;
+  }
   const int item_idx = wg / n_th;
   const int th = wg - item_idx * n_th;
   const TileItem it = p.tile_items[item_idx];
@@ -64,12 +89,15 @@ __global__ __launch_bounds__(Impl<D>::kThreads, 2) __attribute__((amdgpu_num_vgp
   const uint32_t x = blockIdx.x & 7u;
   const uint32_t heads_x = (uint32_t)(H - (int)x + 7) / 8u;  // head groups congruent to x mod 8
   const uint32_t n_t = (uint32_t)p.n_tile_items * (per_xcd ? heads_x : (uint32_t)H);
-  for (;;) {
-    if (threadIdx.x == 0) s_next = atomicAdd(&p.counters[per_xcd ? x : (uint32_t)kCtrTileShared], 1);
-    __syncthreads();
-    const uint32_t idx = (uint32_t)s_next;
-    __syncthreads();  // s_next is rewritten at the top of the next round
-    if (idx >= n_t) break;
+  const uint32_t units = few_units(p);  // dealt to the XCDs by unit index, after the tile items
+  const uint32_t n_all = n_t + (per_xcd ? (units - x + 7u) / 8u : units);
+  // the first round is handed out by index: workgroup blockIdx of XCD x takes the XCD's item blockIdx / 8
+  const uint32_t round = per_xcd ? gridDim.x / 8u : gridDim.x;
+  const bool queued = tile_round(p) > round;  // the same for every XCD
+  int32_t* const queue = &p.counters[per_xcd ? x : (uint32_t)kCtrTileShared];
+  const auto next = [&]() -> uint32_t { return queued ? queue_pull(queue, round, &s_next) : n_all; };
+  uint32_t idx = per_xcd ? blockIdx.x / 8u : blockIdx.x;
+  while (idx < n_t) {
     uint32_t item, th;
     if (per_xcd) {
       const uint32_t hsel = idx / (uint32_t)p.n_tile_items;
@@ -81,16 +109,21 @@ __global__ __launch_bounds__(Impl<D>::kThreads, 2) __attribute__((amdgpu_num_vgp
     }
     const TileItem it = p.tile_items[item];
     Impl<D>::template body<false>(p, it, (int)th, lds);
-    __syncthreads();  // the body leaves LDS in use until every wave is through
+    idx = next();
   }
-  queue_leave(p.counters, 0, 8, kCtrTileShared, kCtrTileLeft);
+  // (a loop of its own: values of one body kept in registers across the other would not fit)
+  while (idx < n_all) {
+    run_few<D>(p, per_xcd ? x + 8u * (idx - n_t) : idx - n_t, lds);
+    idx = next();
+  }
+  if (queued) queue_leave(p.counters, 0, 8, kCtrTileShared, kCtrTileLeft);
 }
 
 }  // namespace
 
 hipError_t launch_tile_kernel(const AttnParams& p, int head_dim, hipStream_t st) {
-  if (p.n_tile_items <= 0) return hipSuccess;
-  const uint64_t grid = (uint64_t)p.n_tile_items * (uint64_t)(p.num_heads >> p.tile_g_shift);
+  const uint64_t grid = (uint64_t)p.n_tile_items * (uint64_t)(p.num_heads >> p.tile_g_shift) + few_units(p);
+  if (grid == 0) return hipSuccess;
   if (grid > 0x7fffffffull) return hipErrorInvalidValue;
   const dim3 g((uint32_t)grid);
   switch (head_dim) {
@@ -104,9 +137,11 @@ hipError_t launch_tile_kernel(const AttnParams& p, int head_dim, hipStream_t st)
 
 // slots is rounded down to a multiple of 8 so that every XCD gets the same number of workgroups.
 hipError_t launch_tile_persist(const AttnParams& p, int head_dim, int slots, bool beside, hipStream_t st) {
-  if (p.n_tile_items <= 0) return hipSuccess;
+  if (p.n_tile_items <= 0 && p.n_few_items <= 0) return hipSuccess;
   if (!p.counters || slots < 8) return hipErrorInvalidValue;
-  const dim3 g((uint32_t)(slots - slots % 8));
+  // no more workgroups than one round needs, and as many per XCD as its queue's share where each has its own
+  const bool per_xcd = (p.num_heads >> p.tile_g_shift) >= 8;
+  const dim3 g(per_xcd ? 8u * std::min((uint32_t)slots / 8u, tile_round(p)) : std::min((uint32_t)(slots - slots % 8), tile_round(p)));
 #define IC_TILE_CASE(DD)                                                                                          \
   case DD:                                                                                                        \
     if (beside) hipLaunchKernelGGL((tile_persist_kernel<DD, true>), g, dim3(Impl<DD>::kThreads), 0, st, p);        \

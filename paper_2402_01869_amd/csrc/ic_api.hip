@@ -25,6 +25,8 @@ constexpr int kUnsplitWorkgroups = 1024;  // tile workgroups (4 per CU) from whi
 // output, with dozens the roundings average out.  The vector path keeps the weights in fp32.
 constexpr int kShareKeys = 8192;  // sequences at least this long keep their tile items side by side
 constexpr int kMfmaMinKeys = 64;
+constexpr int kExpectedCus = 256;        // the planner runs without a device; the launches use the device's own count
+constexpr double kSideBySideUs = 15.0;   // expected time of the shorter kernel from which a second stream pays
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -167,20 +169,22 @@ bool destinations_distinct(const ic_pool_cfg& cfg, const int32_t* dst, size_t ro
 // ---------------------------------------------------------------------------------------
 // Launch plan.  Sizes only (plan_sizes) or the filled descriptor image (plan_fill).
 // Device image layout (all sections 256-byte aligned, in this order):
-//   counters[16] | bt_off[num_seqs] | bt_flat[table_entries] | row_items | tile_items | merge_items
+//   counters[16] | bt_off[num_seqs] | bt_flat[table_entries] | row_items | tile_items | few_items | merge_items | row_dst
 // followed in the workspace by part_o[slots][H][D] and part_ml[slots][H][2].
 // ---------------------------------------------------------------------------------------
 struct PlanSizes {
   ic_plan_info info;
   int row_part, span_part, tile_rows;  // tile_rows: QUERY rows per tile item
   int min_keys;                        // rows that see fewer keys are vector row items whatever their kind
-  int vec_items;                       // row items [0, vec_items) run on the vector kernel, the rest on the group kernel
+  int vec_items;                       // row items [0, vec_items) keep fp32 weights, the rest run on the group kernel
+  int few_runs, few_rows;              // ... of which the last few_rows are the rows of few_runs few-key units (tile kernels)
   int tile_g_shift;                    // log2 of the query heads one tile workgroup serves
   bool spans_as_rows;
   bool decode_as_tiles;                // grouped pools, span_kernel = 2: decode rows as one-row tile items
   bool decode_as_group;                // grouped pools: decode rows stay row items, run by the group kernel
+  bool side_by_side;                   // both kernels are long enough to pay for a second stream
   bool tile_leads;                     // the tile items are expected to take longer than the row items
-  size_t off_ctr, off_bt_off, off_bt_flat, off_row, off_tile, off_merge, off_row_dst, image_bytes;
+  size_t off_ctr, off_bt_off, off_bt_flat, off_row, off_tile, off_few, off_merge, off_row_dst, image_bytes;
   size_t off_part_o, off_part_ml, total_bytes;
 };
 
@@ -200,10 +204,12 @@ struct ic_plan {
 
 namespace {
 
-// Where the rows of one sequence go.  Rows [0, n_few) see fewer than min_keys keys and are vector row
-// items whatever their kind; the rest are row items (vector or group kernel) or tile items.
+// Where the rows of one sequence go.  Rows [0, n_few) see fewer than min_keys keys and are row items whatever their
+// kind, run by the vector kernel or, several to a unit, by the tile kernels' few-key body; the rest are row items
+// (vector or group kernel) or tile items.
 struct SeqRoute {
-  int n_few;        // leading rows of the sequence that stay off the matrix cores
+  int n_few;        // leading rows of the sequence whose weights must not be rounded to bf16
+  bool few_unit;    // ... run as one few-key unit (else: one by one on the vector kernel)
   bool rest_rows;   // the other rows are row items (else: tile items)
   bool rest_group;  // ... run by the group kernel
 };
@@ -213,6 +219,8 @@ SeqRoute route(const PlanSizes& ps, int c, int n) {
   r.n_few = std::min(n, std::max(0, ps.min_keys - 1 - (c - n)));
   r.rest_rows = n == 1 ? !ps.decode_as_tiles : ps.spans_as_rows;
   r.rest_group = r.rest_rows && n == 1 && ps.decode_as_group;
+  // A decode row stays with the vector kernel: alone in its sequence it would fill one of a unit's 64 rows.
+  r.few_unit = r.n_few > 0 && n > 1 && !ps.spans_as_rows;
   return r;
 }
 
@@ -251,17 +259,25 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
   }
   ic_plan_info& in = ps.info;
   double tile_pairs = 0, row_keys = 0;  // (query row, key) pairs of the tile items; keys of the row items
+  int64_t tile_steps = 0, most_steps = 0, most_keys = 0;  // 64-key steps over all tile items and of the longest; keys of the longest row item
   for (int s = 0; s < d->num_seqs; ++s) {
     const int c = d->ctx_len[s], n = d->q_len[s];
     in.table_entries += (c + kBlockSize - 1) / kBlockSize;
     if (n == 1) in.decode_rows += 1; else in.span_rows += n;
     const SeqRoute rt = route(ps, c, n);
     const int n_as_rows = rt.rest_rows ? n : rt.n_few;
+    if (rt.few_unit) {
+      ps.few_runs += 1;
+      ps.few_rows += rt.n_few;
+    }
     for (int i = 0; i < n_as_rows; ++i) {
       const int klen = c - n + i + 1;
       const int parts = (klen + ps.row_part - 1) / ps.row_part;
       in.row_items += parts;
-      row_keys += klen;
+      if (!rt.few_unit) {
+        row_keys += klen;
+        most_keys = std::max<int64_t>(most_keys, std::min(klen, ps.row_part));
+      }
       if (i < rt.n_few || !rt.rest_group) ps.vec_items += parts;
       if (parts > 1) { in.partial_slots += parts; in.merge_rows += 1; }
     }
@@ -273,6 +289,8 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
         const int parts = (klen + part - 1) / part;
         in.tile_items += parts;
         tile_pairs += (double)nr * (klen - 0.5 * nr);
+        tile_steps += (klen + 63) / 64;
+        most_steps = std::max<int64_t>(most_steps, (std::min(klen, part) + 63) / 64);
         if (parts > 1) { in.partial_slots += parts * nr; in.merge_rows += nr; }
       }
     }
@@ -282,12 +300,24 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
   // 0.9 PFLOP/s at 4 D flop per pair and head, row kernels 5.5 TB/s at 4 D bytes per key and K/V head): that one
   // goes on the caller's stream, the other through the fork and join of the second stream.  (head_dim 256: 0.5 PFLOP/s.)
   ps.tile_leads = tile_pairs * H * (4.0 * D / (D > 128 ? 0.5e15 : 0.9e15)) > row_keys * pool->cfg.num_kv_heads * (4.0 * D / 5.5e12);
+  // Two streams cost about 13 us on the way of the kernel that ends last (fork 7, join 6; kernels that follow each
+  // other on one stream start without a gap), so they pay only when the shorter kernel takes longer than that.  A tile
+  // workgroup's step of 64 keys takes the same time however many of its rows are live; a workgroup of the row kernels
+  // alone on its CU reads 40 GB/s.  Measured, two decode rows and two 32-row chunks of 4 heads: 45 us side by side,
+  // 21 us one after the other.
+  const double step_us = 4.0 * tile_rows(D) * 64 * D / (D > 128 ? 0.5e15 / kExpectedCus : 0.9e15 / kExpectedCus) * 1e6;
+  const int64_t n_th = H >> ps.tile_g_shift;
+  const double tile_us = std::max((double)tile_steps * n_th / kExpectedCus, (double)most_steps) * step_us;
+  const double key_bytes = 4.0 * D;  // K and V of one key and K/V head
+  const double row_us = std::max(row_keys * pool->cfg.num_kv_heads * key_bytes / 5.5e6, (double)most_keys * key_bytes / 40e3);
+  ps.side_by_side = std::min(tile_us, row_us) > kSideBySideUs;
   size_t o = 0;
   ps.off_ctr = o;     o = align_up(o + sizeof(int32_t) * 16, 256);
   ps.off_bt_off = o;  o = align_up(o + sizeof(int32_t) * (size_t)d->num_seqs, 256);
   ps.off_bt_flat = o; o = align_up(o + sizeof(int32_t) * (size_t)in.table_entries, 256);
   ps.off_row = o;     o = align_up(o + sizeof(RowItem) * (size_t)in.row_items, 256);
   ps.off_tile = o;    o = align_up(o + sizeof(TileItem) * (size_t)in.tile_items, 256);
+  ps.off_few = o;     o = align_up(o + sizeof(FewItem) * (size_t)ps.few_runs, 256);
   ps.off_merge = o;   o = align_up(o + sizeof(MergeItem) * (size_t)in.merge_rows, 256);
   ps.off_row_dst = o; o = align_up(o + sizeof(int32_t) * (size_t)d->total_q_rows, 256);  // for kv_write_span_planned
   ps.image_bytes = o;
@@ -304,6 +334,7 @@ void plan_fill(const ic_batch_desc* d, const PlanSizes& ps, char* img) {
   int32_t* bt_flat = (int32_t*)(img + ps.off_bt_flat);
   RowItem* rows = (RowItem*)(img + ps.off_row);
   TileItem* tiles = (TileItem*)(img + ps.off_tile);
+  FewItem* fews = (FewItem*)(img + ps.off_few);
   MergeItem* merges = (MergeItem*)(img + ps.off_merge);
   {
     int32_t* row_dst = (int32_t*)(img + ps.off_row_dst);
@@ -311,7 +342,9 @@ void plan_fill(const ic_batch_desc* d, const PlanSizes& ps, char* img) {
     append_destinations(d, row_dst);
   }
   int64_t nbt = 0;
-  int nvec = 0, ngrp = ps.vec_items;  // vector items first, group-kernel items after them
+  // vector items first, then the rows of the few-key units, then the group kernel's items
+  const int few_first = ps.vec_items - ps.few_rows;
+  int nvec = 0, nfew = few_first, ngrp = ps.vec_items, nruns = 0;
   int ntiles = 0, nmerge = 0, slot = 0;
   std::vector<int> tile_slot0, tile_parts;
   for (int s = 0; s < d->num_seqs; ++s) {
@@ -323,6 +356,7 @@ void plan_fill(const ic_batch_desc* d, const PlanSizes& ps, char* img) {
     nbt += nb;
     const SeqRoute rt = route(ps, c, n);
     const int n_as_rows = rt.rest_rows ? n : rt.n_few;
+    if (rt.few_unit) fews[nruns++] = FewItem{nfew, rt.n_few};
     for (int i = 0; i < n_as_rows; ++i) {
       const int klen = c - n + i + 1;
       const int parts = (klen + ps.row_part - 1) / ps.row_part;
@@ -330,7 +364,7 @@ void plan_fill(const ic_batch_desc* d, const PlanSizes& ps, char* img) {
       const bool vec = i < rt.n_few || !rt.rest_group;
       if (parts > 1) merges[nmerge++] = MergeItem{qrow, slot, parts, 0};
       for (int k = 0; k < parts; ++k) {
-        RowItem& it = rows[vec ? nvec++ : ngrp++];
+        RowItem& it = rows[rt.few_unit ? nfew++ : vec ? nvec++ : ngrp++];
         it.seq = s;
         it.qrow = qrow;
         it.k_begin = k * ps.row_part;
@@ -394,7 +428,7 @@ void plan_fill(const ic_batch_desc* d, const PlanSizes& ps, char* img) {
   std::stable_sort(tiles, tiles + ntiles, [&](const TileItem& a, const TileItem& b) { return weight(a) > weight(b); });
   // The same for row items, within the vector kernel's and the group kernel's share: decode contexts differ 16 : 1.
   const auto longer = [](const RowItem& a, const RowItem& b) { return a.k_end - a.k_begin > b.k_end - b.k_begin; };
-  std::stable_sort(rows, rows + ps.vec_items, longer);
+  std::stable_sort(rows, rows + few_first, longer);
   std::stable_sort(rows + ps.vec_items, rows + ps.info.row_items, longer);
 }
 
@@ -657,6 +691,7 @@ static int launch_attention(ic_pool* pool, const PlanSizes& ps, float scale, con
   p.bt_flat = (const int32_t*)(ws + ps.off_bt_flat);
   p.row_items = (const RowItem*)(ws + ps.off_row);
   p.tile_items = (const TileItem*)(ws + ps.off_tile);
+  p.few_items = (const FewItem*)(ws + ps.off_few);
   p.merge_items = (const MergeItem*)(ws + ps.off_merge);
   p.part_o = (float*)(ws + ps.off_part_o);
   p.part_ml = (float*)(ws + ps.off_part_ml);
@@ -665,8 +700,10 @@ static int launch_attention(ic_pool* pool, const PlanSizes& ps, float scale, con
   p.group = pool->cfg.num_heads / pool->cfg.num_kv_heads;
   p.tile_g_shift = ps.tile_g_shift;
   p.n_row_items = ps.info.row_items;
-  p.n_vec_items = ps.vec_items;
+  p.n_vec_items = ps.vec_items - ps.few_rows;
+  p.group_first = ps.vec_items;
   p.n_tile_items = ps.info.tile_items;
+  p.n_few_items = ps.few_runs;
   p.n_merge_items = ps.info.merge_rows;
   p.scale_log2e = scale * 1.4426950408889634f;
   p.row_variant = pool->tune.row_variant;
@@ -678,9 +715,11 @@ static int launch_attention(ic_pool* pool, const PlanSizes& ps, float scale, con
   // workgroup of each per CU, the tile kernel on the pool's second stream (forked from and joined
   // back into the caller's stream by events).  The kernel beside the tile kernel is the slim row
   // kernel (multi-head pools) or the slim group kernel (grouped pools: head_dim 128, groups of up
-  // to 16 heads).  serial_spans = 1 and the other grouped shapes run one kernel after the other instead.
-  const int n_group_items = p.n_row_items - p.n_vec_items;
-  const bool pair_ok = p.n_tile_items > 0 && !pool->tune.serial_spans;
+  // to 16 heads).  serial_spans = 1, the other grouped shapes and batches too small to pay for the second stream run one
+  // kernel after the other instead.
+  const int n_group_items = p.n_row_items - p.group_first;
+  const bool tiles = p.n_tile_items > 0 || p.n_few_items > 0;
+  const bool pair_ok = tiles && ps.side_by_side && !pool->tune.serial_spans;
   const bool beside_rows = pair_ok && p.n_vec_items > 0 && !ps.decode_as_group;
   const bool beside_group = pair_ok && n_group_items > 0 && D == 128 && p.group <= 16;
   const int row_slots = pool->tune.row_slots > 0 ? pool->tune.row_slots : pool->num_cus;
@@ -733,7 +772,7 @@ static int launch_attention(ic_pool* pool, const PlanSizes& ps, float scale, con
     }
     if (!ok) return IC_EHIP;
   } else {
-    if (p.n_tile_items > 0) {
+    if (tiles) {
       ProfScope ps_(pool, IC_K_TILE, st);
       // head_dim <= 128: the persistent launch also when no other kernel runs beside it.  Its per-XCD queues keep the
       // query tiles of one (sequence, head) on one L2: on 2048-row chunks the spans then fetch 2.6 x instead of 6.9 x

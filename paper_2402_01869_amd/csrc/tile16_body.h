@@ -35,12 +35,12 @@ struct G16 {
   static constexpr int kLoads = kTileK * kChunks / kThreads;  // K (and V) chunks per thread and tile
   static constexpr int kQSteps = D / 32;                  // MFMA k-steps of Q K^T
   static constexpr int kDTiles = D / 16;                  // 16-row tiles of O^T
-  static_assert(kTileK * kChunks % kThreads == 0, "a tile must split evenly over the threads");
   static_assert(kThreads <= 1024, "workgroup size");
 };
 
 template <int D>
 struct Staging16 {
+  static_assert(kTileK * G16<D>::kChunks % G16<D>::kThreads == 0, "a tile must split evenly over the threads");
   u32x4 k[G16<D>::kLoads];
   u32x4 v[G16<D>::kLoads];
 };
