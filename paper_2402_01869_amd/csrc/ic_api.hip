@@ -180,6 +180,7 @@ struct PlanSizes {
   int few_runs, few_rows;              // ... of which the last few_rows are the rows of few_runs few-key units (tile kernels)
   int tile_g_shift;                    // log2 of the query heads one tile workgroup serves
   bool spans_as_rows;
+  bool few_as_units;                   // few-key rows of spans go to the tile kernels' few-key body
   bool decode_as_tiles;                // grouped pools, span_kernel = 2: decode rows as one-row tile items
   bool decode_as_group;                // grouped pools: decode rows stay row items, run by the group kernel
   bool side_by_side;                   // both kernels are long enough to pay for a second stream
@@ -220,8 +221,58 @@ SeqRoute route(const PlanSizes& ps, int c, int n) {
   r.rest_rows = n == 1 ? !ps.decode_as_tiles : ps.spans_as_rows;
   r.rest_group = r.rest_rows && n == 1 && ps.decode_as_group;
   // A decode row stays with the vector kernel: alone in its sequence it would fill one of a unit's 64 rows.
-  r.few_unit = r.n_few > 0 && n > 1 && !ps.spans_as_rows;
+  r.few_unit = r.n_few > 0 && n > 1 && ps.few_as_units;
   return r;
+}
+
+// Keys per decode work item when the caller leaves the choice to the library.  Whole rows (up to kDefaultRowPart keys)
+// as long as they give every workgroup of the launch several items; fewer, and most of the chip would idle while the
+// longest rows run: then the partition that is expected to end soonest.  Time is counted in keys a workgroup reads at
+// its share of the memory's rate, 26 (row kernel) or 13 GB/s (group kernel: two workgroups per CU).  An item costs 2 us
+// besides its keys, a split 4.5 us for the merge pass; items of a round that is not full leave the rest idle.
+// Measured: one row of 3000 keys, 40 heads, head_dim 128: row kernel 44 -> 13.4 us
+// (+ 3.9 us of merge); 8 rows of 1000..8000 keys, 64 heads over 8 K/V heads: group kernel 58.8 -> 33.4 us (merge 4.5 -> 7.3).
+int choose_row_part(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& ps) {
+  const bool group = ps.decode_as_group;
+  const int64_t units = group ? pool->cfg.num_kv_heads : pool->cfg.num_heads;
+  bool spans = false;
+  for (int s = 0; s < d->num_seqs && !spans; ++s) spans = d->q_len[s] > 1;
+  const bool two = group && !spans;  // two group workgroups per CU; beside a tile workgroup one
+  const int64_t slots = two ? 2 * kExpectedCus : kExpectedCus;
+  const int64_t enough = 4 * slots;
+  int64_t items = 0, keys = 0;
+  int longest = 0;
+  for (int s = 0; s < d->num_seqs && items * units < enough; ++s) {
+    if (d->q_len[s] != 1) continue;
+    items += (d->ctx_len[s] + kDefaultRowPart - 1) / kDefaultRowPart;
+    keys += d->ctx_len[s];
+    longest = std::max(longest, d->ctx_len[s]);
+  }
+  if (items == 0 || items * units >= enough) return kDefaultRowPart;
+  const double keys_per_us = (two ? 13e3 : 26e3) / (4.0 * pool->cfg.head_dim);
+  const double item_cost = 2.0 * keys_per_us, split_cost = 4.5 * keys_per_us;
+  static const int parts[] = {kDefaultRowPart, 3072, 2048, 1536, 1280, 1024, 768, 640, 512, 448, 384, 320, 256, 192, 128};
+  int best = kDefaultRowPart;
+  double best_cost = 0.0;
+  for (const int part : parts) {
+    int64_t n = 0, full = 0;
+    for (int s = 0; s < d->num_seqs; ++s) {
+      if (d->q_len[s] != 1) continue;
+      full += d->ctx_len[s] / part;
+      n += (d->ctx_len[s] + part - 1) / part;
+    }
+    n *= units;
+    full *= units;
+    const double most = std::min(longest, part) + item_cost;
+    double cost = std::max(most, (double)((full + slots - 1) / slots) * (part + item_cost));
+    if (n > slots) cost = std::max(cost, (keys * units + n * item_cost) / slots + 0.5 * most);
+    if (longest > part) cost += split_cost;
+    if (best_cost == 0.0 || cost < best_cost) {
+      best = part;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
 void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
@@ -237,23 +288,28 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
   const int kTileRows = tile_rows(pool->cfg.head_dim) >> ps.tile_g_shift;
   ps.tile_rows = kTileRows;
   const ic_tuning& t = pool->tune;
-  ps.row_part = t.decode_part_tokens > 0 ? round64(t.decode_part_tokens) : kDefaultRowPart;
-  ps.row_part = std::min(ps.row_part, kMaxRowPart);
   ps.span_part = t.span_part_tokens > 0 ? round64(t.span_part_tokens) : kDefaultSpanPart;
   ps.min_keys = t.mfma_min_keys > 0 ? std::min(t.mfma_min_keys, 64) : kMfmaMinKeys;  // <= the smallest partition
   ps.spans_as_rows = (t.span_kernel == 1);  // default: MFMA tiles
   ps.decode_as_tiles = ps.tile_g_shift > 0 && t.span_kernel == 2;
   ps.decode_as_group = ps.tile_g_shift > 0 && t.span_kernel == 0;
+  ps.row_part = t.decode_part_tokens > 0 ? round64(t.decode_part_tokens) : choose_row_part(pool, d, ps);
+  ps.row_part = std::min(ps.row_part, kMaxRowPart);
+  int64_t tiles = 0, few = 0;  // unsplit query tiles; rows of spans with few keys
+  for (int s = 0; s < d->num_seqs; ++s)
+    if (d->q_len[s] > 1) {
+      const int n_few = route(ps, d->ctx_len[s], d->q_len[s]).n_few;
+      tiles += (d->q_len[s] - n_few + kTileRows - 1) / kTileRows;
+      few += n_few;
+    }
+  // Without tile items the few-key units would be a launch of their own (4-5 us); up to two rounds of one-row items on
+  // the vector kernel take no longer.  Measured: 4 chunks of 2 rows from position 0 + 1 decode row, 16 heads, two
+  // layers: 30 us as row items, 36 as units.
+  ps.few_as_units = !ps.spans_as_rows && (tiles > 0 || few * pool->cfg.num_heads > 2 * kExpectedCus);
   if (t.span_part_tokens == 0) {
     // Splitting a span's keys buys parallelism at the price of fp32 partial results for every row
     // and a merge pass (measured on the long-context shape: 7 % of the call).  When the unsplit query
     // tiles already give every CU several workgroups, do not split.
-    int64_t tiles = 0;
-    for (int s = 0; s < d->num_seqs; ++s)
-      if (d->q_len[s] > 1) {
-        const int rest = d->q_len[s] - route(ps, d->ctx_len[s], d->q_len[s]).n_few;
-        tiles += (rest + kTileRows - 1) / kTileRows;
-      }
     const int64_t head_groups = pool->cfg.num_heads >> ps.tile_g_shift;
     if (tiles * head_groups >= kUnsplitWorkgroups) ps.span_part = 1 << 30;
   }
