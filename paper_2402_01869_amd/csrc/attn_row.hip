@@ -43,26 +43,50 @@ __global__ __launch_bounds__(kRowWaves * 64) void row_persist_kernel(AttnParams 
 }
 
 // Split-KV merge: out = sum_p o_p 2^(m_p - m) / sum_p l_p 2^(m_p - m), m = max_p m_p.
-// One workgroup of D threads per (row, head); partials are read coalesced over d.
+// The partial results of a row are [H][D] fp32 per partition, contiguous: a workgroup of 256 threads takes 1024
+// consecutive values of one row, 16 bytes per thread and load.  Bound by memory (and, for a handful of rows, by latency:
+// launch, merge item, one round of loads), so the partitions are read four at a time, values and (m, l) together, and
+// combined in ascending order with a running maximum.  Measured against one workgroup of D threads per (row, head), which
+// read 4 bytes per thread and needed the maximum before the first value: 8 rows of 64 heads in 2 to 11 partitions 7.3 -> 5.7 us.
+constexpr int kMergeThreads = 256, kMergeElems = 4 * kMergeThreads;
+
 template <int D>
-__global__ __launch_bounds__(D) void merge_kernel(AttnParams p) {
-  const int H = p.num_heads;
-  const uint32_t wg = blockIdx.x;
-  const int mi = wg / H;
-  const int head = wg - mi * H;
+__global__ __launch_bounds__(kMergeThreads) void merge_kernel(AttnParams p, uint32_t chunks) {
+  const uint32_t row_elems = (uint32_t)p.num_heads * D;
+  const uint32_t mi = blockIdx.x / chunks;
+  const uint32_t e = (blockIdx.x - mi * chunks) * kMergeElems + threadIdx.x * 4u;
+  if (e >= row_elems) return;
   const MergeItem it = p.merge_items[mi];
-  const int d = threadIdx.x;
-  float M = kNegBig;
-  for (int k = 0; k < it.nparts; ++k)
-    M = __builtin_fmaxf(M, p.part_ml[((int64_t)(it.slot0 + k) * H + head) * 2]);
-  float L = 0.f, O = 0.f;
-  for (int k = 0; k < it.nparts; ++k) {
-    const int64_t ps = (int64_t)(it.slot0 + k) * H + head;
-    const float wgt = __builtin_amdgcn_exp2f(p.part_ml[ps * 2] - M);
-    L = __builtin_fmaf(p.part_ml[ps * 2 + 1], wgt, L);
-    O = __builtin_fmaf(p.part_o[ps * D + d], wgt, O);
+  const uint32_t head = e / D;
+  const float* po = p.part_o + (int64_t)it.slot0 * row_elems + e;
+  const float* pm = p.part_ml + ((int64_t)it.slot0 * p.num_heads + head) * 2;
+  float M = kNegBig, L = 0.f;
+  f32x4 O = {0.f, 0.f, 0.f, 0.f};
+  constexpr int kBatch = 4;
+  for (int k0 = 0; k0 < it.nparts; k0 += kBatch) {
+    f32x4 o[kBatch];
+    f32x2 ml[kBatch];
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      const int64_t part = min(k0 + k, it.nparts - 1);
+      ml[k] = *(const f32x2*)(pm + part * p.num_heads * 2);
+      o[k] = *(const f32x4*)(po + part * row_elems);
+    }
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      if (k0 + k >= it.nparts) break;
+      const float m_new = __builtin_fmaxf(M, ml[k][0]);
+      const float was = __builtin_amdgcn_exp2f(M - m_new), wgt = __builtin_amdgcn_exp2f(ml[k][0] - m_new);
+      M = m_new;
+      L = __builtin_fmaf(ml[k][1], wgt, L * was);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) O[i] = __builtin_fmaf(o[k][i], wgt, O[i] * was);
+    }
   }
-  p.out[((int64_t)it.qrow * H + head) * D + d] = (uint16_t)f32_to_bf16(O / L);
+  uint32_t out[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) out[i] = f32_to_bf16(O[i] / L);
+  *(u32x2*)(p.out + (int64_t)it.qrow * row_elems + e) = (u32x2){out[0] | (out[1] << 16), out[2] | (out[3] << 16)};
 }
 
 }  // namespace
@@ -141,13 +165,14 @@ hipError_t launch_row_persist_slim(const AttnParams& p, int head_dim, int slots,
 
 hipError_t launch_merge_kernel(const AttnParams& p, int head_dim, hipStream_t st) {
   if (p.n_merge_items <= 0) return hipSuccess;
-  const uint64_t grid = (uint64_t)p.n_merge_items * p.num_heads;
+  const uint32_t chunks = ((uint32_t)(p.num_heads * head_dim) + kMergeElems - 1) / kMergeElems;
+  const uint64_t grid = (uint64_t)p.n_merge_items * chunks;
   if (grid > 0x7fffffffull) return hipErrorInvalidValue;
-  const dim3 g((uint32_t)grid);
+  const dim3 g((uint32_t)grid), b(kMergeThreads);
   switch (head_dim) {
-    case 64: hipLaunchKernelGGL(merge_kernel<64>, g, dim3(64), 0, st, p); break;
-    case 128: hipLaunchKernelGGL(merge_kernel<128>, g, dim3(128), 0, st, p); break;
-    case 256: hipLaunchKernelGGL(merge_kernel<256>, g, dim3(256), 0, st, p); break;
+    case 64: hipLaunchKernelGGL(merge_kernel<64>, g, b, 0, st, p, chunks); break;
+    case 128: hipLaunchKernelGGL(merge_kernel<128>, g, b, 0, st, p, chunks); break;
+    case 256: hipLaunchKernelGGL(merge_kernel<256>, g, b, 0, st, p, chunks); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

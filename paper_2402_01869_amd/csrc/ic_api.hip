@@ -18,7 +18,7 @@ constexpr int kStagingSlots = 4;       // pinned host buffers cycled by successi
 // 4096 keys as ONE item each (no partial results, no merge pass) are 1 % faster than 2048-key items, alone and beside
 // the tile kernel; 512- and 1024-key items are 1-5 % slower (head_dim 256, GPT-J-shaped decode: 6 % slower at 512).
 constexpr int kDefaultRowPart = 4096;
-constexpr int kDefaultSpanPart = 8192; // keys per span-tile work item (partials of 256 rows are costly)
+constexpr int kWholeSpan = 1 << 30;    // span partition: none
 constexpr int kUnsplitWorkgroups = 1024;  // tile workgroups (4 per CU) from which spans are not split at all
 // Rows that see fewer keys than this stay off the matrix cores.  There the weights are rounded to bf16
 // before the PV product; with a handful of keys a single weight's rounding (2^-9 relative) shows in the
@@ -275,6 +275,59 @@ int choose_row_part(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes
   return best;
 }
 
+// Time of one 64-key step of a tile workgroup at the rate all 256 reach together (0.9 PFLOP/s, head_dim 256: 0.5); it
+// takes the same time however many of the tile's rows are live.
+double tile_step_us(int head_dim) {
+  return 4.0 * tile_rows(head_dim) * 64 * head_dim / ((head_dim > 128 ? 0.5e9 : 0.9e9) / kExpectedCus);
+}
+
+// Keys per span work item when the caller leaves the choice to the library: the partition expected to end soonest.
+// Splitting buys parallelism at the price of fp32 partial results for every row and a merge pass (4.5 us, and its bytes
+// written and read at some 4 TB/s; on the long-context shape, which has four rounds of whole tiles, 7 % of the call), so
+// it is looked at only when whole tiles give fewer than four rounds, and pays where one round is not full or the longest
+// tiles run alone at the end.  An item costs two steps besides its keys.  row_us: time of the row items, beside which
+// shorter spans gain nothing.  Measured: one 512-row chunk on 2500 keys, 64 heads over 8 K/V heads (128 whole tiles):
+// 98 ->
+// 62 us + 9 us of merge; 3 chunks of 67 rows on 8900 keys, 16 heads over 2 K/V heads: call 176 -> 34 us.
+int choose_span_part(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& ps, double row_us) {
+  const int H = pool->cfg.num_heads, D = pool->cfg.head_dim;
+  const int64_t n_th = H >> ps.tile_g_shift;
+  const double step_us = tile_step_us(D);
+  constexpr double kItemSteps = 2.0;
+  static const int parts[] = {kWholeSpan, 8192, 6144, 4096, 3072, 2560, 2048, 1536, 1280, 1024, 768, 640, 512, 384, 256};
+  int best = kWholeSpan;
+  double best_us = 0.0;
+  for (const int part : parts) {
+    int64_t items = 0, steps = 0, full = 0, most = 0, split_rows = 0;
+    for (int s = 0; s < d->num_seqs; ++s) {
+      const int c = d->ctx_len[s], n = d->q_len[s];
+      if (n == 1) continue;
+      for (int r0 = route(ps, c, n).n_few; r0 < n; r0 += ps.tile_rows) {
+        const int nr = std::min(ps.tile_rows, n - r0), klen = c - n + r0 + nr;
+        const int64_t np = (klen - 1) / part + 1;
+        items += np;
+        steps += (klen + 63) / 64;
+        full += klen / part;
+        most = std::max<int64_t>(most, (std::min(klen, part) + 63) / 64);
+        if (np > 1) split_rows += np * nr;
+      }
+    }
+    items *= n_th;
+    steps *= n_th;
+    full *= n_th;
+    double cost = std::max((double)most, (double)((full + kExpectedCus - 1) / kExpectedCus) * (std::min<double>(part, 64.0 * most) / 64)) + kItemSteps;
+    if (items > kExpectedCus) cost = std::max(cost, (steps + items * kItemSteps) / kExpectedCus + 0.5 * (most + kItemSteps));
+    double us = cost * step_us;
+    if (split_rows > 0) us += 4.5 + split_rows * H * (D + 2.0) * 4 * 2 / 4e6;
+    if (best_us == 0.0 || us < best_us) {
+      best = part;
+      best_us = us;
+    }
+    if (best_us <= row_us) break;
+  }
+  return best;
+}
+
 void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
   std::memset(&ps, 0, sizeof ps);
   // Grouped-query attention: the G = H / Hkv query heads of a group read the same keys.  When G is a
@@ -288,7 +341,7 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
   const int kTileRows = tile_rows(pool->cfg.head_dim) >> ps.tile_g_shift;
   ps.tile_rows = kTileRows;
   const ic_tuning& t = pool->tune;
-  ps.span_part = t.span_part_tokens > 0 ? round64(t.span_part_tokens) : kDefaultSpanPart;
+  ps.span_part = t.span_part_tokens > 0 ? round64(t.span_part_tokens) : kWholeSpan;
   ps.min_keys = t.mfma_min_keys > 0 ? std::min(t.mfma_min_keys, 64) : kMfmaMinKeys;  // <= the smallest partition
   ps.spans_as_rows = (t.span_kernel == 1);  // default: MFMA tiles
   ps.decode_as_tiles = ps.tile_g_shift > 0 && t.span_kernel == 2;
@@ -307,11 +360,11 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
   // layers: 30 us as row items, 36 as units.
   ps.few_as_units = !ps.spans_as_rows && (tiles > 0 || few * pool->cfg.num_heads > 2 * kExpectedCus);
   if (t.span_part_tokens == 0) {
-    // Splitting a span's keys buys parallelism at the price of fp32 partial results for every row
-    // and a merge pass (measured on the long-context shape: 7 % of the call).  When the unsplit query
-    // tiles already give every CU several workgroups, do not split.
     const int64_t head_groups = pool->cfg.num_heads >> ps.tile_g_shift;
-    if (tiles * head_groups >= kUnsplitWorkgroups) ps.span_part = 1 << 30;
+    double row_us = 0.0;
+    for (int s = 0; s < d->num_seqs; ++s)
+      if (d->q_len[s] == 1) row_us += d->ctx_len[s] * (4.0 * pool->cfg.head_dim * pool->cfg.num_kv_heads / 5.5e6);
+    ps.span_part = ps.spans_as_rows || tiles * head_groups >= kUnsplitWorkgroups ? kWholeSpan : choose_span_part(pool, d, ps, row_us);
   }
   ic_plan_info& in = ps.info;
   double tile_pairs = 0, row_keys = 0;  // (query row, key) pairs of the tile items; keys of the row items
@@ -357,11 +410,10 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
   // goes on the caller's stream, the other through the fork and join of the second stream.  (head_dim 256: 0.5 PFLOP/s.)
   ps.tile_leads = tile_pairs * H * (4.0 * D / (D > 128 ? 0.5e15 : 0.9e15)) > row_keys * pool->cfg.num_kv_heads * (4.0 * D / 5.5e12);
   // Two streams cost about 13 us on the way of the kernel that ends last (fork 7, join 6; kernels that follow each
-  // other on one stream start without a gap), so they pay only when the shorter kernel takes longer than that.  A tile
-  // workgroup's step of 64 keys takes the same time however many of its rows are live; a workgroup of the row kernels
-  // alone on its CU reads 40 GB/s.  Measured, two decode rows and two 32-row chunks of 4 heads: 45 us side by side,
+  // other on one stream start without a gap), so they pay only when the shorter kernel takes longer than that.
+  // A workgroup of the row kernels alone on its CU reads 40 GB/s.  Measured, two decode rows and two 32-row chunks of 4 heads: 45 us side by side,
   // 21 us one after the other.
-  const double step_us = 4.0 * tile_rows(D) * 64 * D / (D > 128 ? 0.5e15 / kExpectedCus : 0.9e15 / kExpectedCus) * 1e6;
+  const double step_us = tile_step_us(D);
   const int64_t n_th = H >> ps.tile_g_shift;
   const double tile_us = std::max((double)tile_steps * n_th / kExpectedCus, (double)most_steps) * step_us;
   const double key_bytes = 4.0 * D;  // K and V of one key and K/V head

@@ -20,6 +20,8 @@ namespace ic {
 namespace rowp {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr float kNegBig = -1.0e30f;  // finite "no key seen yet" maximum (keeps exp2(m - m) = 1)

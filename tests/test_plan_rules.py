@@ -36,3 +36,34 @@ def test_decode_rows_are_split_only_when_they_leave_the_chip_idle(H, Hkv, D, ctx
     assert plan["n_row_items"] == sum(-(-c // part) for c in ctx)
     forced = _plan(H, Hkv, D, ctx, [1] * len(ctx), decode_part_tokens=1024)   # the caller's choice stands
     assert forced["row_part_tokens"] == 1024
+
+
+@pytest.mark.parametrize("H,Hkv,D,ctx,q_len,split", [
+    (64, 8, 128, [3012], [512], True),                     # 128 workgroups of 48 steps on 256 CUs
+    (16, 2, 64, [8900] * 3, [67] * 3, True),
+    (4, 4, 256, [6000], [100], True),
+    (40, 40, 128, [512], [512], False),                    # a fresh chunk: the merge would cost more than it gives
+    (4, 4, 64, [128, 96], [32, 32], False),
+    (64, 8, 128, [3012] * 8, [512] * 8, False),            # four rounds of whole tiles
+    (40, 40, 128, [4000] * 100 + [3012], [1] * 100 + [512], False),   # the decode rows take longer anyway
+])
+def test_spans_are_split_only_when_their_tiles_leave_the_chip_idle(H, Hkv, D, ctx, q_len, split):
+    plan = _plan(H, Hkv, D, ctx, q_len)
+    part, longest = plan["span_part_tokens"], max(c for c, n in zip(ctx, q_len) if n > 1)
+    assert part % 64 == 0 and part >= 256
+    assert (part < longest) == split
+    assert (plan["partial_slots"] > 0) == split
+    whole = _plan(H, Hkv, D, ctx, q_len, span_part_tokens=1 << 20)      # the caller's choice stands
+    assert whole["span_part_tokens"] == 1 << 20 and whole["partial_slots"] == 0
+
+
+def test_few_key_rows_become_units_only_beside_tiles_or_in_numbers():
+    """Their row items stay in the plan either way; the units are a section of the image."""
+    tiny = _plan(16, 16, 256, [2, 2, 2, 20], [2, 2, 2, 1])      # 6 rows x 16 heads: the vector kernel's launch takes them
+    many = _plan(16, 16, 256, [60] * 4, [60] * 4)
+    beside = _plan(16, 16, 256, [2, 300], [2, 300])
+    for plan, rows in ((tiny, 7), (many, 240), (beside, 65)):
+        assert plan["n_row_items"] == rows == plan["n_vector_row_items"]
+    assert tiny["off_merge_items"] - tiny["off_tile_items"] < 256       # no tile items, no units
+    assert many["off_merge_items"] > many["off_tile_items"]             # units only
+    assert beside["off_merge_items"] - beside["off_tile_items"] >= 512  # both
