@@ -175,16 +175,19 @@ int ic_check_batch(const ic_pool_cfg* cfg, const ic_batch_desc* desc);
 /* Launch plan knobs.  Partition sizes are in tokens and are rounded up to a multiple of 64;
  * 0 keeps the built-in choice.  Smaller values force the split-KV path on short contexts. */
 typedef struct {
-  int32_t decode_part_tokens; /* keys per work item of a decode row (built-in: 4096)         */
-  int32_t span_part_tokens;   /* keys per work item of a span's query tile (built-in: 8192, or no split at all
-                                 when the unsplit tiles already give every CU four workgroups) */
+  int32_t decode_part_tokens; /* keys per work item of a decode row (built-in: 4096, or fewer when whole rows would
+                                 leave much of the chip idle)                                */
+  int32_t span_part_tokens;   /* keys per work item of a span's query tile (built-in: no split, unless whole tiles
+                                 would leave much of the chip idle)                          */
   int32_t span_kernel;        /* 0 = built-in choice (spans: MFMA tiles; decode rows: vector kernel, or the MFMA
                                  group kernel in a grouped-query pool), 1 = everything row by row on the vector
                                  kernel, 2 = MFMA tiles, in a grouped-query pool also for decode rows */
   int32_t row_variant;        /* vector-kernel build: bit 0 = prefetch two tiles ahead, bit 1 = cached (not non-temporal) KV loads */
-  int32_t serial_spans;       /* 1 = run the span kernel, then the row kernel, on the caller's stream instead of
-                                 two persistent kernels side by side (the tile kernel on the pool's own stream) */
-  int32_t row_launch;         /* single-role row kernel: 0 = built-in choice (persistent, one workgroup per CU),
+  int32_t serial_spans;       /* 1 = run the span kernel, then the row kernel, on the caller's stream; 0 = built-in
+                                 choice (large batches: two persistent kernels side by side, one on the process's
+                                 second stream)                                              */
+  int32_t row_launch;         /* single-role row kernel: 0 = built-in choice (persistent, one workgroup per CU, or
+                                 one workgroup per work item when the items are short),
                                  1 = one workgroup per work item, 2 = persistent, 3 = persistent, the slim
                                  builds that otherwise run beside the tile kernel (in a grouped-query pool of
                                  head_dim 128 with groups of up to 16: the slim group kernel)  */

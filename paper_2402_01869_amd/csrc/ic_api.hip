@@ -26,7 +26,12 @@ constexpr int kUnsplitWorkgroups = 1024;  // tile workgroups (4 per CU) from whi
 constexpr int kShareKeys = 8192;  // sequences at least this long keep their tile items side by side
 constexpr int kMfmaMinKeys = 64;
 constexpr int kExpectedCus = 256;        // the planner runs without a device; the launches use the device's own count
-constexpr double kSideBySideUs = 15.0;   // expected time of the shorter kernel from which a second stream pays
+// Mean K/V bytes of a row item below which one workgroup per item beats the persistent launch: its queue hands out one
+// item per 12.5 ns (atomics on one address), whatever the number of workgroups.  Measured, us per call, persistent /
+// one per item: head_dim 128, 8000 items of 16 keys 101 / 23, of 100 keys 119 / 71; 10240 of 200 keys (100 KB) 210 / 172,
+// 7800 of 300 keys 212 / 195, 2920 of 800 keys (400 KB) 187.5 / 188.2, 1440 of 1600 keys 179 / 184; head_dim 256, 3200
+// items of 48 keys 52 / 33, 3904 of 300 keys (300 KB) 189.3 / 189.5, 1456 of 800 keys 182 / 184.
+constexpr double kShortItemBytes = 300e3;
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -184,6 +189,7 @@ struct PlanSizes {
   bool decode_as_tiles;                // grouped pools, span_kernel = 2: decode rows as one-row tile items
   bool decode_as_group;                // grouped pools: decode rows stay row items, run by the group kernel
   bool side_by_side;                   // both kernels are long enough to pay for a second stream
+  bool short_rows;                     // the vector kernel's items are short: one workgroup each, no queue
   bool tile_leads;                     // the tile items are expected to take longer than the row items
   size_t off_ctr, off_bt_off, off_bt_flat, off_row, off_tile, off_few, off_merge, off_row_dst, image_bytes;
   size_t off_part_o, off_part_ml, total_bytes;
@@ -255,11 +261,13 @@ int choose_row_part(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes
   int best = kDefaultRowPart;
   double best_cost = 0.0;
   for (const int part : parts) {
+    if (part >= longest && part != kDefaultRowPart) continue;  // no other plan than whole rows
     int64_t n = 0, full = 0;
     for (int s = 0; s < d->num_seqs; ++s) {
       if (d->q_len[s] != 1) continue;
-      full += d->ctx_len[s] / part;
-      n += (d->ctx_len[s] + part - 1) / part;
+      const int whole = d->ctx_len[s] / part;
+      full += whole;
+      n += whole + (whole * part != d->ctx_len[s]);
     }
     n *= units;
     full *= units;
@@ -295,9 +303,12 @@ int choose_span_part(const ic_pool* pool, const ic_batch_desc* d, const PlanSize
   const double step_us = tile_step_us(D);
   constexpr double kItemSteps = 2.0;
   static const int parts[] = {kWholeSpan, 8192, 6144, 4096, 3072, 2560, 2048, 1536, 1280, 1024, 768, 640, 512, 384, 256};
-  int best = kWholeSpan;
+  int best = kWholeSpan, longest = 0;
+  for (int s = 0; s < d->num_seqs; ++s)
+    if (d->q_len[s] > 1) longest = std::max(longest, d->ctx_len[s]);
   double best_us = 0.0;
   for (const int part : parts) {
+    if (part >= longest && part != kWholeSpan) continue;  // no other plan than whole tiles
     int64_t items = 0, steps = 0, full = 0, most = 0, split_rows = 0;
     for (int s = 0; s < d->num_seqs; ++s) {
       const int c = d->ctx_len[s], n = d->q_len[s];
@@ -368,6 +379,7 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
   }
   ic_plan_info& in = ps.info;
   double tile_pairs = 0, row_keys = 0;  // (query row, key) pairs of the tile items; keys of the row items
+  double vec_keys = 0;                  // ... of those on the vector kernel
   int64_t tile_steps = 0, most_steps = 0, most_keys = 0;  // 64-key steps over all tile items and of the longest; keys of the longest row item
   for (int s = 0; s < d->num_seqs; ++s) {
     const int c = d->ctx_len[s], n = d->q_len[s];
@@ -385,6 +397,7 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
       in.row_items += parts;
       if (!rt.few_unit) {
         row_keys += klen;
+        if (i < rt.n_few || !rt.rest_group) vec_keys += klen;
         most_keys = std::max<int64_t>(most_keys, std::min(klen, ps.row_part));
       }
       if (i < rt.n_few || !rt.rest_group) ps.vec_items += parts;
@@ -409,16 +422,21 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
   // 0.9 PFLOP/s at 4 D flop per pair and head, row kernels 5.5 TB/s at 4 D bytes per key and K/V head): that one
   // goes on the caller's stream, the other through the fork and join of the second stream.  (head_dim 256: 0.5 PFLOP/s.)
   ps.tile_leads = tile_pairs * H * (4.0 * D / (D > 128 ? 0.5e15 : 0.9e15)) > row_keys * pool->cfg.num_kv_heads * (4.0 * D / 5.5e12);
-  // Two streams cost about 13 us on the way of the kernel that ends last (fork 7, join 6; kernels that follow each
-  // other on one stream start without a gap), so they pay only when the shorter kernel takes longer than that.
-  // A workgroup of the row kernels alone on its CU reads 40 GB/s.  Measured, two decode rows and two 32-row chunks of 4 heads: 45 us side by side,
-  // 21 us one after the other.
   const double step_us = tile_step_us(D);
   const int64_t n_th = H >> ps.tile_g_shift;
   const double tile_us = std::max((double)tile_steps * n_th / kExpectedCus, (double)most_steps) * step_us;
   const double key_bytes = 4.0 * D;  // K and V of one key and K/V head
+  // a workgroup of the row kernels alone on its CU reads 40 GB/s
   const double row_us = std::max(row_keys * pool->cfg.num_kv_heads * key_bytes / 5.5e6, (double)most_keys * key_bytes / 40e3);
-  ps.side_by_side = std::min(tile_us, row_us) > kSideBySideUs;
+  const int n_vec = ps.vec_items - ps.few_rows;
+  ps.short_rows = n_vec > 0 && vec_keys * key_bytes < n_vec * kShortItemBytes;
+  // Two streams cost a fork and a join (13 us on the way of the kernel that ends last; kernels on one stream follow each
+  // other without a gap), and each kernel takes longer beside the other than alone, so they pay only when the shorter
+  // one is long enough.  Measured, us a call side by side / one after the other (in brackets the expected time of the
+  // shorter kernel, us): 40 heads, head_dim 128: 43 / 16 (2), 79 / 95 (33), 226 / 247 (43), 91 / 107 (45), 303 / 328 (97);
+  // grouped, 64 over 8: 254 / 259 (29), 102 / 98 (43), 114 / 133 (47), 187 / 203 (94); head_dim 256: 132 / 146 (95), 308 /
+  // 363 (220).  Short rows, three times faster as one workgroup per item than from the queue: 105 / 101 (30), 150 / 122 (45).
+  ps.side_by_side = std::min(tile_us, row_us) > (ps.short_rows ? 110.0 : ps.decode_as_group || D > 128 ? 45.0 : 30.0);
   size_t o = 0;
   ps.off_ctr = o;     o = align_up(o + sizeof(int32_t) * 16, 256);
   ps.off_bt_off = o;  o = align_up(o + sizeof(int32_t) * (size_t)d->num_seqs, 256);
@@ -830,7 +848,10 @@ static int launch_attention(ic_pool* pool, const PlanSizes& ps, float scale, con
   const bool pair_ok = tiles && ps.side_by_side && !pool->tune.serial_spans;
   const bool beside_rows = pair_ok && p.n_vec_items > 0 && !ps.decode_as_group;
   const bool beside_group = pair_ok && n_group_items > 0 && D == 128 && p.group <= 16;
+  // One persistent row workgroup per CU; alone at head_dim 64, where a wave has half as many bytes in flight, two
+  // (5856 items of 800 keys: 259 -> 192 us, 2912 of 1600 keys: 239 -> 179 us).
   const int row_slots = pool->tune.row_slots > 0 ? pool->tune.row_slots : pool->num_cus;
+  const int alone_slots = pool->tune.row_slots > 0 || D > 64 ? row_slots : 2 * row_slots;
   if (beside_rows || beside_group) {
     if (!pool->side) {  // the stream is assigned last: a half-made set is retried by the next call
       if (!pool->ev_fork && hipEventCreateWithFlags(&pool->ev_fork, hipEventDisableTiming) != hipSuccess) return IC_EHIP;
@@ -897,9 +918,11 @@ static int launch_attention(ic_pool* pool, const PlanSizes& ps, float scale, con
     }
     if (p.n_vec_items > 0) {
       ProfScope ps_(pool, IC_K_ROW, st);
-      const hipError_t e = pool->tune.row_launch == 3 ? launch_row_persist_slim(p, D, row_slots, st)
-                           : pool->tune.row_launch != 1       ? launch_row_persist(p, D, row_slots, st)
-                                                              : launch_row_kernel(p, D, st);
+      const int how = pool->tune.row_launch;
+      const bool per_item = how == 1 || (how == 0 && pool->tune.row_slots == 0 && ps.short_rows);
+      const hipError_t e = how == 3 ? launch_row_persist_slim(p, D, row_slots, st)
+                           : per_item ? launch_row_kernel(p, D, st)
+                                      : launch_row_persist(p, D, alone_slots, st);
       if (e != hipSuccess) return IC_EHIP;
     }
   }
