@@ -286,9 +286,10 @@ int ic_check_ids(const ic_pool_cfg* cfg, const int32_t* host_ids, int32_t n, int
  * (ic_swap_limit_tokens), the rest of the sequence follows in later iterations (ic_swap_schedule).
  *
  * A swapper serves L pools of ONE shape (the L layers of a model; a multi-layer cache is L pools).
- * It owns two streams of default priority, one per direction (swap-out and swap-in run beside each
- * other), and cycles `num_stages` staging buffers, each max_blocks * kv_block_bytes() bytes, carved from the
- * caller's dev_staging.  Per layer l and list position i, with blk = kv_block_bytes():
+ * Swaps run on two streams of default priority, one per direction (swap-out and swap-in run beside each
+ * other), which all swappers of a process share per device; each direction of a swapper has a staging
+ * buffer of max_blocks * kv_block_bytes() bytes, carved from the caller's dev_staging.
+ * Per layer l and list position i, with blk = kv_block_bytes():
  *   kv_swap_out_layers:  host[l * layer_stride + i * blk ..+blk) <- pool_l[host_ids[i]]
  *   kv_swap_in_layers:   pool_l[host_ids[i]] <- host[l * layer_stride + i * blk ..+blk)   (ids distinct)
  * `host` is pinned host memory (ic_host_alloc, or any hipHostMalloc'ed block; pageable memory is
@@ -306,7 +307,7 @@ typedef struct ic_swapper ic_swapper;
 typedef struct {
   int32_t num_layers; /* L >= 1                                                        */
   int32_t max_blocks; /* most blocks one call may move per layer, >= 1                 */
-  int32_t num_stages; /* staging buffers cycled layer by layer, 2..8                   */
+  int32_t num_stages; /* staging buffers, 2..8 (one per direction is in use)           */
   int32_t reserved;   /* must be 0                                                     */
 } ic_swapper_cfg;
 

@@ -3,8 +3,8 @@
 // moved by the block gather / scatter kernels of kv_swap.hip and by the copy engines.
 //
 // Two streams of default priority, one per direction, each running its layers in order:
-//   out:  gather(pool_l -> stage), copy stage -> host, [record free(stage), done_l], next layer
-//   in:   copy host -> stage, scatter(stage -> pool_l), [record free(stage), done_l], next layer
+//   out:  gather(pool_l -> its staging buffer), copy to the host, [record done_l], next layer
+//   in:   copy host -> its staging buffer, scatter(-> pool_l), [record done_l], next layer
 // Nothing is ordered against the caller's stream except at the start of a call, so the whole
 // swap runs behind the forward pass, and the two directions (the link is full duplex, with a DMA
 // engine each way) run beside each other.  Within one direction the gather kernel of layer l+1
@@ -12,12 +12,23 @@
 // stream of its own would be the process's fifth (caller's, the attention call's side stream,
 // these two).  With the default of four hardware queues a fifth stream shares a queue with
 // another, and the attention call's tile kernel was measured waiting behind 3 ms transfers (call
-// time doubled, swap rate halved).
-// The staging buffers are handed out round-robin over both directions; free(stage) orders a
-// buffer's next user, whichever stream that is, after its last one.
+// time doubled, swap rate halved).  For the same reason the two streams are the process's (per
+// device), shared by all swappers: the two streams of a second swapper were found on one hardware
+// queue, where its directions took turns.
+// Every direction has one staging buffer of its own: within a direction a buffer's next user follows
+// its last one on the same stream, so more would not be used at the same time, and no direction ever
+// waits for a buffer of the other (handed out round-robin over both, the first layers of a swap-in
+// waited for the last ones of a swap-out queued before it).
+// 64 blocks x 4 layers each way, 13B shape, three swappers taking turns: 4.4 ms a pass, with a buffer
+// per direction 3.7 ms, with the streams shared as well 1.87 ms (45 GB/s each way at once), or 2.75 ms
+// where the runtime picks a slow engine for the copies out (seen in processes that freed device memory
+// before; see link_copy).  A kernel of 16 small workgroups that writes the blocks straight to the host
+// does not depend on the engine (2.4 ms), but the mixed 13B attention call beside it took 1.57 instead
+// of 1.11 ms.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -33,12 +44,6 @@ struct IdSlot {
   int32_t* host = nullptr;  // pinned mirror, max_blocks entries
   hipEvent_t ev = nullptr;  // recorded after the last kernel that reads the device copy
   bool pending = false;
-};
-
-struct Stage {
-  hipEvent_t free_ = nullptr;  // the buffer's last user is through with it
-  hipStream_t last = nullptr;  // the stream that recorded free_ (no wait needed from the same one)
-  bool used = false;
 };
 
 bool misaligned16(const void* p) { return ((uintptr_t)p & 15u) != 0; }
@@ -71,10 +76,8 @@ struct ic_swapper {
   size_t stage_bytes = 0;  // one staging buffer
   // runtime state, created by the first swap
   bool live = false;
-  hipStream_t s_out = nullptr, s_in = nullptr;
+  hipStream_t s_out = nullptr, s_in = nullptr;  // the device's, shared: never destroyed
   hipEvent_t ev_start = nullptr;
-  std::vector<Stage> stages;
-  int next_stage = 0;
   IdSlot ids[kIdSlots];
   int32_t* dev_ids = nullptr;  // kIdSlots lists of max_blocks
   int next_ids = 0;
@@ -84,16 +87,25 @@ struct ic_swapper {
 
 namespace {
 
+// The stream of one direction on the current device, for all swappers of the process; lives until it ends.
+hipStream_t shared_swap_stream(int direction) {
+  static std::mutex mu;
+  static hipStream_t streams[64][2] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
+  std::lock_guard<std::mutex> lock(mu);
+  hipStream_t& s = streams[dev][direction];
+  if (!s && hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) s = nullptr;
+  return s;
+}
+
 // Every object is created only if it is still missing, so a call that failed half-way is completed,
 // not repeated, by the next one.
 int init_runtime(ic_swapper* sw) {
   if (sw->live) return IC_OK;
-  if (!sw->s_out && hipStreamCreateWithFlags(&sw->s_out, hipStreamNonBlocking) != hipSuccess) return IC_EHIP;
-  if (!sw->s_in && hipStreamCreateWithFlags(&sw->s_in, hipStreamNonBlocking) != hipSuccess) return IC_EHIP;
+  if (!sw->s_out && !(sw->s_out = shared_swap_stream(IC_SWAP_OUT))) return IC_EHIP;
+  if (!sw->s_in && !(sw->s_in = shared_swap_stream(IC_SWAP_IN))) return IC_EHIP;
   if (!sw->ev_start && hipEventCreateWithFlags(&sw->ev_start, hipEventDisableTiming) != hipSuccess) return IC_EHIP;
-  for (Stage& s : sw->stages) {
-    if (!s.free_ && hipEventCreateWithFlags(&s.free_, hipEventDisableTiming) != hipSuccess) return IC_EHIP;
-  }
   for (int d = 0; d < 2; ++d)
     for (hipEvent_t& e : sw->done[d])
       if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return IC_EHIP;
@@ -121,14 +133,21 @@ int check_call(const ic_swapper* sw, const int32_t* host_ids, int32_t n, const v
   return IC_OK;
 }
 
-// One layer's blocks across the host link.  Issued as a pitched copy of n rows of one block each:
+// One layer's blocks across the host link.  Issued as a pitched copy of rows of a block or a part of one:
 // the runtime hands pitched copies that touch host memory to the DMA engines, whereas it may run a
 // flat hipMemcpyAsync as a copy kernel of one 8-wave workgroup per CU that stays resident for the
 // whole transfer and takes registers the attention kernels count on (measured: attention calls
 // running beside such copies took 1.8x as long).
+// At least 128 rows: where the runtime picks a slow engine for the copies out, 20 MiB in 64 rows took 0.62
+// ms, in 8 rows 1.2 ms, in 128 to 5120 rows 0.5 ms; on a fast engine all take 0.38 ms.
 hipError_t link_copy(void* dst, const void* src, size_t block_bytes, int32_t n, hipMemcpyKind kind,
                      hipStream_t st) {
-  return hipMemcpy2DAsync(dst, block_bytes, src, block_bytes, block_bytes, (size_t)n, kind, st);
+  size_t row = block_bytes, rows = (size_t)n;
+  while (rows < 128 && row > 4096 && row % 32 == 0) {  // rows stay multiples of 16 bytes
+    row /= 2;
+    rows *= 2;
+  }
+  return hipMemcpy2DAsync(dst, row, src, row, row, rows, kind, st);
 }
 
 // Copy the id list to the device on st; *dev receives the device copy, *slot the ring entry whose
@@ -191,7 +210,6 @@ int ic_swapper_create(const ic_swapper_cfg* cfg, ic_pool* const* layer_pools, vo
   sw->block_bytes = v0.block_bytes;
   sw->staging = (char*)dev_staging;
   sw->stage_bytes = stage_bytes;
-  sw->stages.resize((size_t)cfg->num_stages);
   for (int d = 0; d < 2; ++d) {
     sw->done[d].assign((size_t)cfg->num_layers, nullptr);
     sw->done_set[d].assign((size_t)cfg->num_layers, 0);
@@ -211,12 +229,7 @@ int ic_swapper_sync(ic_swapper* sw) {
 int ic_swapper_destroy(ic_swapper* sw) {
   if (!sw) return IC_ENULL;
   const int rc = ic_swapper_sync(sw);
-  if (sw->s_out) (void)hipStreamDestroy(sw->s_out);
-  if (sw->s_in) (void)hipStreamDestroy(sw->s_in);
   if (sw->ev_start) (void)hipEventDestroy(sw->ev_start);
-  for (Stage& s : sw->stages) {
-    if (s.free_) (void)hipEventDestroy(s.free_);
-  }
   for (int d = 0; d < 2; ++d)
     for (hipEvent_t e : sw->done[d])
       if (e) (void)hipEventDestroy(e);
@@ -242,19 +255,12 @@ int kv_swap_out_layers(ic_swapper* sw, const int32_t* host_ids, int32_t n, void*
   int32_t* dev_ids = nullptr;
   IdSlot* slot = nullptr;
   if ((rc = upload_ids(sw, st, host_ids, n, &dev_ids, &slot)) != IC_OK) return rc;
+  char* const buf = sw->staging + (size_t)IC_SWAP_OUT * sw->stage_bytes;
   for (int l = 0; l < sw->cfg.num_layers; ++l) {
-    const int si = sw->next_stage;
-    sw->next_stage = (si + 1) % sw->cfg.num_stages;
-    Stage& sg = sw->stages[si];
-    char* buf = sw->staging + (size_t)si * sw->stage_bytes;
-    if (sg.used && sg.last != st && hipStreamWaitEvent(st, sg.free_, 0) != hipSuccess) return IC_EHIP;
     if (launch_pack(sw->views[l].base, buf, dev_ids, n, sw->block_bytes, st) != hipSuccess) return IC_EHIP;
     if (link_copy((char*)pinned_host_dst + (size_t)l * layer_stride_bytes, buf, sw->block_bytes, n,
                   hipMemcpyDeviceToHost, st) != hipSuccess)
       return IC_EHIP;
-    if (hipEventRecord(sg.free_, st) != hipSuccess) return IC_EHIP;
-    sg.used = true;
-    sg.last = st;
     if (hipEventRecord(sw->done[IC_SWAP_OUT][l], st) != hipSuccess) return IC_EHIP;
     sw->done_set[IC_SWAP_OUT][l] = 1;
   }
@@ -276,19 +282,12 @@ int kv_swap_in_layers(ic_swapper* sw, const int32_t* host_ids, int32_t n, const 
   int32_t* dev_ids = nullptr;
   IdSlot* slot = nullptr;
   if ((rc = upload_ids(sw, st, host_ids, n, &dev_ids, &slot)) != IC_OK) return rc;
+  char* const buf = sw->staging + (size_t)IC_SWAP_IN * sw->stage_bytes;
   for (int l = 0; l < sw->cfg.num_layers; ++l) {
-    const int si = sw->next_stage;
-    sw->next_stage = (si + 1) % sw->cfg.num_stages;
-    Stage& sg = sw->stages[si];
-    char* buf = sw->staging + (size_t)si * sw->stage_bytes;
-    if (sg.used && sg.last != st && hipStreamWaitEvent(st, sg.free_, 0) != hipSuccess) return IC_EHIP;
     if (link_copy(buf, (const char*)pinned_host_src + (size_t)l * layer_stride_bytes, sw->block_bytes, n,
                   hipMemcpyHostToDevice, st) != hipSuccess)
       return IC_EHIP;
     if (launch_unpack(sw->views[l].base, buf, dev_ids, n, sw->block_bytes, st) != hipSuccess) return IC_EHIP;
-    if (hipEventRecord(sg.free_, st) != hipSuccess) return IC_EHIP;
-    sg.used = true;
-    sg.last = st;
     if (hipEventRecord(sw->done[IC_SWAP_IN][l], st) != hipSuccess) return IC_EHIP;
     sw->done_set[IC_SWAP_IN][l] = 1;
   }

@@ -250,3 +250,34 @@ def test_random_sequences_of_swaps_in_both_directions(seed):
         buf.close()
     for buf in keep:
         buf.close()
+
+
+def test_two_swappers_share_the_streams_and_keep_apart():
+    """Swappers of one process use the same two streams; calls of two swappers in flight together, both directions, and
+    the end of one while the other goes on."""
+    a, b = (Layers(3, 64, 5, 64, 12, stages, seed=60 + stages) for stages in (2, 4))
+    perm = np.random.default_rng(8).permutation(64).astype(np.int32)
+    src, dst = perm[:11], perm[11:22]
+    bufs = []
+    for ly in (a, b, a):
+        out, back = B.PinnedBuffer(3 * 11 * ly.bb), B.PinnedBuffer(3 * 11 * ly.bb)
+        back.array[:] = np.random.default_rng(len(bufs)).integers(0, 256, size=back.nbytes, dtype=np.uint8)
+        ly.sw.swap_out(src, out.ptr, 11 * ly.bb)
+        ly.sw.swap_in(dst, back.ptr, 11 * ly.bb)
+        bufs.append((ly, out, back))
+    for ly, out, back in bufs:
+        ly.sw.sync()
+        assert np.array_equal(out.array.reshape(3, -1), oracle.swap_out_layers(ly.host, src))
+    for ly, last in ((a, bufs[2]), (b, bufs[1])):
+        want = [h.copy() for h in ly.host]
+        oracle.swap_in_layers(want, dst, last[2].array.reshape(3, -1))
+        for l in range(3):
+            assert np.array_equal(ly.dev[l].cpu().numpy(), want[l]), l
+    a.close()
+    b.sw.swap_out(dst, bufs[1][1].ptr, 11 * b.bb)
+    b.sw.sync()
+    assert np.array_equal(bufs[1][1].array, bufs[1][2].array)
+    b.close()
+    for _, out, back in bufs:
+        out.close()
+        back.close()
