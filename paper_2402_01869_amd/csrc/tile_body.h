@@ -179,40 +179,41 @@ __device__ __forceinline__ void wave_step(const uint16_t* ks, const uint16_t* vs
   for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
     for (int i = 0; i < 16; ++i) tmax = __builtin_fmaxf(tmax, s_acc[tt][i]);
-  tmax = __builtin_fmaxf(tmax, __shfl_xor(tmax, 32));
+  tmax *= sc;
   // Lazy reference: the running maximum m only has to bound the scores loosely.  It is moved (and the
   // accumulators rescaled, 16 multiplies per 32 output rows) only when a score exceeds it by more than
   // kLazyLog2; until then weights may reach 2^kLazyLog2, which fp32 sums and bf16 weights hold easily.
-  const float m_cand = __builtin_fmaxf(m, tmax * sc);
-  const bool grew = m_cand > m + kLazyLog2;
-  const float m_new = grew ? m_cand : m;
-  const float alpha = grew ? __builtin_amdgcn_exp2f(m - m_cand) : 1.0f;
-  m = m_new;
+  // A lane looks at its own 32 scores; the two lanes of a column meet only when some lane of the wave has to move
+  // (LAZYFIG).
+  if (__builtin_amdgcn_ballot_w64(tmax > m + kLazyLog2) != 0) {
+    tmax = __builtin_fmaxf(tmax, __shfl_xor(tmax, 32));
+    const float m_cand = __builtin_fmaxf(m, tmax);
+    const bool grew = m_cand > m + kLazyLog2;  // the same in both lanes of a column
+    const float alpha = grew ? __builtin_amdgcn_exp2f(m - m_cand) : 1.0f;
+    m = grew ? m_cand : m;
+    l *= alpha;
+#pragma unroll
+    for (int dt = 0; dt < G::kDTiles; ++dt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc_o[dt][i] *= alpha;
+  }
   // Weights: rounded to bf16 in pairs (one v_cvt_pk_bf16_f32), and summed AS ROUNDED by a bf16 dot
   // product with (1, 1): the normaliser then counts exactly what the matrix core will multiply, so
   // the output stays an exact convex combination of the values and a row dominated by one key
   // (short contexts) does not inherit the 2^-9 relative rounding error of its weight.
-  float psum = 0.f;
   bf16x8 pb[4];
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
   for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
     for (int i = 0; i < 16; i += 2) {
-      const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_acc[tt][i], sc, -m_new));
-      const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_acc[tt][i + 1], sc, -m_new));
+      const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_acc[tt][i], sc, -m));
+      const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_acc[tt][i + 1], sc, -m));
       const bf16x2 pr = {(__bf16)p0, (__bf16)p1};
-      psum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, psum, false);
+      l = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, l, false);
       pb[2 * tt + i / 8][i % 8] = pr[0];
       pb[2 * tt + i / 8][i % 8 + 1] = pr[1];
     }
-  l = l * alpha + psum;
-  if (__builtin_amdgcn_ballot_w64(grew) != 0) {  // rescale only when some row's maximum moved
-#pragma unroll
-    for (int dt = 0; dt < G::kDTiles; ++dt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc_o[dt][i] *= alpha;
-  }
   // O^T += V^T P^T, k-step outer so that the kDTiles independent accumulators alternate
   {
     const int lane = col + 32 * hl;
