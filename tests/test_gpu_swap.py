@@ -174,3 +174,20 @@ def test_repeated_and_changing_id_lists():
     pool.kv_unpack_blocks(a, staging.data_ptr(), staging.numel())
     torch.cuda.synchronize()
     pool.close()
+
+
+def test_uploads_in_flight_while_the_pinned_buffers_come_round():
+    """Each call brings another list, none is waited for: the lists fill the pool's four pinned buffers one after the
+    other and the first is used again while earlier copies out of it may still be queued."""
+    nb, H, D, n = 4096, 1, 64, 1000          # a list of 1000 ids: 70 to a pinned buffer of 288 KiB
+    pool_t = torch.randint(-2 ** 15, 2 ** 15, (nb, 2, H, 16, D), dtype=torch.int16, device=DEV)
+    pool = B.KvPool.from_tensor(pool_t, H, D)
+    rng = np.random.default_rng(3)
+    lists = [rng.integers(0, nb, size=n).astype(np.int32) for _ in range(330)]
+    out = torch.zeros((len(lists), n, 2 * H * 16 * D), dtype=torch.int16, device=DEV)
+    for i, ids in enumerate(lists):
+        pool.kv_pack_blocks(ids, out[i].data_ptr(), out[i].numel() * 2)
+    pool.close()                              # waits for what is queued
+    flat = pool_t.reshape(nb, -1)
+    for i, ids in enumerate(lists):
+        assert torch.equal(out[i], flat[torch.from_numpy(ids.astype(np.int64)).to(DEV)]), i
