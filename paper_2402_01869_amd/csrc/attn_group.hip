@@ -13,6 +13,7 @@
 //     (same operand layouts, V through the LDS transpose loads).
 // At the end the four waves' (m, l, O) are combined through LDS and written as bf16 rows, or as
 // split-KV partial results for the merge kernel.
+#include "merge_body.h"
 #include "tile_body.h"
 
 namespace ic {
@@ -147,7 +148,7 @@ __device__ __forceinline__ void group_step(const uint16_t* ks, const uint16_t* v
 }
 
 template <int D>
-__device__ __forceinline__ void group_body(const AttnParams& p, const RowItem& it, int kvh, uint16_t* lds) {
+__device__ __forceinline__ void group_body(const AttnParams& p, const RowItem& it, int kvh, uint16_t* lds, int* s_last) {
   using G = TG<D>;
   const int H = p.num_heads, Hk = p.num_kv_heads, Gq = p.group;  // Gq <= 32 query heads per K/V head
   const int tid = threadIdx.x;
@@ -234,24 +235,26 @@ __device__ __forceinline__ void group_body(const AttnParams& p, const RowItem& i
       p.out[((int64_t)it.qrow * H + hq) * D + d] = __builtin_bit_cast(uint16_t, o);
     } else {
       const int64_t ps = (int64_t)it.slot * H + hq;
-      p.part_o[ps * D + d] = O;
+      mergep::store_shared(&p.part_o[ps * D + d], O);
       if (d == 0) {
-        p.part_ml[ps * 2] = M;
-        p.part_ml[ps * 2 + 1] = L;
+        mergep::store_shared(&p.part_ml[ps * 2], M);
+        mergep::store_shared(&p.part_ml[ps * 2 + 1], L);
       }
     }
   }
+  if (it.slot >= 0 && p.split_units > 0) mergep::finish_split<D, 4>(p, it.slot, kvh, kvh * Gq, Gq, s_last);
 }
 
 template <int D>
 __global__ __launch_bounds__(64 * kGroupWaves, (D <= 128 ? 2 : 1)) void group_attn_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[group_lds_bytes<D>() / 2];
+  __shared__ int s_last;
   const int Hk = p.num_kv_heads;
   const uint32_t wg = blockIdx.x;
   const int item_idx = wg / Hk;
   const int kvh = wg - item_idx * Hk;
   const RowItem it = p.row_items[p.group_first + item_idx];
-  group_body<D>(p, it, kvh, lds);
+  group_body<D>(p, it, kvh, lds, &s_last);
 }
 
 }  // namespace

@@ -12,12 +12,13 @@ using namespace rowp;
 template <int D, int PF, bool NT>
 __global__ __launch_bounds__(kRowWaves * 64) void row_attn_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(16))) float lds[row_lds_bytes<D>() / sizeof(float)];
+  __shared__ int s_last;
   const int H = p.num_heads;
   const uint32_t wg = blockIdx.x;
   const int item_idx = wg / H;
   const int head = wg - item_idx * H;
   const RowItem it = p.row_items[item_idx];
-  row_body<D, PF, NT>(p, it, head, lds);
+  row_body<D, PF, NT, false, true>(p, it, head, lds, &s_last);
 }
 
 // Persistent launch of the same body: `slots` workgroups (one per CU) pull (item, head) pairs from a
@@ -42,51 +43,20 @@ __global__ __launch_bounds__(kRowWaves * 64) void row_persist_kernel(AttnParams 
   queue_leave(p.counters, kCtrRowQueue, 1, -1, kCtrRowLeft);
 }
 
-// Split-KV merge: out = sum_p o_p 2^(m_p - m) / sum_p l_p 2^(m_p - m), m = max_p m_p.
+// Merge pass for the rows of split tiles, and for split decode rows that their last partition has not merged (merge_body.h).
 // The partial results of a row are [H][D] fp32 per partition, contiguous: a workgroup of 256 threads takes 1024
-// consecutive values of one row, 16 bytes per thread and load.  Bound by memory (and, for a handful of rows, by latency:
-// launch, merge item, one round of loads), so the partitions are read four at a time, values and (m, l) together, and
-// combined in ascending order with a running maximum.  Measured against one workgroup of D threads per (row, head), which
-// read 4 bytes per thread and needed the maximum before the first value: 8 rows of 64 heads in 2 to 11 partitions 7.3 -> 5.7 us.
+// consecutive values of one row, 16 bytes per thread and load.  Bound by memory.  Measured against one workgroup of D
+// threads per (row, head), which read 4 bytes per thread and needed the maximum before the first value: 8 rows of 64
+// heads in 2 to 11 partitions 7.3 -> 5.7 us.
 constexpr int kMergeThreads = 256, kMergeElems = 4 * kMergeThreads;
 
 template <int D>
 __global__ __launch_bounds__(kMergeThreads) void merge_kernel(AttnParams p, uint32_t chunks) {
-  const uint32_t row_elems = (uint32_t)p.num_heads * D;
   const uint32_t mi = blockIdx.x / chunks;
   const uint32_t e = (blockIdx.x - mi * chunks) * kMergeElems + threadIdx.x * 4u;
-  if (e >= row_elems) return;
-  const MergeItem it = p.merge_items[mi];
-  const uint32_t head = e / D;
-  const float* po = p.part_o + (int64_t)it.slot0 * row_elems + e;
-  const float* pm = p.part_ml + ((int64_t)it.slot0 * p.num_heads + head) * 2;
-  float M = kNegBig, L = 0.f;
-  f32x4 O = {0.f, 0.f, 0.f, 0.f};
-  constexpr int kBatch = 4;
-  for (int k0 = 0; k0 < it.nparts; k0 += kBatch) {
-    f32x4 o[kBatch];
-    f32x2 ml[kBatch];
-#pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      const int64_t part = min(k0 + k, it.nparts - 1);
-      ml[k] = *(const f32x2*)(pm + part * p.num_heads * 2);
-      o[k] = *(const f32x4*)(po + part * row_elems);
-    }
-#pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      if (k0 + k >= it.nparts) break;
-      const float m_new = __builtin_fmaxf(M, ml[k][0]);
-      const float was = __builtin_amdgcn_exp2f(M - m_new), wgt = __builtin_amdgcn_exp2f(ml[k][0] - m_new);
-      M = m_new;
-      L = __builtin_fmaf(ml[k][1], wgt, L * was);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) O[i] = __builtin_fmaf(o[k][i], wgt, O[i] * was);
-    }
-  }
-  uint32_t out[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) out[i] = f32_to_bf16(O[i] / L);
-  *(u32x2*)(p.out + (int64_t)it.qrow * row_elems + e) = (u32x2){out[0] | (out[1] << 16), out[2] | (out[3] << 16)};
+  if (e >= (uint32_t)p.num_heads * D) return;
+  const MergeItem it = p.merge_items[p.merge_first + mi];
+  mergep::merge_four<D, 4, false>(p, it.qrow, it.slot0, it.nparts, e);
 }
 
 }  // namespace

@@ -1,6 +1,7 @@
 // C ABI, host-side validation and launch planning for the intercept hot path.
 // See include/infercept_hot.h for the contract of every entry point.
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <memory>
 #include <mutex>
@@ -175,7 +176,7 @@ bool destinations_distinct(const ic_pool_cfg& cfg, const int32_t* dst, size_t ro
 // ---------------------------------------------------------------------------------------
 // Launch plan.  Sizes only (plan_sizes) or the filled descriptor image (plan_fill).
 // Device image layout (all sections 256-byte aligned, in this order):
-//   counters[16] | bt_off[num_seqs] | bt_flat[table_entries] | row_items | tile_items | few_items | merge_items | row_dst
+//   counters[16] | bt_off[num_seqs] | bt_flat[table_entries] | row_items | tile_items | few_items | merge_items | row_dst | slot_merge | arrived
 // followed in the workspace by part_o[slots][H][D] and part_ml[slots][H][2].
 // ---------------------------------------------------------------------------------------
 struct PlanSizes {
@@ -190,9 +191,10 @@ struct PlanSizes {
   bool decode_as_tiles;                // grouped pools, span_kernel = 2: decode rows as one-row tile items
   bool decode_as_group;                // grouped pools: decode rows stay row items, run by the group kernel
   bool side_by_side;                   // both kernels are long enough to pay for a second stream
-  bool short_rows;                     // the vector kernel's items are short: one workgroup each, no queue
+  bool row_per_item;                   // the vector kernel's items are short, or split by choose_row_part: one workgroup each, no queue
   bool tile_leads;                     // the tile items are expected to take longer than the row items
-  size_t off_ctr, off_bt_off, off_bt_flat, off_row, off_tile, off_few, off_merge, off_row_dst, image_bytes;
+  size_t off_ctr, off_bt_off, off_bt_flat, off_row, off_tile, off_few, off_merge, off_row_dst, off_slot_merge, off_arrived, image_bytes;
+  int row_slots, row_merges;           // partial slots and merge items of split decode rows: the first of each
   size_t off_part_o, off_part_ml, total_bytes;
 };
 
@@ -233,20 +235,28 @@ SeqRoute route(const PlanSizes& ps, int c, int n) {
 }
 
 // Keys per decode work item when the caller leaves the choice to the library.  Whole rows (up to kDefaultRowPart keys)
-// as long as they give every workgroup of the launch several items; fewer, and most of the chip would idle while the
-// longest rows run: then the partition that is expected to end soonest.  Time is counted in keys a workgroup reads at
-// its share of the memory's rate, 26 (row kernel) or 13 GB/s (group kernel: two workgroups per CU).  An item costs 2 us
-// besides its keys, a split 4.5 us for the merge pass; items of a round that is not full leave the rest idle.
-// Measured: one row of 3000 keys, 40 heads, head_dim 128: row kernel 44 -> 13.4 us
-// (+ 3.9 us of merge); 8 rows of 1000..8000 keys, 64 heads over 8 K/V heads: group kernel 58.8 -> 33.4 us (merge 4.5 -> 7.3).
+// as long as they give every workgroup two items; fewer, and part of the chip may idle while the longest rows run: then
+// the partition that is expected to end soonest.  The model, in us:
+//   - the keys' bytes at 6.6 TB/s, or at what the launch's workgroups reach where they are few; a workgroup alone on its
+//     CU reads 22 / 38 / 50 GB/s at head_dim 64 / 128 / 256 (one tile of K and V in flight per wave), and that is the
+//     least the longest item takes; the group kernel's, two to a CU, reach 6.6 TB/s times the root of their share of the
+//     places (measured 3.2 TB/s at 112 of 512, 4.4 expected and 5.2 measured at 224); a quarter of the longest item's
+//     time comes on top, for the end where only the longest are left, half from a second round on;
+//   - 3.5 us between two items of a persistent workgroup (whole rows), 1 us per round of the others, which overlap;
+//   - a split: 1.5 us, and 0.8 us for every four partitions the last one has to read back.
+// Measured per layer, with the append (us), chosen partition / whole rows: 13B shape, one row of 3000 keys 18 (512) / 45,
+// 4 of 1000..2000 33 (1536) / 36, 10 of 1000..3000 76 (1024) / 75.5; GPT-J shape, 2 of 2000 22 (384) / 44, 16 of 512..2048
+// 66 (640) / 64; 70B shape, one of 6000 16.5 (384) / 61, 8 of 1000..8000 40 (768) / 66, 32 of 1000..5000 75 (768) / 80;
+// 32 heads of 64 dims, 8 of 1000..3000 31 (768) / 40.  From two rounds on whole rows win: 13B shape, 20 rows of 500..3000
+// 115, in partitions of 1024 keys 123.
 int choose_row_part(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& ps) {
   const bool group = ps.decode_as_group;
+  const int D = pool->cfg.head_dim;
   const int64_t units = group ? pool->cfg.num_kv_heads : pool->cfg.num_heads;
   bool spans = false;
   for (int s = 0; s < d->num_seqs && !spans; ++s) spans = d->q_len[s] > 1;
-  const bool two = group && !spans;  // two group workgroups per CU; beside a tile workgroup one
-  const int64_t slots = two ? 2 * kExpectedCus : kExpectedCus;
-  const int64_t enough = 4 * slots;
+  const int64_t slots = group && !spans ? 2 * kExpectedCus : kExpectedCus;  // two group workgroups per CU; beside a tile workgroup one
+  const int64_t enough = 2 * slots;
   int64_t items = 0, keys = 0;
   int longest = 0;
   for (int s = 0; s < d->num_seqs && items * units < enough; ++s) {
@@ -256,29 +266,24 @@ int choose_row_part(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes
     longest = std::max(longest, d->ctx_len[s]);
   }
   if (items == 0 || items * units >= enough) return kDefaultRowPart;
-  const double keys_per_us = (two ? 13e3 : 26e3) / (4.0 * pool->cfg.head_dim);
-  const double item_cost = 2.0 * keys_per_us, split_cost = 4.5 * keys_per_us;
+  const double key_bytes = 4.0 * D, alone = D == 64 ? 22e3 : D == 128 ? 38e3 : 50e3;  // bytes per us
   static const int parts[] = {kDefaultRowPart, 3072, 2048, 1536, 1280, 1024, 768, 640, 512, 448, 384, 320, 256, 192, 128};
   int best = kDefaultRowPart;
-  double best_cost = 0.0;
+  double best_us = 0.0;
   for (const int part : parts) {
     if (part >= longest && part != kDefaultRowPart) continue;  // no other plan than whole rows
-    int64_t n = 0, full = 0;
-    for (int s = 0; s < d->num_seqs; ++s) {
-      if (d->q_len[s] != 1) continue;
-      const int whole = d->ctx_len[s] / part;
-      full += whole;
-      n += whole + (whole * part != d->ctx_len[s]);
-    }
+    int64_t n = 0;
+    for (int s = 0; s < d->num_seqs; ++s)
+      if (d->q_len[s] == 1) n += (d->ctx_len[s] + part - 1) / part;
     n *= units;
-    full *= units;
-    const double most = std::min(longest, part) + item_cost;
-    double cost = std::max(most, (double)((full + slots - 1) / slots) * (part + item_cost));
-    if (n > slots) cost = std::max(cost, (keys * units + n * item_cost) / slots + 0.5 * most);
-    if (longest > part) cost += split_cost;
-    if (best_cost == 0.0 || cost < best_cost) {
+    const double last = std::min(longest, part) * key_bytes / alone;
+    const double rate = group ? 6.6e6 * std::min(1.0, std::sqrt((double)n / slots)) : std::min(6.6e6, 0.8 * alone * n);
+    double us = std::max(last, keys * units * key_bytes / rate) + (n > slots ? 0.5 : 0.25) * last;
+    us += (part == kDefaultRowPart && !group ? 3.5 : 1.0) * n / slots;
+    if (longest > part) us += 1.5 + 0.8 * ((longest + 4 * part - 1) / (4 * part));
+    if (best_us == 0.0 || us < std::min(0.985 * best_us, best_us - 0.5)) {
       best = part;
-      best_cost = cost;
+      best_us = us;
     }
   }
   return best;
@@ -338,6 +343,18 @@ int choose_span_part(const ic_pool* pool, const ic_batch_desc* d, const PlanSize
     if (best_us <= row_us) break;
   }
   return best;
+}
+
+// Units of a split decode row that are merged by their last partition: K/V heads on the group kernel, query heads on the
+// vector kernel (in a pool whose decode rows are the group kernel's, the vector kernel only has rows too short to
+// split).  0: the merge kernel merges them.  A partition's end takes 2-3 us longer that way (its stores have to reach
+// memory, then a counter), which overlaps only where several workgroups share a CU: on the launches of one workgroup
+// per item, which are the ones choose_row_part splits for.  From the queue of a persistent kernel it adds up: 44 rows
+// of 600..10200 keys, 40 heads, in 4096-key items 729 us a layer against 710 with the merge kernel.
+int split_units(const ic_pool* pool, const PlanSizes& ps) {
+  const ic_tuning& t = pool->tune;
+  if (t.decode_part_tokens > 0 || t.row_launch > 1 || t.row_slots > 0 || ps.row_part >= kDefaultRowPart || ps.side_by_side) return 0;
+  return ps.decode_as_group ? pool->cfg.num_kv_heads : pool->cfg.num_heads;
 }
 
 void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
@@ -402,7 +419,7 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
         most_keys = std::max<int64_t>(most_keys, std::min(klen, ps.row_part));
       }
       if (i < rt.n_few || !rt.rest_group) ps.vec_items += parts;
-      if (parts > 1) { in.partial_slots += parts; in.merge_rows += 1; }
+      if (parts > 1) { in.partial_slots += parts; in.merge_rows += 1; ps.row_slots += parts; ps.row_merges += 1; }
     }
     if (!rt.rest_rows) {
       const int part = n == 1 ? ps.row_part : ps.span_part;
@@ -430,14 +447,15 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
   // a workgroup of the row kernels alone on its CU reads 40 GB/s
   const double row_us = std::max(row_keys * pool->cfg.num_kv_heads * key_bytes / 5.5e6, (double)most_keys * key_bytes / 40e3);
   const int n_vec = ps.vec_items - ps.few_rows;
-  ps.short_rows = n_vec > 0 && vec_keys * key_bytes < n_vec * kShortItemBytes;
+  const bool short_rows = n_vec > 0 && vec_keys * key_bytes < n_vec * kShortItemBytes;
+  ps.row_per_item = short_rows || (t.decode_part_tokens == 0 && ps.row_part < kDefaultRowPart);
   // Two streams cost a fork and a join (13 us on the way of the kernel that ends last; kernels on one stream follow each
   // other without a gap), and each kernel takes longer beside the other than alone, so they pay only when the shorter
   // one is long enough.  Measured, us a call side by side / one after the other (in brackets the expected time of the
   // shorter kernel, us): 40 heads, head_dim 128: 43 / 16 (2), 79 / 95 (33), 226 / 247 (43), 91 / 107 (45), 303 / 328 (97);
   // grouped, 64 over 8: 254 / 259 (29), 102 / 98 (43), 114 / 133 (47), 187 / 203 (94); head_dim 256: 132 / 146 (95), 308 /
   // 363 (220).  Short rows, three times faster as one workgroup per item than from the queue: 105 / 101 (30), 150 / 122 (45).
-  ps.side_by_side = std::min(tile_us, row_us) > (ps.short_rows ? 110.0 : ps.decode_as_group || D > 128 ? 45.0 : 30.0);
+  ps.side_by_side = std::min(tile_us, row_us) > (short_rows ? 110.0 : ps.decode_as_group || D > 128 ? 45.0 : 30.0);
   size_t o = 0;
   ps.off_ctr = o;     o = align_up(o + sizeof(int32_t) * 16, 256);
   ps.off_bt_off = o;  o = align_up(o + sizeof(int32_t) * (size_t)d->num_seqs, 256);
@@ -447,6 +465,8 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
   ps.off_few = o;     o = align_up(o + sizeof(FewItem) * (size_t)ps.few_runs, 256);
   ps.off_merge = o;   o = align_up(o + sizeof(MergeItem) * (size_t)in.merge_rows, 256);
   ps.off_row_dst = o; o = align_up(o + sizeof(int32_t) * (size_t)d->total_q_rows, 256);  // for kv_write_span_planned
+  ps.off_slot_merge = o; o = align_up(o + sizeof(int32_t) * (size_t)ps.row_slots, 256);
+  ps.off_arrived = o;    o = align_up(o + sizeof(int32_t) * (size_t)ps.row_merges * split_units(pool, ps), 256);
   ps.image_bytes = o;
   ps.off_part_o = o;  o = align_up(o + sizeof(float) * (size_t)in.partial_slots * H * D, 256);
   ps.off_part_ml = o; o = align_up(o + sizeof(float) * (size_t)in.partial_slots * H * 2, 256);
@@ -457,6 +477,8 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
 void plan_fill(const ic_batch_desc* d, const PlanSizes& ps, char* img) {
   const int kTileRows = ps.tile_rows;
   std::memset(img + ps.off_ctr, 0, sizeof(int32_t) * 16);  // work-queue counters start at zero
+  std::memset(img + ps.off_arrived, 0, ps.image_bytes - ps.off_arrived);
+  int32_t* slot_merge = (int32_t*)(img + ps.off_slot_merge);
   int32_t* bt_off = (int32_t*)(img + ps.off_bt_off);
   int32_t* bt_flat = (int32_t*)(img + ps.off_bt_flat);
   RowItem* rows = (RowItem*)(img + ps.off_row);
@@ -465,14 +487,15 @@ void plan_fill(const ic_batch_desc* d, const PlanSizes& ps, char* img) {
   MergeItem* merges = (MergeItem*)(img + ps.off_merge);
   {
     int32_t* row_dst = (int32_t*)(img + ps.off_row_dst);
-    std::fill(row_dst, row_dst + (ps.image_bytes - ps.off_row_dst) / sizeof(int32_t), -1);
+    std::fill(row_dst, row_dst + (ps.off_slot_merge - ps.off_row_dst) / sizeof(int32_t), -1);
     append_destinations(d, row_dst);
   }
   int64_t nbt = 0;
   // vector items first, then the rows of the few-key units, then the group kernel's items
   const int few_first = ps.vec_items - ps.few_rows;
   int nvec = 0, nfew = few_first, ngrp = ps.vec_items, nruns = 0;
-  int ntiles = 0, nmerge = 0, slot = 0;
+  // the split decode rows' slots and merge items come before those of split tiles
+  int ntiles = 0, nmerge = ps.row_merges, slot = ps.row_slots, nrmerge = 0, rslot = 0;
   std::vector<int> tile_slot0, tile_parts;
   for (int s = 0; s < d->num_seqs; ++s) {
     const int c = d->ctx_len[s], n = d->q_len[s];
@@ -489,14 +512,17 @@ void plan_fill(const ic_batch_desc* d, const PlanSizes& ps, char* img) {
       const int parts = (klen + ps.row_part - 1) / ps.row_part;
       const int qrow = d->q_start[s] + i;
       const bool vec = i < rt.n_few || !rt.rest_group;
-      if (parts > 1) merges[nmerge++] = MergeItem{qrow, slot, parts, 0};
+      if (parts > 1) {
+        for (int k = 0; k < parts; ++k) slot_merge[rslot + k] = nrmerge;
+        merges[nrmerge++] = MergeItem{qrow, rslot, parts, 0};
+      }
       for (int k = 0; k < parts; ++k) {
         RowItem& it = rows[rt.few_unit ? nfew++ : vec ? nvec++ : ngrp++];
         it.seq = s;
         it.qrow = qrow;
         it.k_begin = k * ps.row_part;
         it.k_end = std::min(klen, (k + 1) * ps.row_part);
-        it.slot = parts > 1 ? slot++ : -1;
+        it.slot = parts > 1 ? rslot++ : -1;
         it.pad[0] = it.pad[1] = it.pad[2] = 0;
       }
     }
@@ -831,6 +857,8 @@ static int launch_attention(ic_pool* pool, const PlanSizes& ps, float scale, con
   p.tile_items = (const TileItem*)(ws + ps.off_tile);
   p.few_items = (const FewItem*)(ws + ps.off_few);
   p.merge_items = (const MergeItem*)(ws + ps.off_merge);
+  p.slot_merge = (const int32_t*)(ws + ps.off_slot_merge);
+  p.arrived = (int32_t*)(ws + ps.off_arrived);
   p.part_o = (float*)(ws + ps.off_part_o);
   p.part_ml = (float*)(ws + ps.off_part_ml);
   p.num_heads = pool->cfg.num_heads;
@@ -842,7 +870,9 @@ static int launch_attention(ic_pool* pool, const PlanSizes& ps, float scale, con
   p.group_first = ps.vec_items;
   p.n_tile_items = ps.info.tile_items;
   p.n_few_items = ps.few_runs;
-  p.n_merge_items = ps.info.merge_rows;
+  p.split_units = split_units(pool, ps);
+  p.merge_first = p.split_units > 0 ? ps.row_merges : 0;
+  p.n_merge_items = ps.info.merge_rows - p.merge_first;
   p.scale_log2e = scale * 1.4426950408889634f;
   p.row_variant = pool->tune.row_variant;
   p.tile_first = 0;
@@ -931,7 +961,7 @@ static int launch_attention(ic_pool* pool, const PlanSizes& ps, float scale, con
     if (p.n_vec_items > 0) {
       ProfScope ps_(pool, IC_K_ROW, st);
       const int how = pool->tune.row_launch;
-      const bool per_item = how == 1 || (how == 0 && pool->tune.row_slots == 0 && ps.short_rows);
+      const bool per_item = how == 1 || (how == 0 && pool->tune.row_slots == 0 && ps.row_per_item);
       const hipError_t e = how == 3 ? launch_row_persist_slim(p, D, row_slots, st)
                            : per_item ? launch_row_kernel(p, D, st)
                                       : launch_row_persist(p, D, alone_slots, st);

@@ -75,7 +75,9 @@ struct AttnParams {
   const RowItem* row_items;
   const TileItem* tile_items;
   const FewItem* few_items;
-  const MergeItem* merge_items;
+  const MergeItem* merge_items;  // split decode rows first (merged by their last partition), then rows of split tiles
+  const int32_t* slot_merge;  // merge item of each of the split decode rows' partial slots
+  int32_t* arrived;        // [split decode rows][split_units] partitions that are through, zero between launches
   float* part_o;           // [slots][H][D] unnormalised partial outputs
   float* part_ml;          // [slots][H][2] (running max in log2 units, normaliser)
   int32_t num_heads;       // query heads H
@@ -88,7 +90,9 @@ struct AttnParams {
   int32_t group_first;     // row items [group_first, n_row_items) belong to the group kernels; those between are the few items' rows
   int32_t n_tile_items;
   int32_t n_few_items;     // units of the tile kernels: n_few_items x pairs of query heads
+  int32_t merge_first;     // merge items [merge_first, merge_first + n_merge_items) are the merge kernel's
   int32_t n_merge_items;
+  int32_t split_units;     // units of a split decode row merged by its last partition (heads, or K/V heads on the group kernel); 0: none is
   float scale_log2e;       // scale * log2(e): scores are kept in log2 units
   int32_t row_variant;     // row-kernel build: bit0 = prefetch depth 2, bit1 = plain (cached) loads
   int32_t tile_first;      // persistent tile kernel: its waves ask for issue priority over the kernel beside it

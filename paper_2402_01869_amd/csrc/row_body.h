@@ -14,14 +14,12 @@
 // Scores are kept in log2 units (multiplied by scale * log2 e) so exp is one v_exp_f32.
 #pragma once
 
-#include "ic_internal.h"
+#include "merge_body.h"
 
 namespace ic {
 namespace rowp {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr float kNegBig = -1.0e30f;  // finite "no key seen yet" maximum (keeps exp2(m - m) = 1)
@@ -154,8 +152,9 @@ constexpr int row_lds_bytes() {
 // NT = non-temporal KV loads.  lds: at least row_lds_bytes<D>() bytes of workgroup LDS.
 // HALF (with PF = 0 only): a block is loaded and consumed in two halves of 8 tokens, which halves the registers a
 // tile takes: the slim build for head_dim 256.
-template <int D, int PF, bool NT, bool HALF = false>
-__device__ __forceinline__ void row_body(const AttnParams& p, const RowItem& it, int head, float* lds) {
+// s_last: an int of LDS where the last partition of a split row may have to merge it (merge_body.h), or null.
+template <int D, int PF, bool NT, bool HALF = false, bool kMerge = false>
+__device__ __forceinline__ void row_body(const AttnParams& p, const RowItem& it, int head, float* lds, int* s_last = nullptr) {
   using G = Geo<D>;
   constexpr int STAGES = PF + 1;  // register buffers
   static_assert(!HALF || (PF == 0 && G::kLoads % 2 == 0), "half-block steps have no prefetch");
@@ -258,12 +257,15 @@ __device__ __forceinline__ void row_body(const AttnParams& p, const RowItem& it,
       p.out[((int64_t)it.qrow * H + head) * D + d] = (uint16_t)f32_to_bf16(O / L);
     } else {
       const int64_t ps = (int64_t)it.slot * H + head;
-      p.part_o[ps * D + d] = O;
+      mergep::store_shared(&p.part_o[ps * D + d], O);
       if (d == 0) {
-        p.part_ml[ps * 2] = M;
-        p.part_ml[ps * 2 + 1] = L;
+        mergep::store_shared(&p.part_ml[ps * 2], M);
+        mergep::store_shared(&p.part_ml[ps * 2 + 1], L);
       }
     }
+  }
+  if constexpr (kMerge) {
+    if (it.slot >= 0 && p.split_units > 0) mergep::finish_split<D, 4>(p, it.slot, head, head, 1, s_last);
   }
 }
 

@@ -67,3 +67,37 @@ def test_few_key_rows_become_units_only_beside_tiles_or_in_numbers():
     assert tiny["off_merge_items"] - tiny["off_tile_items"] < 256       # no tile items, no units
     assert many["off_merge_items"] > many["off_tile_items"]             # units only
     assert beside["off_merge_items"] - beside["off_tile_items"] >= 512  # both
+
+
+@pytest.mark.parametrize("H,Hkv,D,ctx", [(5, 5, 64, [700, 3000, 90, 1500]), (3, 3, 128, [4096, 130, 2000]), (2, 2, 256, [1000, 2600]),
+                                         (16, 2, 128, [5000, 300, 64]), (6, 2, 64, [2500, 40]), (32, 1, 256, [1800, 700])])
+@pytest.mark.gpu
+def test_rows_merged_by_their_last_partition(H, Hkv, D, ctx):
+    """The split the planner chooses for a few decode rows (merged inside the row or group kernel) against the oracle, and
+    the merge kernel's result for the same partitions; several layers and repetitions from one plan, whose arrival
+    counters have to come back to zero."""
+    import torch
+    import oracle
+    from gpu_common import AttnRunner, make_pool, max_abs_err, from_dev_bits
+    batch = W.assemble_batch(H, D, 16, 800, ctx, [1] * len(ctx), np.random.default_rng(D), num_kv_heads=Hkv)
+    pool_bits, q_bits = W.make_host_inputs(batch, 3 + H, poison_unused=True)
+    want = oracle.attn_batch(batch, pool_bits, q_bits)
+    pool, keep = make_pool(pool_bits, H)
+    desc = B.HostDesc.from_batch(batch)
+    part = pool.plan_image(desc)["row_part_tokens"]
+    assert part < max(ctx)                                        # the plan does split
+    r = AttnRunner(pool, batch, q_bits)
+    once = r.run().copy()
+    assert max_abs_err(once, want) <= 1e-2
+    ws = torch.empty(pool.workspace_bytes(desc), dtype=torch.uint8, device="cuda:0")
+    plan = pool.plan_create(desc, ws.data_ptr(), ws.numel())
+    for _ in range(20):
+        r.out.fill_(0x7FFF)
+        for _ in range(3):
+            pool.paged_attn_planned(plan, r.q.data_ptr(), r.out.data_ptr())
+        torch.cuda.synchronize()
+        assert np.array_equal(from_dev_bits(r.out), once)
+    plan.close()
+    pool.set_tuning(decode_part_tokens=part)                      # the same partitions, merged by the merge kernel
+    assert np.array_equal(AttnRunner(pool, batch, q_bits).run(), once)
+    pool.close()
