@@ -126,8 +126,9 @@ size_t paged_attn_mixed_workspace_bytes(const ic_pool* pool, const ic_batch_desc
 /*
  * dev_q, dev_out: device bf16 [total_q_rows][num_heads][head_dim].  dev_workspace: device, 256-byte
  * aligned (IC_EALIGN otherwise; device allocators return such addresses), at least
- * paged_attn_mixed_workspace_bytes() (IC_ESIZE otherwise); its contents are scratch.
- * Deterministic: the same inputs give the same bits on every call.
+ * paged_attn_mixed_workspace_bytes(), or enough to run the batch without the splits that only save time
+ * (IC_ESIZE otherwise); its contents are scratch.
+ * Deterministic: the same inputs and workspace size give the same bits on every call.
  */
 int paged_attn_mixed(ic_pool* pool, const ic_batch_desc* desc, const void* dev_q, void* dev_out,
                      void* dev_workspace, size_t workspace_bytes, void* hip_stream);

@@ -357,7 +357,9 @@ int split_units(const ic_pool* pool, const PlanSizes& ps) {
   return ps.decode_as_group ? pool->cfg.num_kv_heads : pool->cfg.num_heads;
 }
 
-void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
+// compact: no split that only buys time and no few-key units, for a caller whose workspace is too small for the plan that
+// paged_attn_mixed_workspace_bytes sizes (one allocated for another batch, say): the least this batch can run in.
+void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, bool compact = false) {
   std::memset(&ps, 0, sizeof ps);
   // Grouped-query attention: the G = H / Hkv query heads of a group read the same keys.  When G is a
   // power of two up to 32, a tile workgroup takes all of them (G rows per query row), so keys are
@@ -375,7 +377,7 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
   ps.spans_as_rows = (t.span_kernel == 1);  // default: MFMA tiles
   ps.decode_as_tiles = ps.tile_g_shift > 0 && t.span_kernel == 2;
   ps.decode_as_group = ps.tile_g_shift > 0 && t.span_kernel == 0;
-  ps.row_part = t.decode_part_tokens > 0 ? round64(t.decode_part_tokens) : choose_row_part(pool, d, ps);
+  ps.row_part = t.decode_part_tokens > 0 ? round64(t.decode_part_tokens) : compact ? kDefaultRowPart : choose_row_part(pool, d, ps);
   ps.row_part = std::min(ps.row_part, kMaxRowPart);
   int64_t tiles = 0, few = 0;  // unsplit query tiles; rows of spans with few keys
   for (int s = 0; s < d->num_seqs; ++s)
@@ -387,13 +389,13 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
   // Without tile items the few-key units would be a launch of their own (4-5 us); up to two rounds of one-row items on
   // the vector kernel take no longer.  Measured: 4 chunks of 2 rows from position 0 + 1 decode row, 16 heads, two
   // layers: 30 us as row items, 36 as units.
-  ps.few_as_units = !ps.spans_as_rows && (tiles > 0 || few * pool->cfg.num_heads > 2 * kExpectedCus);
+  ps.few_as_units = !compact && !ps.spans_as_rows && (tiles > 0 || few * pool->cfg.num_heads > 2 * kExpectedCus);
   if (t.span_part_tokens == 0) {
     const int64_t head_groups = pool->cfg.num_heads >> ps.tile_g_shift;
     double row_us = 0.0;
     for (int s = 0; s < d->num_seqs; ++s)
       if (d->q_len[s] == 1) row_us += d->ctx_len[s] * (4.0 * pool->cfg.head_dim * pool->cfg.num_kv_heads / 5.5e6);
-    ps.span_part = ps.spans_as_rows || tiles * head_groups >= kUnsplitWorkgroups ? kWholeSpan : choose_span_part(pool, d, ps, row_us);
+    ps.span_part = compact || ps.spans_as_rows || tiles * head_groups >= kUnsplitWorkgroups ? kWholeSpan : choose_span_part(pool, d, ps, row_us);
   }
   ic_plan_info& in = ps.info;
   double tile_pairs = 0, row_keys = 0;  // (query row, key) pairs of the tile items; keys of the row items
@@ -465,8 +467,9 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps) {
   ps.off_few = o;     o = align_up(o + sizeof(FewItem) * (size_t)ps.few_runs, 256);
   ps.off_merge = o;   o = align_up(o + sizeof(MergeItem) * (size_t)in.merge_rows, 256);
   ps.off_row_dst = o; o = align_up(o + sizeof(int32_t) * (size_t)d->total_q_rows, 256);  // for kv_write_span_planned
-  ps.off_slot_merge = o; o = align_up(o + sizeof(int32_t) * (size_t)ps.row_slots, 256);
-  ps.off_arrived = o;    o = align_up(o + sizeof(int32_t) * (size_t)ps.row_merges * split_units(pool, ps), 256);
+  const int units = split_units(pool, ps);
+  ps.off_slot_merge = o; if (units > 0) o = align_up(o + sizeof(int32_t) * (size_t)ps.row_slots, 256);
+  ps.off_arrived = o;    o = align_up(o + sizeof(int32_t) * (size_t)ps.row_merges * units, 256);
   ps.image_bytes = o;
   ps.off_part_o = o;  o = align_up(o + sizeof(float) * (size_t)in.partial_slots * H * D, 256);
   ps.off_part_ml = o; o = align_up(o + sizeof(float) * (size_t)in.partial_slots * H * 2, 256);
@@ -513,7 +516,8 @@ void plan_fill(const ic_batch_desc* d, const PlanSizes& ps, char* img) {
       const int qrow = d->q_start[s] + i;
       const bool vec = i < rt.n_few || !rt.rest_group;
       if (parts > 1) {
-        for (int k = 0; k < parts; ++k) slot_merge[rslot + k] = nrmerge;
+        if (ps.off_arrived > ps.off_slot_merge)
+          for (int k = 0; k < parts; ++k) slot_merge[rslot + k] = nrmerge;
         merges[nrmerge++] = MergeItem{qrow, rslot, parts, 0};
       }
       for (int k = 0; k < parts; ++k) {
@@ -985,6 +989,7 @@ int paged_attn_mixed(ic_pool* pool, const ic_batch_desc* desc, const void* dev_q
     if (misaligned(dev_q) || misaligned(dev_out) || ((uintptr_t)dev_workspace & 255u)) return IC_EALIGN;
     PlanSizes ps;
     plan_sizes(pool, desc, ps);
+    if (workspace_bytes < ps.total_bytes) plan_sizes(pool, desc, ps, true);
     if (workspace_bytes < ps.total_bytes) return IC_ESIZE;
     hipStream_t st = (hipStream_t)hip_stream;
     char* ws = (char*)dev_workspace;
@@ -1002,6 +1007,7 @@ int paged_attn_plan_create(ic_pool* pool, const ic_batch_desc* desc, void* dev_w
   if ((uintptr_t)dev_workspace & 255u) return IC_EALIGN;
   std::unique_ptr<ic_plan> pl(new ic_plan());
   plan_sizes(pool, desc, pl->ps);
+  if (workspace_bytes < pl->ps.total_bytes) plan_sizes(pool, desc, pl->ps, true);
   if (workspace_bytes < pl->ps.total_bytes) return IC_ESIZE;
   pl->cfg = pool->cfg;
   pl->tune = pool->tune;

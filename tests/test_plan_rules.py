@@ -101,3 +101,38 @@ def test_rows_merged_by_their_last_partition(H, Hkv, D, ctx):
     pool.set_tuning(decode_part_tokens=part)                      # the same partitions, merged by the merge kernel
     assert np.array_equal(AttnRunner(pool, batch, q_bits).run(), once)
     pool.close()
+
+
+@pytest.mark.parametrize("H,Hkv,D,ctx,q_len", [(5, 5, 128, [3000, 90], [1, 1]), (16, 2, 128, [5000, 700], [1, 100]),
+                                               (4, 4, 64, [2600, 300], [40, 300])])
+@pytest.mark.gpu
+def test_a_workspace_without_room_for_the_split_runs_whole_rows(H, Hkv, D, ctx, q_len):
+    """A workspace large enough for whole rows and tiles (allocated for another batch, say) is accepted."""
+    import torch
+    import oracle
+    from gpu_common import from_dev_bits, make_pool, max_abs_err, to_dev_bits
+    batch = W.assemble_batch(H, D, 16, 512, ctx, q_len, np.random.default_rng(D), num_kv_heads=Hkv)
+    pool_bits, q_bits = W.make_host_inputs(batch, 21, poison_unused=True)
+    want = oracle.attn_batch(batch, pool_bits, q_bits)
+    pool, keep = make_pool(pool_bits, H)
+    desc = B.HostDesc.from_batch(batch)
+    full = pool.workspace_bytes(desc)
+    pool.set_tuning(decode_part_tokens=4096, span_part_tokens=1 << 20)
+    whole = pool.workspace_bytes(desc)
+    if max(ctx) <= 4096:
+        assert pool.plan_query(desc)["partial_slots"] == 0
+    pool.set_tuning()
+    assert whole < full
+    q, ws = to_dev_bits(q_bits), torch.empty(full, dtype=torch.uint8, device="cuda:0")
+    for planned in (False, True):
+        out = torch.full(tuple(q_bits.shape), 0x7FFF, dtype=torch.int16, device="cuda:0")
+        if planned:
+            plan = pool.plan_create(desc, ws.data_ptr(), whole)
+            pool.paged_attn_planned(plan, q.data_ptr(), out.data_ptr())
+        else:
+            pool.paged_attn_mixed(desc, q.data_ptr(), out.data_ptr(), ws.data_ptr(), whole)
+        torch.cuda.synchronize()
+        assert max_abs_err(from_dev_bits(out), want) <= 1e-2
+    plan.close()
+    assert pool.paged_attn_mixed(desc, q.data_ptr(), out.data_ptr(), ws.data_ptr(), 1024, check=False) == B.IC_ESIZE
+    pool.close()
