@@ -194,9 +194,10 @@ typedef struct {
                                  head_dim 128 with groups of up to 16: the slim group kernel)  */
   int32_t row_slots;          /* resident workgroups of the persistent row kernel (and of the slim group kernel);
                                  0 = one per CU */
-  int32_t mfma_min_keys;      /* query rows that see fewer keys than this run on the vector kernel, which keeps the
-                                 softmax weights in fp32 (the matrix-core kernels round them to bf16, and with a
-                                 handful of keys one weight's rounding shows in the output); 0 = built-in 64,
+  int32_t mfma_min_keys;      /* the softmax weights of query rows that see fewer keys than this are not rounded to
+                                 bf16 as the matrix-core kernels do (with a handful of keys one weight's rounding
+                                 shows in the output): such rows run on the vector kernel, which keeps them in
+                                 fp32, or as units that split them into two bf16 parts; 0 = built-in 64,
                                  1 = no such routing, at most 64                              */
   int32_t reserved[1];        /* must be 0                                                   */
 } ic_tuning;

@@ -21,9 +21,10 @@ constexpr int kStagingSlots = 4;       // pinned host buffers, each filled by su
 constexpr int kDefaultRowPart = 4096;
 constexpr int kWholeSpan = 1 << 30;    // span partition: none
 constexpr int kUnsplitWorkgroups = 1024;  // tile workgroups (4 per CU) from which spans are not split at all
-// Rows that see fewer keys than this stay off the matrix cores.  There the weights are rounded to bf16
+// The weights of rows that see fewer keys than this are not rounded to bf16.  The matrix-core kernels round them
 // before the PV product; with a handful of keys a single weight's rounding (2^-9 relative) shows in the
-// output, with dozens the roundings average out.  The vector path keeps the weights in fp32.
+// output, with dozens the roundings average out.  The vector path keeps the weights in fp32, the
+// few-key units split them into two bf16 parts.
 constexpr int kShareKeys = 8192;  // sequences at least this long keep their tile items side by side
 constexpr int kMfmaMinKeys = 64;
 constexpr int kExpectedCus = 256;        // the planner runs without a device; the launches use the device's own count
