@@ -480,31 +480,23 @@ def kernel_table(prof, steps=None):
     return out
 
 
-def attention_kernel_names(pool, desc, acfg, args):
-    """Names of the kernels the default plan launches for this batch, from the planner's own report."""
-    info = pool.plan_query(desc)
-    D = acfg.head_dim
-    G = acfg.num_heads // acfg.kv_heads
-    grouped = 2 <= G <= 32 and G & (G - 1) == 0 and args.span_kernel == 0
-    pair = info["tile_items"] > 0 and not args.serial_spans
-    lay = pool.plan_image(desc)
-    n_vec, n_group = lay["n_vector_row_items"], lay["n_row_items"] - lay["n_vector_row_items"]
-    beside_rows = pair and n_vec > 0 and not grouped
-    beside_group = pair and n_group > 0 and D == 128 and G <= 16
-    beside = beside_rows or beside_group
-    row = ("row_persist_slim_kernel" if beside or args.row_launch == 3 else
-           "row_attn_kernel" if args.row_launch == 1 else "row_persist_kernel")
-    tile = f"tile_persist_kernel<{D}, {'true' if beside else 'false'}>" if beside or D <= 128 else f"tile_attn_kernel<{D}>"
-    group = "group_slim_kernel" if beside_group else f"group_attn_kernel<{D}>"
+def attention_kernel_names(pool, desc, acfg):
+    """Names of the kernels the pool launches for this batch under its tuning, from the planner's own report."""
+    from paper_2402_01869_amd import binding as B
+    D, how = acfg.head_dim, pool.plan_launches(desc)
+    beside = bool(how["side_by_side"])
+    row = {B.IC_LAUNCH_SLIM: "row_persist_slim_kernel", B.IC_LAUNCH_PER_ITEM: "row_attn_kernel"}.get(how["row_launch"], "row_persist_kernel")
+    tile = f"tile_attn_kernel<{D}>" if how["tile_launch"] == B.IC_LAUNCH_PER_ITEM else f"tile_persist_kernel<{D}, {'true' if beside else 'false'}>"
+    group = "group_slim_kernel" if how["group_launch"] == B.IC_LAUNCH_SLIM else f"group_attn_kernel<{D}>"
     return {"row": f"{row}<{D}>", "group": group, "tile": tile, "merge": f"merge_kernel<{D}>",
-            "side_by_side": beside}
+            "side_by_side": beside, "beside_tile": group if how["group_launch"] else f"{row}<{D}>"}
 
 
 def attention_report(S, args, steps, warm, default_plan):
     """Times one attention workload: wall time per call, per-kernel HIP-event times, the call's roofline figures and the
     dominant kernel's."""
     acfg, pool = S.acfg, S.pool
-    names = attention_kernel_names(pool, S.descs[0], acfg, args)
+    names = attention_kernel_names(pool, S.descs[0], acfg)
     ms = wall_ms(S.call, steps, warm)
     pool.prof_begin(8 * steps + 8)
     ms_ev = wall_ms(S.call, steps, 0)
@@ -533,7 +525,7 @@ def attention_report(S, args, steps, warm, default_plan):
     traffic = MEASURED_TRAFFIC.get(tkey) if default_plan else None
     if dom == "tile":
         ach = S.span_flops / (cand[dom] * 1e-3) / 1e12
-        roof = {"kernel": names[dom], "runs_beside": names["row"] if names["side_by_side"] else None, "bound": "mfma",
+        roof = {"kernel": names[dom], "runs_beside": names["beside_tile"] if names["side_by_side"] else None, "bound": "mfma",
                 "achieved": round(ach, 1), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(ach / MFMA_BF16_PEAK_TFLOPS, 4), "flops_per_launch": S.span_flops}
     else:

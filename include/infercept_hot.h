@@ -206,10 +206,12 @@ int ic_pool_set_tuning(ic_pool* pool, const ic_tuning* tuning);
 /* What the planner would launch for this batch (host only; for tests and reports). */
 typedef struct {
   int32_t decode_rows, span_rows;      /* query rows handled by each path                     */
-  int32_t row_items;                   /* work items of the vector (row) kernel, per head     */
+  int32_t row_items;                   /* rows x key partitions run row by row (vector kernel), by
+                                          the group kernel, or as rows of few-key units       */
   int32_t tile_items;                  /* work items of the MFMA tile kernel, per head        */
   int32_t partial_slots;               /* split-KV partial results, per head                  */
-  int32_t merge_rows;                  /* rows that need the merge pass                       */
+  int32_t merge_rows;                  /* rows whose partial results are merged, by the merge
+                                          kernel or by the kernel of their last partition     */
   int64_t table_entries;               /* block-table entries copied to the device            */
 } ic_plan_info;
 int ic_plan_query(const ic_pool* pool, const ic_batch_desc* desc, ic_plan_info* out);
@@ -218,7 +220,8 @@ int ic_plan_query(const ic_pool* pool, const ic_batch_desc* desc, ic_plan_info* 
  * into host_image the descriptor image paged_attn_mixed would upload for this batch under the
  * pool's current tuning, and describes its layout.  All sections are int32 arrays at the given byte
  * offsets: counters[16] (zero) | bt_off[num_seqs] | bt_flat[table_entries] (the sequences' block
- * ids, back to back) | row items | tile items | merge items | row_dst[total_q_rows].
+ * ids, back to back) | row items | tile items | few items | merge items | row_dst[total_q_rows] | slot_merge | arrived
+ * (few items, slot_merge and arrived: ic_plan_launches below).
  *   row item   (8 x int32): seq, qrow, k_begin, k_end, slot (-1: whole row, direct output), 0, 0, 0
  *              one query row against keys [k_begin, k_end) of its sequence, all heads
  *   tile item  (8 x int32): seq, qrow0, n_rows, pos0, k_begin, k_end, slot0 (-1: direct), nparts
@@ -238,10 +241,34 @@ typedef struct {
   int32_t tile_query_rows;   /* query rows per tile item                                      */
   int32_t tile_head_shift;   /* log2 of the query heads one tile workgroup serves             */
   int32_t n_row_items, n_tile_items, n_merge_items;
-  int32_t n_vector_row_items; /* row items [0, n) run on the vector kernel, the rest on the group kernel */
+  int32_t n_vector_row_items; /* row items [0, n) keep more than bf16 of their softmax weights: the vector kernel's, then the
+                                 rows of the few items (tile kernel); the rest run on the group kernel */
 } ic_plan_layout;
 int ic_plan_image(const ic_pool* pool, const ic_batch_desc* desc, void* host_image, size_t host_bytes,
                   ic_plan_layout* out);
+
+/*
+ * The kernels paged_attn_mixed launches for this batch under the pool's current tuning, and the sections of the
+ * descriptor image that ic_plan_layout does not list (host only; for tests and reports):
+ *   few item   (2 x int32): first, n_rows    row items first .. first + n_rows - 1, consecutive rows of one sequence at
+ *              ascending positions, n_rows <= 63, run as one unit per pair of query heads by the tile kernel
+ *   slot_merge merge item of each partial slot of a decode row that its last partition merges
+ *   arrived    [n_merged_inside][n_split_units] counters of finished partitions (zero)
+ */
+enum { IC_LAUNCH_NONE = 0, IC_LAUNCH_PER_ITEM = 1, IC_LAUNCH_PERSISTENT = 2, IC_LAUNCH_SLIM = 3 };
+typedef struct {
+  int64_t off_few_items, off_slot_merge, off_arrived;
+  int32_t side_by_side;     /* 1: the tile kernel beside the slim row or group kernel, 0: one kernel after the other */
+  int32_t tile_launch;      /* IC_LAUNCH_*: tile kernel (tile items, then few items)                  */
+  int32_t row_launch;       /* ... vector row kernel (row items [0, n_vector_row_items - n_few_rows)) */
+  int32_t group_launch;     /* ... group kernel (row items from n_vector_row_items on)                */
+  int32_t n_few_items, n_few_rows;
+  int32_t n_merged_inside;  /* merge items [0, n) are merged by the row or group kernel, the rest by the merge kernel */
+  int32_t n_split_slots;    /* entries of slot_merge                                                  */
+  int32_t n_split_units;    /* units of such a row: query heads, or K/V heads on the group kernel     */
+  int32_t reserved;
+} ic_plan_launch_info;
+int ic_plan_launches(const ic_pool* pool, const ic_batch_desc* desc, ic_plan_launch_info* out);
 
 /* ------------------------------------------------------------------------------------------
  * Swap of scattered blocks (Section 3.2, swap-based approach: a paged context is scattered over

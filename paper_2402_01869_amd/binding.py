@@ -35,6 +35,7 @@ EXPORTS = (
     "ic_chunk_tokens", "ic_chunk_count", "ic_saturation_point", "ic_schedule_intercepted",
     "paged_attn_plan_create", "paged_attn_planned", "paged_attn_plan_destroy", "kv_write_span_planned",
     "ic_mfma_ceiling", "ic_plan_image", "ic_hbm_ceiling", "ic_paged_read_ceiling", "kv_pack_blocks_static",
+    "ic_plan_launches",
 )
 IC_CEILING_OPERAND_BYTES = 1 << 20
 IC_CEILING_SINK_BYTES = 256 * 512 * 4 + 256 * 16
@@ -75,6 +76,15 @@ class PlanLayout(C.Structure):
                                           "off_tile_items", "off_merge_items", "off_row_dst")] +
                 [(n, C.c_int32) for n in ("row_part_tokens", "span_part_tokens", "tile_query_rows", "tile_head_shift",
                                           "n_row_items", "n_tile_items", "n_merge_items", "n_vector_row_items")])
+
+
+IC_LAUNCH_NONE, IC_LAUNCH_PER_ITEM, IC_LAUNCH_PERSISTENT, IC_LAUNCH_SLIM = range(4)
+
+
+class PlanLaunchInfo(C.Structure):
+    _fields_ = ([(n, C.c_int64) for n in ("off_few_items", "off_slot_merge", "off_arrived")] +
+                [(n, C.c_int32) for n in ("side_by_side", "tile_launch", "row_launch", "group_launch", "n_few_items", "n_few_rows",
+                                          "n_merged_inside", "n_split_slots", "n_split_units", "reserved")])
 
 
 class ProfStats(C.Structure):
@@ -131,6 +141,7 @@ def lib():
         L.ic_check_batch.argtypes = [C.POINTER(PoolCfg), C.POINTER(BatchDesc)]
         L.ic_pool_set_tuning.argtypes = [vp, C.POINTER(Tuning)]
         L.ic_plan_query.argtypes = [vp, C.POINTER(BatchDesc), C.POINTER(PlanInfo)]
+        L.ic_plan_launches.argtypes = [vp, C.POINTER(BatchDesc), C.POINTER(PlanLaunchInfo)]
         L.kv_pack_blocks.argtypes = [vp, i32p, C.c_int32, vp, C.c_size_t, vp]
         L.kv_unpack_blocks.argtypes = [vp, i32p, C.c_int32, vp, C.c_size_t, vp]
         L.kv_pack_blocks_static.argtypes = [vp, i32p, C.c_int32, vp, C.c_size_t, vp]
@@ -270,9 +281,18 @@ class KvPool:
             raise InferceptError(rc, "ic_plan_query")
         return {n: int(getattr(info, n)) for n, _ in PlanInfo._fields_}
 
+    def plan_launches(self, desc: HostDesc) -> dict:
+        """ic_plan_launches: the kernels the call launches for this batch, and how (host only, no GPU)."""
+        info = PlanLaunchInfo()
+        rc = lib().ic_plan_launches(self._h, C.byref(desc.struct), C.byref(info))
+        if rc != IC_OK:
+            raise InferceptError(rc, "ic_plan_launches")
+        return {n: int(getattr(info, n)) for n, _ in PlanLaunchInfo._fields_ if n != "reserved"}
+
     def plan_image(self, desc: HostDesc) -> dict:
         """ic_plan_image: the launch plan as numpy arrays (host only, no GPU): layout fields plus `bt_off`, `bt_flat`,
-        `row_items` [n][8], `tile_items` [n][8], `merge_items` [n][4], `row_dst`, `counters`."""
+        `row_items` [n][8], `tile_items` [n][8], `few_items` [n][2], `merge_items` [n][4], `row_dst`, `slot_merge`,
+        `arrived`, `counters`, and what `plan_launches` says."""
         lay = PlanLayout()
         rc = lib().ic_plan_image(self._h, C.byref(desc.struct), None, C.c_size_t(0), C.byref(lay))
         if rc != IC_OK:
@@ -293,6 +313,10 @@ class KvPool:
         out["merge_items"] = sec(out["off_merge_items"], 4 * out["n_merge_items"]).reshape(-1, 4)
         out["row_dst"] = sec(out["off_row_dst"], int(desc.struct.total_q_rows))
         out["partial_slots"] = info["partial_slots"]
+        out.update(self.plan_launches(desc))
+        out["few_items"] = sec(out["off_few_items"], 2 * out["n_few_items"]).reshape(-1, 2)
+        out["slot_merge"] = sec(out["off_slot_merge"], out["n_split_slots"])
+        out["arrived"] = sec(out["off_arrived"], out["n_merged_inside"] * out["n_split_units"])
         return out
 
     def paged_read_ceiling(self, ids, dev_sink: int, reps: int = 1, stream: int = 0, check: bool = True):

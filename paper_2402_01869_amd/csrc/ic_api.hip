@@ -477,6 +477,42 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, bool
   ps.total_bytes = o;
 }
 
+// The kernels that run a plan, and how.
+struct PlanLaunches {
+  bool side_by_side;     // the tile kernel beside the slim builds, on two streams; else one kernel after the other
+  int tile, row, group;  // IC_LAUNCH_*
+};
+
+// Decode rows are memory-bound and span tiles are MFMA-bound (the complementarity Section 4.2
+// builds on): a batch that has both runs them as two persistent kernels side by side, one
+// workgroup of each per CU, the tile kernel on the pool's second stream (forked from and joined
+// back into the caller's stream by events).  The kernel beside the tile kernel is the slim row
+// kernel (multi-head pools) or the slim group kernel (grouped pools: head_dim 128, groups of up
+// to 16 heads).  serial_spans = 1, the other grouped shapes and batches too small to pay for the second stream run one
+// kernel after the other instead.
+PlanLaunches plan_launches(const ic_pool* pool, const PlanSizes& ps) {
+  const ic_tuning& t = pool->tune;
+  const int D = pool->cfg.head_dim;
+  const bool slim_group = D == 128 && pool->cfg.num_heads / pool->cfg.num_kv_heads <= 16;
+  const bool tiles = ps.info.tile_items > 0 || ps.few_runs > 0;
+  const bool rows = ps.vec_items > ps.few_rows, groups = ps.info.row_items > ps.vec_items;
+  PlanLaunches how;
+  how.side_by_side = tiles && ps.side_by_side && !t.serial_spans && (ps.decode_as_group ? groups && slim_group : rows);
+  // head_dim <= 128: the persistent tile launch also when no other kernel runs beside it.  Its per-XCD queues keep the
+  // query tiles of one (sequence, head) on one L2: on 2048-row chunks the spans then fetch 2.6 x instead of 6.9 x
+  // their keys from HBM and finish 7 % sooner (9.66 against 10.41 ms); shorter chunks and grouped pools: no change.
+  // head_dim 256: one workgroup per work item; the persistent build is held to 208 registers for the sake of
+  // its neighbour and is 19 % slower alone (0.197 against 0.166 ms on the GPT-J-shaped chunks).
+  how.tile = !tiles ? IC_LAUNCH_NONE : how.side_by_side || D <= 128 ? IC_LAUNCH_PERSISTENT : IC_LAUNCH_PER_ITEM;
+  // row_launch = 3: the side-by-side builds, alone
+  how.group = !groups ? IC_LAUNCH_NONE : how.side_by_side || (t.row_launch == 3 && slim_group) ? IC_LAUNCH_SLIM : IC_LAUNCH_PER_ITEM;
+  how.row = !rows ? IC_LAUNCH_NONE
+            : how.side_by_side || t.row_launch == 3 ? IC_LAUNCH_SLIM
+            : t.row_launch == 1 || (t.row_launch == 0 && t.row_slots == 0 && ps.row_per_item) ? IC_LAUNCH_PER_ITEM
+                                                                                              : IC_LAUNCH_PERSISTENT;
+  return how;
+}
+
 // May throw std::bad_alloc (per-sequence scratch vectors); callers at the ABI catch it.
 void plan_fill(const ic_batch_desc* d, const PlanSizes& ps, char* img) {
   const int kTileRows = ps.tile_rows;
@@ -823,6 +859,32 @@ int ic_plan_image(const ic_pool* pool, const ic_batch_desc* desc, void* host_ima
   });
 }
 
+int ic_plan_launches(const ic_pool* pool, const ic_batch_desc* desc, ic_plan_launch_info* out) {
+  if (!pool || !desc || !out) return IC_ENULL;
+  return guarded([&]() -> int {
+  const int rc = check_batch(pool->cfg, desc, false);
+  if (rc != IC_OK) return rc;
+  PlanSizes ps;
+  plan_sizes(pool, desc, ps);
+  const PlanLaunches how = plan_launches(pool, ps);
+  const int units = split_units(pool, ps);
+  std::memset(out, 0, sizeof *out);
+  out->off_few_items = (int64_t)ps.off_few;
+  out->off_slot_merge = (int64_t)ps.off_slot_merge;
+  out->off_arrived = (int64_t)ps.off_arrived;
+  out->side_by_side = how.side_by_side;
+  out->tile_launch = how.tile;
+  out->row_launch = how.row;
+  out->group_launch = how.group;
+  out->n_few_items = ps.few_runs;
+  out->n_few_rows = ps.few_rows;
+  out->n_merged_inside = units > 0 ? ps.row_merges : 0;
+  out->n_split_slots = units > 0 ? ps.row_slots : 0;
+  out->n_split_units = units;
+  return IC_OK;
+  });
+}
+
 size_t paged_attn_mixed_workspace_bytes(const ic_pool* pool, const ic_batch_desc* desc) {
   if (!pool || !desc) return 0;
   if (check_batch(pool->cfg, desc, true) != IC_OK) return 0;
@@ -883,23 +945,12 @@ static int launch_attention(ic_pool* pool, const PlanSizes& ps, float scale, con
   p.tile_first = 0;
   p.counters = (int32_t*)(ws + ps.off_ctr);
 
-  // Decode rows are memory-bound and span tiles are MFMA-bound (the complementarity Section 4.2
-  // builds on): a batch that has both runs them as two persistent kernels side by side, one
-  // workgroup of each per CU, the tile kernel on the pool's second stream (forked from and joined
-  // back into the caller's stream by events).  The kernel beside the tile kernel is the slim row
-  // kernel (multi-head pools) or the slim group kernel (grouped pools: head_dim 128, groups of up
-  // to 16 heads).  serial_spans = 1, the other grouped shapes and batches too small to pay for the second stream run one
-  // kernel after the other instead.
-  const int n_group_items = p.n_row_items - p.group_first;
-  const bool tiles = p.n_tile_items > 0 || p.n_few_items > 0;
-  const bool pair_ok = tiles && ps.side_by_side && !pool->tune.serial_spans;
-  const bool beside_rows = pair_ok && p.n_vec_items > 0 && !ps.decode_as_group;
-  const bool beside_group = pair_ok && n_group_items > 0 && D == 128 && p.group <= 16;
+  const PlanLaunches how = plan_launches(pool, ps);
   // One persistent row workgroup per CU; alone at head_dim 64, where a wave has half as many bytes in flight, two
   // (5856 items of 800 keys: 259 -> 192 us, 2912 of 1600 keys: 239 -> 179 us).
   const int row_slots = pool->tune.row_slots > 0 ? pool->tune.row_slots : pool->num_cus;
   const int alone_slots = pool->tune.row_slots > 0 || D > 64 ? row_slots : 2 * row_slots;
-  if (beside_rows || beside_group) {
+  if (how.side_by_side) {
     if (!pool->side) {  // the stream is assigned last: a half-made set is retried by the next call
       if (!pool->ev_fork && hipEventCreateWithFlags(&pool->ev_fork, hipEventDisableTiming) != hipSuccess) return IC_EHIP;
       if (!pool->ev_join && hipEventCreateWithFlags(&pool->ev_join, hipEventDisableTiming) != hipSuccess) return IC_EHIP;
@@ -922,11 +973,11 @@ static int launch_attention(ic_pool* pool, const PlanSizes& ps, float scale, con
       ok = launch_tile_persist(p, D, pool->num_cus, true, s_tile) == hipSuccess;
     };
     auto run_rows = [&] {
-      if (ok && beside_group) {
+      if (ok && how.group == IC_LAUNCH_SLIM) {
         ProfScope ps_(pool, IC_K_GROUP, s_rows);
         ok = launch_group_slim(p, D, row_slots, s_rows) == hipSuccess;
       }
-      if (ok && p.n_vec_items > 0) {  // in a grouped pool: the rows with too few keys for the matrix cores
+      if (ok && how.row == IC_LAUNCH_SLIM) {  // in a grouped pool: the rows with too few keys for the matrix cores
         ProfScope ps_(pool, IC_K_ROW, s_rows);
         ok = launch_row_persist_slim(p, D, row_slots, s_rows) == hipSuccess;
       }
@@ -948,28 +999,21 @@ static int launch_attention(ic_pool* pool, const PlanSizes& ps, float scale, con
     }
     if (!ok) return IC_EHIP;
   } else {
-    if (tiles) {
+    if (how.tile != IC_LAUNCH_NONE) {
       ProfScope ps_(pool, IC_K_TILE, st);
-      // head_dim <= 128: the persistent launch also when no other kernel runs beside it.  Its per-XCD queues keep the
-      // query tiles of one (sequence, head) on one L2: on 2048-row chunks the spans then fetch 2.6 x instead of 6.9 x
-      // their keys from HBM and finish 7 % sooner (9.66 against 10.41 ms); shorter chunks and grouped pools: no change.
-      // head_dim 256: one workgroup per work item; the persistent build is held to 208 registers for the sake of
-      // its neighbour and is 19 % slower alone (0.197 against 0.166 ms on the GPT-J-shaped chunks).
-      const hipError_t e = D <= 128 ? launch_tile_persist(p, D, pool->num_cus, false, st) : launch_tile_kernel(p, D, st);
+      const hipError_t e = how.tile == IC_LAUNCH_PERSISTENT ? launch_tile_persist(p, D, pool->num_cus, false, st)
+                                                            : launch_tile_kernel(p, D, st);
       if (e != hipSuccess) return IC_EHIP;
     }
-    if (n_group_items > 0) {
+    if (how.group != IC_LAUNCH_NONE) {
       ProfScope ps_(pool, IC_K_GROUP, st);
-      const bool slim = pool->tune.row_launch == 3 && D == 128 && p.group <= 16;  // the side-by-side build, alone
-      if ((slim ? launch_group_slim(p, D, row_slots, st) : launch_group_kernel(p, D, st)) != hipSuccess) return IC_EHIP;
+      if ((how.group == IC_LAUNCH_SLIM ? launch_group_slim(p, D, row_slots, st) : launch_group_kernel(p, D, st)) != hipSuccess) return IC_EHIP;
     }
-    if (p.n_vec_items > 0) {
+    if (how.row != IC_LAUNCH_NONE) {
       ProfScope ps_(pool, IC_K_ROW, st);
-      const int how = pool->tune.row_launch;
-      const bool per_item = how == 1 || (how == 0 && pool->tune.row_slots == 0 && ps.row_per_item);
-      const hipError_t e = how == 3 ? launch_row_persist_slim(p, D, row_slots, st)
-                           : per_item ? launch_row_kernel(p, D, st)
-                                      : launch_row_persist(p, D, alone_slots, st);
+      const hipError_t e = how.row == IC_LAUNCH_SLIM       ? launch_row_persist_slim(p, D, row_slots, st)
+                           : how.row == IC_LAUNCH_PER_ITEM ? launch_row_kernel(p, D, st)
+                                                           : launch_row_persist(p, D, alone_slots, st);
       if (e != hipSuccess) return IC_EHIP;
     }
   }

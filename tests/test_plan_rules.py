@@ -69,6 +69,62 @@ def test_few_key_rows_become_units_only_beside_tiles_or_in_numbers():
     assert beside["off_merge_items"] - beside["off_tile_items"] >= 512  # both
 
 
+@pytest.mark.parametrize("H,Hkv,D", [(4, 4, 64), (5, 5, 128), (2, 2, 256), (64, 8, 128), (6, 2, 64)])
+def test_few_items_and_split_slots_of_the_image(H, Hkv, D):
+    """Every few item covers consecutive rows of one sequence, each such row exactly once; every partial slot of a row that
+    its last partition merges names that row's merge item; the arrival counters start at zero."""
+    rng = np.random.default_rng(H + Hkv + D)
+    seen_units = seen_split = 0
+    for trial in range(40):
+        n = int(rng.integers(1, 7))
+        ctx = [int(rng.integers(1, 70)) if rng.random() < 0.4 else int(rng.integers(64, 5000)) for _ in range(n)]
+        q_len = [1 if rng.random() < (0.5, 1.0)[trial % 2] else int(rng.integers(1, min(c, 400) + 1)) for c in ctx]
+        plan = _plan(H, Hkv, D, ctx, q_len)
+        rows, few = plan["row_items"], plan["few_items"]
+        first = plan["n_vector_row_items"] - plan["n_few_rows"]
+        assert few[:, 1].sum() == plan["n_few_rows"]
+        for at, k in few.tolist():
+            assert at == first and 1 <= k <= 63            # back to back, behind the vector kernel's items
+            first += k
+            seq, pos = rows[at, 0], rows[at:at + k, 3]
+            assert (rows[at:at + k, 0] == seq).all() and q_len[seq] > 1
+            assert (rows[at:at + k, 1] == rows[at, 1] + np.arange(k)).all() and (pos == pos[0] + np.arange(k)).all()
+            assert pos[0] == ctx[seq] - q_len[seq] + 1 and pos[-1] <= 63
+            assert (rows[at:at + k, 2] == 0).all() and (rows[at:at + k, 4] == -1).all()
+        assert first == plan["n_vector_row_items"]
+        assert bool(len(few)) <= bool(plan["tile_launch"])
+        inside = plan["n_merged_inside"]
+        for mi, (qrow, slot0, nparts, _) in enumerate(plan["merge_items"].tolist()[:inside]):
+            assert (plan["slot_merge"][slot0:slot0 + nparts] == mi).all()
+            mine = rows[rows[:, 1] == qrow]
+            assert sorted(mine[:, 4].tolist()) == list(range(slot0, slot0 + nparts))
+        assert plan["n_split_slots"] == sum(m[2] for m in plan["merge_items"].tolist()[:inside])
+        assert len(plan["arrived"]) == inside * plan["n_split_units"] and not plan["arrived"].any()
+        seen_units += len(few)
+        seen_split += inside
+    assert seen_units and seen_split
+
+
+def test_the_benchmark_names_the_kernels_that_run():
+    """The report's kernel names follow the planner's launches, not the tuning alone."""
+    import types
+    import bench
+    for H, Hkv, D, ctx, q_len, want in [
+            (4, 4, 64, [16, 100, 64, 90], [1, 1, 32, 32], ("row_attn_kernel<64>", "tile_persist_kernel<64, false>", False)),
+            (40, 40, 128, [3000], [1], ("row_attn_kernel<128>", None, False)),               # split, merged by its last partition
+            (40, 40, 128, [4000] * 40, [1] * 40, ("row_persist_kernel<128>", None, False)),
+            (16, 16, 256, [600, 900], [300, 1], ("row_attn_kernel<256>", "tile_attn_kernel<256>", False)),
+            (40, 40, 128, [3000] * 60 + [3000] * 8, [1] * 60 + [512] * 8, ("row_persist_slim_kernel<128>", "tile_persist_kernel<128, true>", True))]:
+        rng = np.random.default_rng(1)
+        blocks = sum(-(-c // 16) for c in ctx) + 4
+        batch = W.assemble_batch(H, D, 16, blocks, ctx, q_len, rng, num_kv_heads=Hkv)
+        pool = B.KvPool(B.make_cfg(blocks, H, D, num_kv_heads=Hkv), 0x10000, blocks * 64 * Hkv * D)
+        names = bench.attention_kernel_names(pool, B.HostDesc.from_batch(batch), types.SimpleNamespace(head_dim=D, num_heads=H, kv_heads=Hkv))
+        assert names["row"] == want[0] and names["side_by_side"] == want[2]
+        assert want[1] is None or names["tile"] == want[1]
+        pool.close()
+
+
 @pytest.mark.parametrize("H,Hkv,D,ctx", [(5, 5, 64, [700, 3000, 90, 1500]), (3, 3, 128, [4096, 130, 2000]), (2, 2, 256, [1000, 2600]),
                                          (16, 2, 128, [5000, 300, 64]), (6, 2, 64, [2500, 40]), (32, 1, 256, [1800, 700])])
 @pytest.mark.gpu
