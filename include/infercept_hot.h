@@ -185,12 +185,12 @@ typedef struct {
                                  kernel, 2 = MFMA tiles, in a grouped-query pool also for decode rows */
   int32_t row_variant;        /* vector-kernel build: bit 0 = prefetch two tiles ahead, bit 1 = cached (not non-temporal) KV loads */
   int32_t serial_spans;       /* 1 = run the span kernel, then the row kernel, on the caller's stream; 0 = built-in
-                                 choice (large batches: two persistent kernels side by side, one on the process's
-                                 second stream)                                              */
-  int32_t row_launch;         /* single-role row kernel: 0 = built-in choice (persistent, one workgroup per CU, or
-                                 one workgroup per work item when the items are short),
-                                 1 = one workgroup per work item, 2 = persistent, 3 = persistent, the slim
-                                 builds that otherwise run beside the tile kernel (in a grouped-query pool of
+                                 choice (large batches, and with row_launch 2 or 3 or row_slots any batch: two
+                                 persistent kernels side by side, one on the process's second stream) */
+  int32_t row_launch;         /* row kernel: 0 = built-in choice (alone persistent, one workgroup per CU, or
+                                 one workgroup per work item when the items are short or split),
+                                 1 = alone one workgroup per work item, 2 = persistent, 3 = persistent, alone too
+                                 the slim builds that run beside the tile kernel (in a grouped-query pool of
                                  head_dim 128 with groups of up to 16: the slim group kernel)  */
   int32_t row_slots;          /* resident workgroups of the persistent row kernel (and of the slim group kernel);
                                  0 = one per CU */

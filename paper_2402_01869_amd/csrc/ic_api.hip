@@ -488,8 +488,8 @@ struct PlanLaunches {
 // workgroup of each per CU, the tile kernel on the pool's second stream (forked from and joined
 // back into the caller's stream by events).  The kernel beside the tile kernel is the slim row
 // kernel (multi-head pools) or the slim group kernel (grouped pools: head_dim 128, groups of up
-// to 16 heads).  serial_spans = 1, the other grouped shapes and batches too small to pay for the second stream run one
-// kernel after the other instead.
+// to 16 heads).  serial_spans = 1, the other grouped shapes and, unless the caller asks for persistent row workgroups
+// (row_launch 2 or 3, row_slots), batches too small to pay for the second stream run one kernel after the other instead.
 PlanLaunches plan_launches(const ic_pool* pool, const PlanSizes& ps) {
   const ic_tuning& t = pool->tune;
   const int D = pool->cfg.head_dim;
@@ -497,7 +497,8 @@ PlanLaunches plan_launches(const ic_pool* pool, const PlanSizes& ps) {
   const bool tiles = ps.info.tile_items > 0 || ps.few_runs > 0;
   const bool rows = ps.vec_items > ps.few_rows, groups = ps.info.row_items > ps.vec_items;
   PlanLaunches how;
-  how.side_by_side = tiles && ps.side_by_side && !t.serial_spans && (ps.decode_as_group ? groups && slim_group : rows);
+  const bool asked = t.row_launch >= 2 || t.row_slots > 0;
+  how.side_by_side = tiles && (ps.side_by_side || asked) && !t.serial_spans && (ps.decode_as_group ? groups && slim_group : rows);
   // head_dim <= 128: the persistent tile launch also when no other kernel runs beside it.  Its per-XCD queues keep the
   // query tiles of one (sequence, head) on one L2: on 2048-row chunks the spans then fetch 2.6 x instead of 6.9 x
   // their keys from HBM and finish 7 % sooner (9.66 against 10.41 ms); shorter chunks and grouped pools: no change.

@@ -95,7 +95,8 @@ def test_spans_across_tiles_and_partitions(D, H):
 def test_every_launch_path(D, H):
     """The launch shapes a tuning can select give the same answer as the default: span kernel before
     the row kernel on one stream, one workgroup per work item, persistent row kernels of both builds
-    with slot counts that do not divide the item count, and the prefetch / load-policy builds."""
+    with slot counts that do not divide the item count, alone and (serial_spans = 0) beside the tile kernel,
+    and the prefetch / load-policy builds."""
     ctx = [700, 33, 300, 1, 129, 1000, 64, 515, 2100, 90, 17]
     qlen = [200, 1, 300, 1, 128, 257, 1, 130, 1, 1, 1]
     rng = np.random.default_rng(31 + D)
@@ -115,8 +116,8 @@ def test_every_launch_path(D, H):
 def test_grouped_query_attention(H, Hkv, D):
     """H query heads over Hkv K/V heads: decode rows and spans, whole-row and split-KV plans, head groups
     of 2 to 32 on the MFMA path (keys staged once per group), a group of 3 (not a power of two) and one
-    of 64 on the per-head path, and the row-by-row plan.  With head_dim 128 and groups of 2 to 16 the default
-    launch runs the slim group kernel beside the tile kernel, serial_spans = 1 the group kernel after it."""
+    of 64 on the per-head path, and the row-by-row plan.  With head_dim 128 and groups of 2 to 16 row_launch = 2 or 3
+    and row_slots run the slim group kernel beside the tile kernel, serial_spans = 1 the group kernel after it."""
     ctx = [700, 33, 300, 1, 129, 1000, 64, 515, 2100, 90, 17, 40]
     qlen = [200, 1, 300, 1, 128, 257, 1, 130, 1, 1, 1, 40]
     rng = np.random.default_rng(H * 7 + Hkv + D)
@@ -124,7 +125,8 @@ def test_grouped_query_attention(H, Hkv, D):
     tunings = [dict(), dict(decode_part_tokens=64, span_part_tokens=128), dict(decode_part_tokens=256, span_part_tokens=64),
                dict(span_kernel=1), dict(span_kernel=1, decode_part_tokens=128), dict(serial_spans=1),
                dict(span_kernel=2), dict(span_kernel=2, decode_part_tokens=64, span_part_tokens=64),
-               dict(row_launch=3, serial_spans=1), dict(row_slots=5), dict(row_launch=3, serial_spans=1, row_slots=600)]
+               dict(row_launch=3, serial_spans=1), dict(row_slots=5), dict(row_launch=3, serial_spans=1, row_slots=600),
+               dict(row_launch=2), dict(row_launch=3, row_slots=600, decode_part_tokens=128)]
     _check_batch(batch, 300 + H + Hkv + D, tunings=tunings)
 
 
@@ -214,7 +216,9 @@ def test_random_long_batches_and_plans(seed):
 
 @pytest.mark.parametrize("H,Hkv,D,tuning", [(5, 5, 128, dict()), (5, 5, 128, dict(serial_spans=1, decode_part_tokens=128)),
                                             (4, 4, 256, dict()), (16, 2, 128, dict()), (3, 3, 64, dict(span_kernel=1)),
-                                            (8, 8, 64, dict(span_part_tokens=128, decode_part_tokens=64))])
+                                            (8, 8, 64, dict(span_part_tokens=128, decode_part_tokens=64)),
+                                            (5, 5, 64, dict(row_launch=2)), (5, 5, 128, dict(row_slots=3)), (16, 2, 128, dict(row_slots=3)),
+                                            (4, 4, 256, dict(row_launch=3, row_slots=7, decode_part_tokens=64))])
 def test_plan_once_run_for_every_layer(H, Hkv, D, tuning):
     """One plan, three layers (three pools of one shape, their own q), each layer run twice from the same
     descriptor image: bit-identical to paged_attn_mixed on that layer, which the oracle checks.  The
@@ -255,6 +259,37 @@ def test_plan_once_run_for_every_layer(H, Hkv, D, tuning):
     other.close()
     for pool, _, _, _ in layers:
         pool.close()
+
+
+@pytest.mark.parametrize("H,Hkv,D", [(40, 40, 64), (37, 37, 128), (64, 8, 128), (40, 40, 256)])
+def test_queues_beyond_the_first_round_start_again_from_zero(H, Hkv, D):
+    """Side by side with more tile items, few-key units and row items than workgroups, from one plan several times: the
+    queues hand out everything once and are back at zero for the next run."""
+    rng = np.random.default_rng(H + Hkv + D)
+    ctx, qlen = [1300, 900, 1500] + [200 + 17 * i for i in range(36)] + [9], [1300, 700, 33] + [1] * 37
+    batch = W.assemble_batch(H, D, 16, 1600, ctx, qlen, rng, num_kv_heads=Hkv)
+    pool_bits, q_bits = W.make_host_inputs(batch, 17 + D, poison_unused=True)
+    pool, keep = make_pool(pool_bits, H)
+    pool.set_tuning(row_launch=2)
+    desc = B.HostDesc.from_batch(batch)
+    how = pool.plan_image(desc)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert how["side_by_side"] and how["n_few_items"] == 1
+    assert how["n_tile_items"] * (H >> how["tile_head_shift"]) + how["n_few_items"] * ((H + 1) // 2) > cus
+    assert max(how["n_row_items"] - how["n_vector_row_items"], 0) * Hkv > cus or (how["n_vector_row_items"] - how["n_few_rows"]) * H > cus
+    r = AttnRunner(pool, batch, q_bits)
+    once = r.run().copy()
+    assert max_abs_err(once, oracle.attn_batch(batch, pool_bits, q_bits)) <= TOL
+    ws = torch.empty(pool.workspace_bytes(desc), dtype=torch.uint8, device=DEV)
+    plan = pool.plan_create(desc, ws.data_ptr(), ws.numel())
+    for rep in range(4):
+        r.out.fill_(0x7FFF)
+        pool.paged_attn_planned(plan, r.q.data_ptr(), r.out.data_ptr())
+        torch.cuda.synchronize()
+        assert np.array_equal(from_dev_bits(r.out), once), rep
+        assert not from_dev_bits(ws[:64].view(torch.int16)).any(), rep      # the counters at the head of the image
+    plan.close()
+    pool.close()
 
 
 @pytest.mark.parametrize("H,Hkv", [(2, 2), (8, 2)])
@@ -321,9 +356,10 @@ def test_wide_batch_of_short_decode_sequences():
     _check_batch(batch, 4242, tunings=((0, 0, 0), dict(row_launch=1), dict(row_launch=3)), grid_slack=True)
 
 
-def test_caller_stream_and_back_to_back_calls():
+@pytest.mark.parametrize("tuning", [dict(row_launch=2), dict()])
+def test_caller_stream_and_back_to_back_calls(tuning):
     """Calls issued back to back on a caller's (non-default) stream, alternating two batches that share
-    the pool's descriptor ring and side stream, give what each gives alone."""
+    the pool's descriptor ring and (row_launch = 2) side stream, give what each gives alone."""
     H, D = 5, 128
     rng = np.random.default_rng(404)
     b1 = W.assemble_batch(H, D, 16, 512, [700, 33, 300, 1000, 2100], [200, 1, 300, 1, 1], rng)
@@ -333,7 +369,10 @@ def test_caller_stream_and_back_to_back_calls():
     want1 = oracle.attn_batch(b1, pool_bits, q1)
     want2 = oracle.attn_batch(b2, pool_bits, q2)
     pool, keep = make_pool(pool_bits)
+    pool.set_tuning(**tuning)
     r1, r2 = AttnRunner(pool, b1, q1), AttnRunner(pool, b2, q2)
+    for r in (r1, r2):
+        assert pool.plan_launches(r.desc)["side_by_side"] == bool(tuning)
     st = torch.cuda.Stream()
     for r in (r1, r2):
         r.ws = torch.empty(pool.workspace_bytes(r.desc), dtype=torch.uint8, device=DEV)
@@ -347,9 +386,11 @@ def test_caller_stream_and_back_to_back_calls():
     pool.close()
 
 
-def test_two_pools_on_two_streams_share_the_side_stream():
+@pytest.mark.parametrize("tuning", [dict(row_launch=2), dict()])
+def test_two_pools_on_two_streams_share_the_side_stream(tuning):
     """Two pools (two layers, say), each driven on a stream of its own with several calls in flight: their tile
-    kernels share the one side stream of the device, their row kernels the CUs; every call gives what it gives alone."""
+    kernels share the one side stream of the device (row_launch = 2), their row kernels the CUs; every call gives what it
+    gives alone."""
     H, D = 5, 128
     rng = np.random.default_rng(808)
     b1 = W.assemble_batch(H, D, 16, 512, [700, 33, 300, 1000, 2100], [200, 1, 300, 1, 1], rng)
@@ -359,7 +400,11 @@ def test_two_pools_on_two_streams_share_the_side_stream():
     want1, want2 = oracle.attn_batch(b1, bits1, q1), oracle.attn_batch(b2, bits2, q2)
     pool1, keep1 = make_pool(bits1)
     pool2, keep2 = make_pool(bits2)
+    pool1.set_tuning(**tuning)
+    pool2.set_tuning(**tuning)
     r1, r2 = AttnRunner(pool1, b1, q1), AttnRunner(pool2, b2, q2)
+    for r, pool in ((r1, pool1), (r2, pool2)):
+        assert pool.plan_launches(r.desc)["side_by_side"] == bool(tuning)
     s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
     for r, pool in ((r1, pool1), (r2, pool2)):
         r.ws = torch.empty(pool.workspace_bytes(r.desc), dtype=torch.uint8, device=DEV)

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import oracle
+from paper_2402_01869_amd import binding as B
 from paper_2402_01869_amd import workloads as W
 from gpu_common import AttnRunner, make_pool
 
@@ -17,6 +18,9 @@ EDGES = [(2, 2), (15, 15), (16, 16), (17, 17), (33, 33), (62, 62), (63, 63), (64
 def _run(batch, pool_bits, q_bits, **tuning):
     pool, keep = make_pool(pool_bits, batch.num_heads)
     pool.set_tuning(**tuning)
+    if tuning.get("span_kernel") != 1:
+        how = pool.plan_launches(B.HostDesc.from_batch(batch))
+        assert how["n_few_items"] > 0 and how["side_by_side"] == ("row_launch" in tuning)
     out = W.bf16_bits_to_f64(AttnRunner(pool, batch, q_bits).run())
     pool.close()
     return out
@@ -31,7 +35,8 @@ def test_few_key_rows_match_the_vector_kernel(H, Hkv, D):
     want = oracle.attn_batch(batch, pool_bits, q_bits)
     rows = np.concatenate([np.arange(c - n, c) for c, n in EDGES]) < 63   # rows that see fewer than 64 keys
     by_row = _run(batch, pool_bits, q_bits, span_kernel=1)
-    for tuning in (dict(), dict(serial_spans=1), dict(mfma_min_keys=64), dict(mfma_min_keys=30)):
+    # alone, beside the slim row or group kernel, and with another limit
+    for tuning in (dict(), dict(row_launch=2), dict(row_launch=3, row_slots=9), dict(mfma_min_keys=30)):
         got = _run(batch, pool_bits, q_bits, **tuning)
         assert np.isfinite(got).all()
         mine = rows if tuning.get("mfma_min_keys", 64) == 64 else np.concatenate([np.arange(c - n, c) for c, n in EDGES]) < 29
@@ -44,13 +49,13 @@ def test_few_key_rows_match_the_vector_kernel(H, Hkv, D):
 @pytest.mark.parametrize("D", [64, 128, 256])
 def test_few_key_rows_with_infinite_and_nan_values(D):
     """An infinite or NaN value shows in exactly the rows that see its key, as on the vector kernel."""
-    H = 3
-    batch = W.assemble_batch(H, D, 16, 64, [50, 63, 30], [50, 63, 20], np.random.default_rng(D))
+    H, few = 3, 50 + 63 + 20 + 63      # the last chunk's other rows are a tile item, beside which the units run
+    batch = W.assemble_batch(H, D, 16, 64, [50, 63, 30, 90], [50, 63, 20, 90], np.random.default_rng(D))
     pool_bits, q_bits = W.make_host_inputs(batch, 9, poison_unused=True)
     for s, key, head, dim, bits in ((0, 20, 0, 3, 0x7F80), (0, 33, 1, D - 1, 0xFF80), (1, 62, 2, 17, 0x7FC0), (2, 12, 0, 0, 0x7F80)):
         pool_bits[batch.block_tables[s, key // 16], 1, head, key % 16, dim] = bits
-    by_row = _run(batch, pool_bits, q_bits, span_kernel=1)
-    got = _run(batch, pool_bits, q_bits)
+    by_row = _run(batch, pool_bits, q_bits, span_kernel=1)[:few]
+    got = _run(batch, pool_bits, q_bits)[:few]
     fine = np.isfinite(by_row)
     assert not fine.all() and fine.any()
     assert np.array_equal(np.isnan(got), np.isnan(by_row)) and np.array_equal(got[~fine & ~np.isnan(got)], by_row[~fine & ~np.isnan(by_row)])

@@ -69,6 +69,20 @@ def test_few_key_rows_become_units_only_beside_tiles_or_in_numbers():
     assert beside["off_merge_items"] - beside["off_tile_items"] >= 512  # both
 
 
+@pytest.mark.parametrize("H,Hkv,D,ctx,q_len", [(4, 4, 64, [16, 100, 64, 90], [1, 1, 32, 32]), (16, 16, 256, [200, 700], [200, 1]),
+                                               (64, 8, 128, [700, 300], [1, 40]), (6, 2, 128, [9, 200], [1, 100])])
+def test_asking_for_persistent_rows_asks_for_both_kernels_side_by_side(H, Hkv, D, ctx, q_len):
+    """By itself a small batch runs one kernel after the other; with persistent row workgroups asked for it runs the pair."""
+    assert not _plan(H, Hkv, D, ctx, q_len)["side_by_side"] and not _plan(H, Hkv, D, ctx, q_len, row_launch=1)["side_by_side"]
+    for tuning in (dict(row_launch=2), dict(row_launch=3), dict(row_slots=7)):
+        plan = _plan(H, Hkv, D, ctx, q_len, **tuning)
+        assert plan["side_by_side"] and plan["tile_launch"] == B.IC_LAUNCH_PERSISTENT
+        assert {plan["row_launch"], plan["group_launch"]} <= {B.IC_LAUNCH_NONE, B.IC_LAUNCH_SLIM}
+        assert plan["n_merged_inside"] == 0                  # from a queue the merge kernel merges
+        assert not _plan(H, Hkv, D, ctx, q_len, serial_spans=1, **tuning)["side_by_side"]
+        assert not _plan(H, Hkv, D, ctx[:1], q_len[:1], **tuning)["side_by_side"]     # nothing to run beside
+
+
 @pytest.mark.parametrize("H,Hkv,D", [(4, 4, 64), (5, 5, 128), (2, 2, 256), (64, 8, 128), (6, 2, 64)])
 def test_few_items_and_split_slots_of_the_image(H, Hkv, D):
     """Every few item covers consecutive rows of one sequence, each such row exactly once; every partial slot of a row that
