@@ -191,7 +191,8 @@ struct PlanSizes {
   bool few_as_units;                   // few-key rows of spans go to the tile kernels' few-key body
   bool decode_as_tiles;                // grouped pools, span_kernel = 2: decode rows as one-row tile items
   bool decode_as_group;                // grouped pools: decode rows stay row items, run by the group kernel
-  bool side_by_side;                   // both kernels are long enough to pay for a second stream
+  bool slim_group;                     // the group kernel has a slim build for the shape
+  bool side_by_side;                   // the tile kernel beside the slim row or group kernel, on two streams
   bool row_per_item;                   // the vector kernel's items are short, or split by choose_row_part: one workgroup each, no queue
   bool tile_leads;                     // the tile items are expected to take longer than the row items
   size_t off_ctr, off_bt_off, off_bt_flat, off_row, off_tile, off_few, off_merge, off_row_dst, off_slot_merge, off_arrived, image_bytes;
@@ -233,6 +234,44 @@ SeqRoute route(const PlanSizes& ps, int c, int n) {
   // A decode row stays with the vector kernel: alone in its sequence it would fill one of a unit's 64 rows.
   r.few_unit = r.n_few > 0 && n > 1 && ps.few_as_units;
   return r;
+}
+
+// Expected times of a batch with both kinds of work, in us, for the choice between the two launches of it.  Fitted to 4184
+// calls of 892 batches (4 to 40 K/V heads of 64, 128, 256 dims, 1 to 2000 decode rows of 40 to 8000 keys, 1 to 22 chunks;
+// rms 8 %).  Of the two the one with the shorter expected time took 1.7 % longer than the better one in the mean; side by side
+// always 16 % (up to 3.5 times: thousands of rows of 40 keys), one after the other below a threshold of the shorter kernel's time
+// (30, 45 or 110 us) 6 %.
+struct RowLoad {
+  int64_t items = 0;                 // work items x (query heads on the vector kernel, K/V heads on the group kernel)
+  double bytes = 0.0, longest = 0.0; // K/V bytes they read, of the longest item
+  bool group = false;                // the group kernel's
+  void add(int64_t n, int64_t keys, int most, int heads, int head_dim) {
+    items += n * heads;
+    bytes += (double)keys * heads * 4.0 * head_dim;
+    longest = std::max(longest, most * 4.0 * head_dim);
+  }
+};
+
+// Whole tile items: a 64-key step of a workgroup at 1.1 (head_dim 128: 1.4) PFLOP/s over all CUs, two steps more per item, and
+// half an item where more than one round leaves the last ones running alone.
+double tiles_us(int head_dim, int64_t items, int64_t steps, int64_t most) {
+  if (items == 0) return 0.0;
+  const double step = 4.0 * tile_rows(head_dim) * 64 * head_dim / ((head_dim == 128 ? 1.38e9 : 1.12e9) / kExpectedCus);
+  const double one = most + 2.0, all = (steps + 2.0 * items) / kExpectedCus + (items > kExpectedCus ? 0.5 * one : 0.0);
+  return step * std::max(one, all);
+}
+
+// Side by side the rows come from the queue of one workgroup per CU: 2.4 us an item and 37 to 46 GB/s a workgroup (group kernel 65);
+// the shorter of the two kernels costs the longer one 0.44 of its own time.  Fork, join and the upload: 28 us.
+double side_by_side_us(int head_dim, double tiles, const RowLoad& r) {
+  const double wg = r.group ? 65e3 : head_dim == 64 ? 39e3 : head_dim == 128 ? 46e3 : 37e3;
+  const double rows = std::max({r.bytes / 6.2e6, (r.items * 2.4 + r.bytes / wg) / kExpectedCus, r.longest / wg + 2.4});
+  return 28.0 + std::max(tiles, rows) + 0.44 * std::min(tiles, rows);
+}
+
+// One after the other the rows run at the memory's rate, or as long as the longest item takes (choose_row_part's rates).
+double serial_us(int head_dim, double tiles, const RowLoad& r) {
+  return 20.0 + tiles + std::max(r.bytes / 5.95e6, r.longest / (head_dim == 64 ? 22e3 : head_dim == 128 ? 38e3 : 50e3));
 }
 
 // Keys per decode work item when the caller leaves the choice to the library.  Whole rows (up to kDefaultRowPart keys)
@@ -401,7 +440,8 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, bool
   ic_plan_info& in = ps.info;
   double tile_pairs = 0, row_keys = 0;  // (query row, key) pairs of the tile items; keys of the row items
   double vec_keys = 0;                  // ... of those on the vector kernel
-  int64_t tile_steps = 0, most_steps = 0, most_keys = 0;  // 64-key steps over all tile items and of the longest; keys of the longest row item
+  int64_t tile_steps = 0, most_steps = 0;  // 64-key steps over all tile items and of the longest
+  int most_vec = 0, most_group = 0;      // keys of the longest row item of each kernel
   for (int s = 0; s < d->num_seqs; ++s) {
     const int c = d->ctx_len[s], n = d->q_len[s];
     in.table_entries += (c + kBlockSize - 1) / kBlockSize;
@@ -418,8 +458,10 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, bool
       in.row_items += parts;
       if (!rt.few_unit) {
         row_keys += klen;
-        if (i < rt.n_few || !rt.rest_group) vec_keys += klen;
-        most_keys = std::max<int64_t>(most_keys, std::min(klen, ps.row_part));
+        const bool vec = i < rt.n_few || !rt.rest_group;
+        if (vec) vec_keys += klen;
+        int& most = vec ? most_vec : most_group;
+        most = std::max(most, std::min(klen, ps.row_part));
       }
       if (i < rt.n_few || !rt.rest_group) ps.vec_items += parts;
       if (parts > 1) { in.partial_slots += parts; in.merge_rows += 1; ps.row_slots += parts; ps.row_merges += 1; }
@@ -443,22 +485,22 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, bool
   // 0.9 PFLOP/s at 4 D flop per pair and head, row kernels 5.5 TB/s at 4 D bytes per key and K/V head): that one
   // goes on the caller's stream, the other through the fork and join of the second stream.  (head_dim 256: 0.5 PFLOP/s.)
   ps.tile_leads = tile_pairs * H * (4.0 * D / (D > 128 ? 0.5e15 : 0.9e15)) > row_keys * pool->cfg.num_kv_heads * (4.0 * D / 5.5e12);
-  const double step_us = tile_step_us(D);
-  const int64_t n_th = H >> ps.tile_g_shift;
-  const double tile_us = std::max((double)tile_steps * n_th / kExpectedCus, (double)most_steps) * step_us;
-  const double key_bytes = 4.0 * D;  // K and V of one key and K/V head
-  // a workgroup of the row kernels alone on its CU reads 40 GB/s
-  const double row_us = std::max(row_keys * pool->cfg.num_kv_heads * key_bytes / 5.5e6, (double)most_keys * key_bytes / 40e3);
-  const int n_vec = ps.vec_items - ps.few_rows;
-  const bool short_rows = n_vec > 0 && vec_keys * key_bytes < n_vec * kShortItemBytes;
+  const int n_vec = ps.vec_items - ps.few_rows, n_group = in.row_items - ps.vec_items;
+  const bool short_rows = n_vec > 0 && vec_keys * (4.0 * D) < n_vec * kShortItemBytes;
   ps.row_per_item = short_rows || (t.decode_part_tokens == 0 && ps.row_part < kDefaultRowPart);
-  // Two streams cost a fork and a join (13 us on the way of the kernel that ends last; kernels on one stream follow each
-  // other without a gap), and each kernel takes longer beside the other than alone, so they pay only when the shorter
-  // one is long enough.  Measured, us a call side by side / one after the other (in brackets the expected time of the
-  // shorter kernel, us): 40 heads, head_dim 128: 43 / 16 (2), 79 / 95 (33), 226 / 247 (43), 91 / 107 (45), 303 / 328 (97);
-  // grouped, 64 over 8: 254 / 259 (29), 102 / 98 (43), 114 / 133 (47), 187 / 203 (94); head_dim 256: 132 / 146 (95), 308 /
-  // 363 (220).  Short rows, three times faster as one workgroup per item than from the queue: 105 / 101 (30), 150 / 122 (45).
-  ps.side_by_side = std::min(tile_us, row_us) > (short_rows ? 110.0 : ps.decode_as_group || D > 128 ? 45.0 : 30.0);
+  // Side by side: tile items or few-key units beside rows of a kernel that has a slim build, unless one after the other is
+  // expected to take 4 % less, or because the caller asks for persistent row workgroups.
+  ps.slim_group = D == 128 && G <= 16;
+  ps.side_by_side = (in.tile_items > 0 || ps.few_runs > 0) && !t.serial_spans && (ps.decode_as_group ? n_group > 0 && ps.slim_group : n_vec > 0);
+  if (ps.side_by_side && t.row_launch < 2 && t.row_slots == 0) {
+    const int64_t n_th = H >> ps.tile_g_shift;
+    const double tiles_time = tiles_us(D, in.tile_items * n_th, tile_steps * n_th, most_steps);
+    RowLoad rows;
+    rows.group = n_group > 0;
+    rows.add(n_vec, (int64_t)vec_keys, most_vec, H, D);
+    rows.add(n_group, (int64_t)(row_keys - vec_keys), most_group, pool->cfg.num_kv_heads, D);
+    ps.side_by_side = side_by_side_us(D, tiles_time, rows) < 1.04 * serial_us(D, tiles_time, rows);
+  }
   size_t o = 0;
   ps.off_ctr = o;     o = align_up(o + sizeof(int32_t) * 16, 256);
   ps.off_bt_off = o;  o = align_up(o + sizeof(int32_t) * (size_t)d->num_seqs, 256);
@@ -493,12 +535,10 @@ struct PlanLaunches {
 PlanLaunches plan_launches(const ic_pool* pool, const PlanSizes& ps) {
   const ic_tuning& t = pool->tune;
   const int D = pool->cfg.head_dim;
-  const bool slim_group = D == 128 && pool->cfg.num_heads / pool->cfg.num_kv_heads <= 16;
   const bool tiles = ps.info.tile_items > 0 || ps.few_runs > 0;
   const bool rows = ps.vec_items > ps.few_rows, groups = ps.info.row_items > ps.vec_items;
   PlanLaunches how;
-  const bool asked = t.row_launch >= 2 || t.row_slots > 0;
-  how.side_by_side = tiles && (ps.side_by_side || asked) && !t.serial_spans && (ps.decode_as_group ? groups && slim_group : rows);
+  how.side_by_side = ps.side_by_side;
   // head_dim <= 128: the persistent tile launch also when no other kernel runs beside it.  Its per-XCD queues keep the
   // query tiles of one (sequence, head) on one L2: on 2048-row chunks the spans then fetch 2.6 x instead of 6.9 x
   // their keys from HBM and finish 7 % sooner (9.66 against 10.41 ms); shorter chunks and grouped pools: no change.
@@ -506,7 +546,7 @@ PlanLaunches plan_launches(const ic_pool* pool, const PlanSizes& ps) {
   // its neighbour and is 19 % slower alone (0.197 against 0.166 ms on the GPT-J-shaped chunks).
   how.tile = !tiles ? IC_LAUNCH_NONE : how.side_by_side || D <= 128 ? IC_LAUNCH_PERSISTENT : IC_LAUNCH_PER_ITEM;
   // row_launch = 3: the side-by-side builds, alone
-  how.group = !groups ? IC_LAUNCH_NONE : how.side_by_side || (t.row_launch == 3 && slim_group) ? IC_LAUNCH_SLIM : IC_LAUNCH_PER_ITEM;
+  how.group = !groups ? IC_LAUNCH_NONE : how.side_by_side || (t.row_launch == 3 && ps.slim_group) ? IC_LAUNCH_SLIM : IC_LAUNCH_PER_ITEM;
   how.row = !rows ? IC_LAUNCH_NONE
             : how.side_by_side || t.row_launch == 3 ? IC_LAUNCH_SLIM
             : t.row_launch == 1 || (t.row_launch == 0 && t.row_slots == 0 && ps.row_per_item) ? IC_LAUNCH_PER_ITEM

@@ -69,6 +69,34 @@ def test_few_key_rows_become_units_only_beside_tiles_or_in_numbers():
     assert beside["off_merge_items"] - beside["off_tile_items"] >= 512  # both
 
 
+@pytest.mark.parametrize("H,Hkv,D,n,keys,n_span,pair", [
+    # decode rows x keys beside chunks of 512 rows on 1500 keys; measured side by side / one after the other, us
+    (40, 40, 128, 43, 560, 2, True),      # 112 / 145
+    (40, 40, 128, 46, 350, 4, True),      # 140 / 179
+    (16, 16, 256, 100, 200, 3, True),     # 108 / 140
+    (32, 32, 64, 54, 1100, 6, True),      # 132 / 170
+    (64, 8, 128, 40, 1500, 2, True),      # 98 / 119
+    (16, 4, 128, 54, 1500, 5, True),      # 78 / 101
+    (40, 40, 128, 604, 40, 2, False),     # 318 / 161: the queue, not the memory
+    (32, 32, 64, 1007, 40, 6, False),     # 413 / 155
+    (40, 40, 128, 483, 100, 2, False),    # 299 / 239
+    (16, 16, 256, 755, 40, 2, False),     # 204 / 165
+])
+def test_batches_run_side_by_side_where_that_is_faster(H, Hkv, D, n, keys, n_span, pair):
+    ctx, q_len = [keys] * n + [2012] * n_span, [1] * n + [512] * n_span
+    assert bool(_plan(H, Hkv, D, ctx, q_len)["side_by_side"]) == pair
+    # one request that has just begun to decode changes nothing for the others
+    assert bool(_plan(H, Hkv, D, [40] + ctx, [1] + q_len)["side_by_side"]) == pair
+
+
+@pytest.mark.parametrize("n_span", [1, 2, 3])
+def test_one_short_decode_row_leaves_a_grouped_batch_side_by_side(n_span):
+    ctx = [2000] * 64 + [2500] * n_span
+    for short in (0, 1, 5):
+        plan = _plan(64, 8, 128, [40] * short + ctx[short:], [1] * 64 + [512] * n_span)
+        assert plan["side_by_side"] and plan["group_launch"] == B.IC_LAUNCH_SLIM
+
+
 @pytest.mark.parametrize("H,Hkv,D,ctx,q_len", [(4, 4, 64, [16, 100, 64, 90], [1, 1, 32, 32]), (16, 16, 256, [200, 700], [200, 1]),
                                                (64, 8, 128, [700, 300], [1, 40]), (6, 2, 128, [9, 200], [1, 100])])
 def test_asking_for_persistent_rows_asks_for_both_kernels_side_by_side(H, Hkv, D, ctx, q_len):
