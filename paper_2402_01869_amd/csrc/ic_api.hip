@@ -236,42 +236,53 @@ SeqRoute route(const PlanSizes& ps, int c, int n) {
   return r;
 }
 
-// Expected times of a batch with both kinds of work, in us, for the choice between the two launches of it.  Fitted to 4184
-// calls of 892 batches (4 to 40 K/V heads of 64, 128, 256 dims, 1 to 2000 decode rows of 40 to 8000 keys, 1 to 22 chunks;
-// rms 8 %).  Of the two the one with the shorter expected time took 1.7 % longer than the better one in the mean; side by side
-// always 16 % (up to 3.5 times: thousands of rows of 40 keys), one after the other below a threshold of the shorter kernel's time
-// (30, 45 or 110 us) 6 %.
+// Expected times of a batch with both kinds of work, in us, for the choice between the two launches of it and of the decode
+// rows' partition.  Fitted to 4184 calls of 892 batches (4 to 40 K/V heads of 64, 128, 256 dims, 1 to 2000 decode rows of 40 to
+// 9600 keys, 1 to 22 chunks, the rows whole and in partitions of 384 to 2048 keys; rms 7 %).  What these times choose took 1.6 %
+// longer in the mean than the best of what was measured for the batch (at most 17 %); whole rows always side by side 16 % (up
+// to 3.5 times: thousands of rows of 40 keys), and one after the other below a threshold on the shorter kernel's time 6 %.
 struct RowLoad {
-  int64_t items = 0;                 // work items x (query heads on the vector kernel, K/V heads on the group kernel)
-  double bytes = 0.0, longest = 0.0; // K/V bytes they read, of the longest item
-  bool group = false;                // the group kernel's
-  void add(int64_t n, int64_t keys, int most, int heads, int head_dim) {
-    items += n * heads;
-    bytes += (double)keys * heads * 4.0 * head_dim;
-    longest = std::max(longest, most * 4.0 * head_dim);
-  }
+  int64_t items = 0;                  // work items x (query heads on the vector kernel, K/V heads on the group kernel)
+  double bytes = 0.0, longest = 0.0;  // K/V bytes they read, of the longest item
+  int64_t long_items = 0;             // items of at least 3/4 of the longest
+  bool group = false;                 // some are the group kernel's
 };
 
-// Whole tile items: a 64-key step of a workgroup at 1.1 (head_dim 128: 1.4) PFLOP/s over all CUs, two steps more per item, and
-// half an item where more than one round leaves the last ones running alone.
-double tiles_us(int head_dim, int64_t items, int64_t steps, int64_t most) {
+// What differs between head_dim 64, 128, 256 and the group kernel's pools.
+struct LaunchRates {
+  double tile_flops;  // per us, all CUs: 64-key steps of tile workgroups
+  double row_many;    // K/V bytes per us of a persistent row workgroup among many,
+  double row_one;     // ... of the longest item's, beside a tile workgroup,
+  double row_alone;   // ... of a workgroup of the stand-alone launches on a CU of its own
+  double pair_us;     // fork, join and upload
+};
+const LaunchRates& launch_rates(int head_dim, bool group) {
+  static const LaunchRates rates[4] = {{1.11e9, 40e3, 39e3, 22e3, 29.0}, {1.29e9, 92e3, 41e3, 38e3, 26.0},
+                                       {1.15e9, 100e3, 38e3, 50e3, 35.5}, {1.44e9, 28e3, 64e3, 38e3, 32.0}};
+  return rates[group ? 3 : head_dim == 64 ? 0 : head_dim == 128 ? 1 : 2];
+}
+
+// Tile items, two steps more per item, and half an item where more than one round leaves the last ones running alone.
+double tiles_us(const LaunchRates& rate, int head_dim, int64_t items, int64_t steps, int64_t most) {
   if (items == 0) return 0.0;
-  const double step = 4.0 * tile_rows(head_dim) * 64 * head_dim / ((head_dim == 128 ? 1.38e9 : 1.12e9) / kExpectedCus);
-  const double one = most + 2.0, all = (steps + 2.0 * items) / kExpectedCus + (items > kExpectedCus ? 0.5 * one : 0.0);
+  const double step = 4.0 * tile_rows(head_dim) * 64 * head_dim / (rate.tile_flops / kExpectedCus);
+  const double one = most + 2.0, all = (steps + 2.0 * items) / kExpectedCus + (items > kExpectedCus ? 0.54 * one : 0.0);
   return step * std::max(one, all);
 }
 
-// Side by side the rows come from the queue of one workgroup per CU: 2.4 us an item and 37 to 46 GB/s a workgroup (group kernel 65);
-// the shorter of the two kernels costs the longer one 0.44 of its own time.  Fork, join and the upload: 28 us.
-double side_by_side_us(int head_dim, double tiles, const RowLoad& r) {
-  const double wg = r.group ? 65e3 : head_dim == 64 ? 39e3 : head_dim == 128 ? 46e3 : 37e3;
-  const double rows = std::max({r.bytes / 6.2e6, (r.items * 2.4 + r.bytes / wg) / kExpectedCus, r.longest / wg + 2.4});
-  return 28.0 + std::max(tiles, rows) + 0.44 * std::min(tiles, rows);
+// Side by side the rows come from the queue of one workgroup per CU, 2.7 us an item; up to two rounds of long ones run one
+// after the other.  The shorter of the two kernels costs the longer one 0.4 of its own time.
+double side_by_side_us(const LaunchRates& rate, double tiles, const RowLoad& r) {
+  const int64_t rounds = (r.long_items + kExpectedCus - 1) / kExpectedCus;
+  const double rows = std::max({r.bytes / 6.35e6, (r.items * 2.7 + r.bytes / rate.row_many) / kExpectedCus,
+                                (rounds <= 2 ? rounds : 1) * (r.longest / rate.row_one + 2.7)});
+  return rate.pair_us + std::max(tiles, rows) + 0.4 * std::min(tiles, rows);
 }
 
-// One after the other the rows run at the memory's rate, or as long as the longest item takes (choose_row_part's rates).
-double serial_us(int head_dim, double tiles, const RowLoad& r) {
-  return 20.0 + tiles + std::max(r.bytes / 5.95e6, r.longest / (head_dim == 64 ? 22e3 : head_dim == 128 ? 38e3 : 50e3));
+// One after the other the rows run at the memory's rate, or as long as the longest item takes.  Few-key units cost less than
+// behind tile items that share the CUs.
+double serial_us(const LaunchRates& rate, double tiles, const RowLoad& r, bool few_units) {
+  return (few_units ? 17.5 : 24.5) + tiles + std::max(r.bytes / 6.15e6, r.longest / rate.row_alone);
 }
 
 // Keys per decode work item when the caller leaves the choice to the library.  Whole rows (up to kDefaultRowPart keys)
@@ -325,6 +336,80 @@ int choose_row_part(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes
       best = part;
       best_us = us;
     }
+  }
+  return best;
+}
+
+// The row items of a batch whose decode rows are cut into items of `part` keys.
+RowLoad row_load(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& ps, int part) {
+  const double key_bytes = 4.0 * pool->cfg.head_dim;
+  RowLoad load;
+  int longest = 0;
+  for (int s = 0; s < d->num_seqs; ++s)
+    if (d->q_len[s] == 1) longest = std::max(longest, std::min(d->ctx_len[s], part));
+  for (int s = 0; s < d->num_seqs; ++s) {
+    const int c = d->ctx_len[s], n = d->q_len[s];
+    const SeqRoute rt = route(ps, c, n);
+    if (n == 1 && (rt.rest_rows || rt.n_few > 0)) {
+      const bool group = rt.rest_group && rt.n_few == 0;
+      const int64_t units = group ? pool->cfg.num_kv_heads : pool->cfg.num_heads;
+      load.group = load.group || group;
+      load.items += (c + part - 1) / part * units;
+      load.bytes += key_bytes * c * units;
+      load.long_items += (c / part + (4 * (int64_t)(c % part) >= 3 * (int64_t)longest)) * units;
+    } else if (n > 1 && rt.n_few > 0 && !rt.few_unit) {
+      const int last = c - n + rt.n_few;  // keys of the last of these rows
+      load.items += (int64_t)rt.n_few * pool->cfg.num_heads;
+      load.bytes += key_bytes * pool->cfg.num_heads * rt.n_few * (last - 0.5 * (rt.n_few - 1));
+    }
+  }
+  load.longest = key_bytes * longest;
+  return load;
+}
+
+// Its tile items.
+double tile_load_us(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& ps) {
+  int64_t items = 0, steps = 0, most = 0;
+  for (int s = 0; s < d->num_seqs; ++s) {
+    const int c = d->ctx_len[s], n = d->q_len[s], part = n == 1 ? ps.row_part : ps.span_part;
+    const SeqRoute rt = route(ps, c, n);
+    if (rt.rest_rows) continue;
+    for (int r0 = rt.n_few; r0 < n; r0 += ps.tile_rows) {
+      const int klen = c - n + std::min(n, r0 + ps.tile_rows);
+      items += (klen - 1) / part + 1;
+      steps += (klen + 63) / 64;
+      most = std::max<int64_t>(most, (std::min(klen, part) + 63) / 64);
+    }
+  }
+  const int64_t n_th = pool->cfg.num_heads >> ps.tile_g_shift;
+  return tiles_us(launch_rates(pool->cfg.head_dim, ps.decode_as_group), pool->cfg.head_dim, items * n_th, steps * n_th, most);
+}
+
+// Keys per decode work item beside tile items that are expected to take tiles_time.  While whole rows give fewer items than
+// CUs the finer partition wins ties, because one long item slows the tile workgroup on its CU and the next CU has none; from
+// then on it has to be expected to save 1.5 %.  A merge launch, where the spans need none, costs 5 us.  Measured, whole rows /
+// 1024 keys an item: 40 heads, 3 rows of 4000 keys and 2 chunks of 512 on 2000 116 / 94, 7 such rows and 3 chunks on 1500 159 /
+// 132, 16 heads of 256 dims, 6 and 2 161 / 113; where the tiles lead, 40 heads, 5 and 4 chunks on 2500 200 / 204.
+int choose_row_part_beside(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& ps, double tiles_time, double* us) {
+  static const int parts[] = {kDefaultRowPart, 2048, 1024, 768, 512, 384};
+  const LaunchRates& rate = launch_rates(pool->cfg.head_dim, ps.decode_as_group);
+  const double merge = ps.span_part == kWholeSpan ? 5.0 : 0.0;
+  int best = kDefaultRowPart, longest = 0;
+  for (int s = 0; s < d->num_seqs; ++s)
+    if (d->q_len[s] == 1) longest = std::max(longest, d->ctx_len[s]);
+  int64_t items = 0;
+  double least = 0.0;
+  for (const int part : parts) {
+    if (part >= longest && part != kDefaultRowPart) continue;  // no other plan than whole rows
+    const RowLoad rows = row_load(pool, d, ps, part);
+    const double t = side_by_side_us(rate, tiles_time, rows) + (longest > part ? merge : 0.0);
+    if (least == 0.0 || t < (items < kExpectedCus ? 1.02 : 0.985) * least) {
+      best = part;
+      items = rows.items;
+      *us = t;
+      least = least == 0.0 ? t : std::min(least, t);
+    }
+    if (rows.items >= 4 * kExpectedCus) break;  // rounds enough: a finer partition only adds items
   }
   return best;
 }
@@ -417,8 +502,7 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, bool
   ps.spans_as_rows = (t.span_kernel == 1);  // default: MFMA tiles
   ps.decode_as_tiles = ps.tile_g_shift > 0 && t.span_kernel == 2;
   ps.decode_as_group = ps.tile_g_shift > 0 && t.span_kernel == 0;
-  ps.row_part = t.decode_part_tokens > 0 ? round64(t.decode_part_tokens) : compact ? kDefaultRowPart : choose_row_part(pool, d, ps);
-  ps.row_part = std::min(ps.row_part, kMaxRowPart);
+  ps.row_part = std::min(t.decode_part_tokens > 0 ? round64(t.decode_part_tokens) : kDefaultRowPart, kMaxRowPart);
   int64_t tiles = 0, few = 0;  // unsplit query tiles; rows of spans with few keys
   for (int s = 0; s < d->num_seqs; ++s)
     if (d->q_len[s] > 1) {
@@ -437,11 +521,31 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, bool
       if (d->q_len[s] == 1) row_us += d->ctx_len[s] * (4.0 * pool->cfg.head_dim * pool->cfg.num_kv_heads / 5.5e6);
     ps.span_part = compact || ps.spans_as_rows || tiles * head_groups >= kUnsplitWorkgroups ? kWholeSpan : choose_span_part(pool, d, ps, row_us);
   }
+  // Side by side: tile items or few-key units beside rows of a kernel that has a slim build, unless one after the other is
+  // expected to take 4 % less, or not 2 % more where the rows are split (their last partitions merge them there), or because
+  // the caller asks for persistent row workgroups.  The decode rows' partition goes with the launch.
+  ps.slim_group = pool->cfg.head_dim == 128 && G <= 16;
+  {
+    const double tiles_time = tile_load_us(pool, d, ps);
+    const RowLoad whole = row_load(pool, d, ps, ps.row_part);
+    const bool choose = t.decode_part_tokens == 0 && !compact;
+    const int part_alone = choose ? choose_row_part(pool, d, ps) : ps.row_part;
+    ps.side_by_side = (tiles_time > 0.0 || (ps.few_as_units && few > 0)) && !t.serial_spans && whole.items > 0 &&
+                      (ps.decode_as_group ? whole.group && ps.slim_group : true);
+    if (ps.side_by_side) {
+      const LaunchRates& rate = launch_rates(pool->cfg.head_dim, ps.decode_as_group);
+      double beside = side_by_side_us(rate, tiles_time, whole);
+      const int part_beside = choose ? choose_row_part_beside(pool, d, ps, tiles_time, &beside) : ps.row_part;
+      const double serial = serial_us(rate, tiles_time, row_load(pool, d, ps, part_alone), ps.few_as_units && few > 0);
+      ps.side_by_side = t.row_launch >= 2 || t.row_slots > 0 || beside < (part_beside < ps.row_part ? 0.98 : 1.04) * serial;
+      ps.row_part = ps.side_by_side ? part_beside : part_alone;
+    } else {
+      ps.row_part = part_alone;
+    }
+  }
   ic_plan_info& in = ps.info;
   double tile_pairs = 0, row_keys = 0;  // (query row, key) pairs of the tile items; keys of the row items
   double vec_keys = 0;                  // ... of those on the vector kernel
-  int64_t tile_steps = 0, most_steps = 0;  // 64-key steps over all tile items and of the longest
-  int most_vec = 0, most_group = 0;      // keys of the longest row item of each kernel
   for (int s = 0; s < d->num_seqs; ++s) {
     const int c = d->ctx_len[s], n = d->q_len[s];
     in.table_entries += (c + kBlockSize - 1) / kBlockSize;
@@ -458,10 +562,7 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, bool
       in.row_items += parts;
       if (!rt.few_unit) {
         row_keys += klen;
-        const bool vec = i < rt.n_few || !rt.rest_group;
-        if (vec) vec_keys += klen;
-        int& most = vec ? most_vec : most_group;
-        most = std::max(most, std::min(klen, ps.row_part));
+        if (i < rt.n_few || !rt.rest_group) vec_keys += klen;
       }
       if (i < rt.n_few || !rt.rest_group) ps.vec_items += parts;
       if (parts > 1) { in.partial_slots += parts; in.merge_rows += 1; ps.row_slots += parts; ps.row_merges += 1; }
@@ -474,8 +575,6 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, bool
         const int parts = (klen + part - 1) / part;
         in.tile_items += parts;
         tile_pairs += (double)nr * (klen - 0.5 * nr);
-        tile_steps += (klen + 63) / 64;
-        most_steps = std::max<int64_t>(most_steps, (std::min(klen, part) + 63) / 64);
         if (parts > 1) { in.partial_slots += parts * nr; in.merge_rows += nr; }
       }
     }
@@ -485,22 +584,9 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, bool
   // 0.9 PFLOP/s at 4 D flop per pair and head, row kernels 5.5 TB/s at 4 D bytes per key and K/V head): that one
   // goes on the caller's stream, the other through the fork and join of the second stream.  (head_dim 256: 0.5 PFLOP/s.)
   ps.tile_leads = tile_pairs * H * (4.0 * D / (D > 128 ? 0.5e15 : 0.9e15)) > row_keys * pool->cfg.num_kv_heads * (4.0 * D / 5.5e12);
-  const int n_vec = ps.vec_items - ps.few_rows, n_group = in.row_items - ps.vec_items;
+  const int n_vec = ps.vec_items - ps.few_rows;
   const bool short_rows = n_vec > 0 && vec_keys * (4.0 * D) < n_vec * kShortItemBytes;
   ps.row_per_item = short_rows || (t.decode_part_tokens == 0 && ps.row_part < kDefaultRowPart);
-  // Side by side: tile items or few-key units beside rows of a kernel that has a slim build, unless one after the other is
-  // expected to take 4 % less, or because the caller asks for persistent row workgroups.
-  ps.slim_group = D == 128 && G <= 16;
-  ps.side_by_side = (in.tile_items > 0 || ps.few_runs > 0) && !t.serial_spans && (ps.decode_as_group ? n_group > 0 && ps.slim_group : n_vec > 0);
-  if (ps.side_by_side && t.row_launch < 2 && t.row_slots == 0) {
-    const int64_t n_th = H >> ps.tile_g_shift;
-    const double tiles_time = tiles_us(D, in.tile_items * n_th, tile_steps * n_th, most_steps);
-    RowLoad rows;
-    rows.group = n_group > 0;
-    rows.add(n_vec, (int64_t)vec_keys, most_vec, H, D);
-    rows.add(n_group, (int64_t)(row_keys - vec_keys), most_group, pool->cfg.num_kv_heads, D);
-    ps.side_by_side = side_by_side_us(D, tiles_time, rows) < 1.04 * serial_us(D, tiles_time, rows);
-  }
   size_t o = 0;
   ps.off_ctr = o;     o = align_up(o + sizeof(int32_t) * 16, 256);
   ps.off_bt_off = o;  o = align_up(o + sizeof(int32_t) * (size_t)d->num_seqs, 256);

@@ -89,6 +89,22 @@ def test_batches_run_side_by_side_where_that_is_faster(H, Hkv, D, n, keys, n_spa
     assert bool(_plan(H, Hkv, D, [40] + ctx, [1] + q_len)["side_by_side"]) == pair
 
 
+@pytest.mark.parametrize("H,Hkv,D,n,keys,n_span,prefix,split", [
+    # measured side by side with whole rows / in items of 1024 keys, us
+    (40, 40, 128, 4, 4000, 4, 2500, False),      # the tiles lead
+    (40, 40, 128, 5, 4000, 4, 2500, False),      # 200 / 204
+    (40, 40, 128, 8, 4000, 4, 2500, False),
+    (64, 8, 128, 63, 1500, 4, 1500, False),      # 157 / 164 (768 keys)
+    (40, 40, 128, 3, 4000, 2, 2000, True),       # 116 / 94: 120 long items beside 160 tiles on 256 CUs
+    (40, 40, 128, 7, 4000, 3, 1500, True),       # 159 / 132: the second round of long items has 24
+    (16, 16, 256, 6, 4000, 2, 1500, True),       # 161 / 113
+])
+def test_rows_beside_tiles_are_split_where_that_ends_sooner(H, Hkv, D, n, keys, n_span, prefix, split):
+    plan = _plan(H, Hkv, D, [keys] * n + [prefix + 512] * n_span, [1] * n + [512] * n_span)
+    assert plan["side_by_side"] and (plan["row_part_tokens"] < 4096) == split
+    assert (plan["row_items"][:, 4] >= 0).any() == split
+
+
 @pytest.mark.parametrize("n_span", [1, 2, 3])
 def test_one_short_decode_row_leaves_a_grouped_batch_side_by_side(n_span):
     ctx = [2000] * 64 + [2500] * n_span
