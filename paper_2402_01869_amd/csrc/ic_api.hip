@@ -306,6 +306,9 @@ int choose_row_part(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes
   const int64_t units = group ? pool->cfg.num_kv_heads : pool->cfg.num_heads;
   bool spans = false;
   for (int s = 0; s < d->num_seqs && !spans; ++s) spans = d->q_len[s] > 1;
+  // Decode rows as one-row tiles are not what this model is about; and where spans run row by row, their rows take the
+  // partition too, in numbers that fill the chip whole.
+  if (ps.decode_as_tiles || (spans && ps.spans_as_rows)) return kDefaultRowPart;
   const int64_t slots = group && !spans ? 2 * kExpectedCus : kExpectedCus;  // two group workgroups per CU; beside a tile workgroup one
   const int64_t enough = 2 * slots;
   int64_t items = 0, keys = 0;

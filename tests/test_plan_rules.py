@@ -105,6 +105,17 @@ def test_rows_beside_tiles_are_split_where_that_ends_sooner(H, Hkv, D, n, keys, 
     assert (plan["row_items"][:, 4] >= 0).any() == split
 
 
+@pytest.mark.parametrize("H,Hkv,ctx,q_len,kernel", [
+    (40, 40, [3000, 16384], [1, 2048], 1),     # 2048 span rows row by row
+    (64, 8, [3000, 700], [1, 100], 1),
+    (64, 8, [3000, 6000], [1, 1], 2),          # decode rows as one-row tiles
+    (64, 8, [3000, 16384], [1, 512], 2),
+])
+def test_the_partition_of_a_few_decode_rows_is_not_put_on_other_rows(H, Hkv, ctx, q_len, kernel):
+    plan, whole = (_plan(H, Hkv, 128, ctx, q_len, span_kernel=kernel, **t) for t in (dict(), dict(decode_part_tokens=4096)))
+    assert plan["row_part_tokens"] == 4096 and plan["workspace"] == whole["workspace"]
+
+
 @pytest.mark.parametrize("n_span", [1, 2, 3])
 def test_one_short_decode_row_leaves_a_grouped_batch_side_by_side(n_span):
     ctx = [2000] * 64 + [2500] * n_span
