@@ -348,12 +348,16 @@ RowLoad row_load(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& p
   const double key_bytes = 4.0 * pool->cfg.head_dim;
   RowLoad load;
   int longest = 0;
+  const auto is_row = [&](int s) {  // decode rows that are row items (span_kernel = 2: only those of few keys)
+    const SeqRoute rt = route(ps, d->ctx_len[s], d->q_len[s]);
+    return d->q_len[s] == 1 && (rt.rest_rows || rt.n_few > 0);
+  };
   for (int s = 0; s < d->num_seqs; ++s)
-    if (d->q_len[s] == 1) longest = std::max(longest, std::min(d->ctx_len[s], part));
+    if (is_row(s)) longest = std::max(longest, std::min(d->ctx_len[s], part));
   for (int s = 0; s < d->num_seqs; ++s) {
     const int c = d->ctx_len[s], n = d->q_len[s];
     const SeqRoute rt = route(ps, c, n);
-    if (n == 1 && (rt.rest_rows || rt.n_few > 0)) {
+    if (is_row(s)) {
       const bool group = rt.rest_group && rt.n_few == 0;
       const int64_t units = group ? pool->cfg.num_kv_heads : pool->cfg.num_heads;
       load.group = load.group || group;
@@ -412,7 +416,7 @@ int choose_row_part_beside(const ic_pool* pool, const ic_batch_desc* d, const Pl
       *us = t;
       least = least == 0.0 ? t : std::min(least, t);
     }
-    if (rows.items >= 4 * kExpectedCus) break;  // rounds enough: a finer partition only adds items
+    if (ps.decode_as_tiles || rows.items >= 4 * kExpectedCus) break;  // rounds enough: a finer partition only adds items
   }
   return best;
 }

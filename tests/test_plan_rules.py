@@ -110,6 +110,7 @@ def test_rows_beside_tiles_are_split_where_that_ends_sooner(H, Hkv, D, n, keys, 
     (64, 8, [3000, 700], [1, 100], 1),
     (64, 8, [3000, 6000], [1, 1], 2),          # decode rows as one-row tiles
     (64, 8, [3000, 16384], [1, 512], 2),
+    (64, 8, [3000, 40, 6000, 2000, 2000], [1, 1, 1, 512, 512], 2),   # ... beside one that is a row item
 ])
 def test_the_partition_of_a_few_decode_rows_is_not_put_on_other_rows(H, Hkv, ctx, q_len, kernel):
     plan, whole = (_plan(H, Hkv, 128, ctx, q_len, span_kernel=kernel, **t) for t in (dict(), dict(decode_part_tokens=4096)))
