@@ -200,7 +200,9 @@ __device__ __forceinline__ void wave_step(const uint16_t* ks, const uint16_t* vs
   // Weights: rounded to bf16 in pairs (one v_cvt_pk_bf16_f32), and summed AS ROUNDED by a bf16 dot
   // product with (1, 1): the normaliser then counts exactly what the matrix core will multiply, so
   // the output stays an exact convex combination of the values and a row dominated by one key
-  // (short contexts) does not inherit the 2^-9 relative rounding error of its weight.
+  // (short contexts) does not inherit the 2^-9 relative rounding error of its weight.  A step's weights are summed by
+  // themselves first: the running total is rounded once a step, not once a pair.
+  float psum = 0.f;
   bf16x8 pb[4];
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
@@ -210,10 +212,11 @@ __device__ __forceinline__ void wave_step(const uint16_t* ks, const uint16_t* vs
       const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_acc[tt][i], sc, -m));
       const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_acc[tt][i + 1], sc, -m));
       const bf16x2 pr = {(__bf16)p0, (__bf16)p1};
-      l = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, l, false);
+      psum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, psum, false);
       pb[2 * tt + i / 8][i % 8] = pr[0];
       pb[2 * tt + i / 8][i % 8 + 1] = pr[1];
     }
+  l += psum;
   // O^T += V^T P^T, k-step outer so that the kDTiles independent accumulators alternate
   {
     const int lane = col + 32 * hl;

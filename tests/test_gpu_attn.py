@@ -292,6 +292,40 @@ def test_queues_beyond_the_first_round_start_again_from_zero(H, Hkv, D):
     pool.close()
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_normaliser_of_a_long_row_is_rounded_once_a_step(D):
+    """8192 keys of weight 1, then 8192 of weight 2^-12 x 1.42 (exact in bf16), in one partition of a chunk: the small ones
+    are a third of the running total's spacing above it, pair by pair, and would be lost there one at a time.  The normaliser
+    the tile kernel leaves in the partial results is off by at most half a spacing a step (256 steps x 2^-24), and the
+    rounding of a step's own sum."""
+    H, part, ctx = 1, 16384, 16384 + 64
+    small = 91.0 / 64 * 2.0 ** -12
+    batch = W.assemble_batch(H, D, 16, ctx // 16 + 1, [ctx], [2], np.random.default_rng(D))
+    keys = np.zeros((ctx, D), dtype=np.float32)
+    keys[8192:part, 0] = -1.0                       # score 0 or -scale
+    pool_bits = np.zeros(W.pool_shape(ctx // 16 + 1, H, 16, D), dtype=np.uint16)
+    bits = W.f32_to_bf16_bits(keys).reshape(-1, 16, D)
+    for j, blk in enumerate(batch.block_tables[0, :ctx // 16]):
+        pool_bits[blk, 0, 0] = bits[j]
+    q = np.zeros((2, H, D), dtype=np.float32)
+    q[..., 0] = 1.0
+    pool, keep = make_pool(pool_bits, H)
+    pool.set_tuning(span_part_tokens=part, mfma_min_keys=1)
+    desc = B.HostDesc(batch.ctx_len, batch.q_len, batch.q_start, batch.block_tables, -math.log(small), 2)
+    plan = pool.plan_image(desc)
+    slot0, nparts = plan["tile_items"][0][6:8].tolist()
+    assert nparts == 2 and plan["tile_items"][0][4] == 0 and plan["partial_slots"] == 4
+    q_t, out = to_dev_bits(W.f32_to_bf16_bits(q)), torch.zeros((2, H, D), dtype=torch.int16, device=DEV)
+    ws = torch.zeros(pool.workspace_bytes(desc), dtype=torch.uint8, device=DEV)
+    pool.paged_attn_mixed(desc, q_t.data_ptr(), out.data_ptr(), ws.data_ptr(), ws.numel())
+    torch.cuda.synchronize()
+    at = (plan["image_bytes"] + 4 * plan["partial_slots"] * H * D + 255) // 256 * 256      # behind the partial outputs
+    m, l = ws.cpu().numpy()[at:].view(np.float32)[2 * slot0: 2 * slot0 + 2].tolist()
+    want = 8192 + 8192 * small
+    assert m == 0.0 and abs(l - want) <= want * (256 + 8) * 2.0 ** -24, (l, want)
+    pool.close()
+
+
 @pytest.mark.parametrize("H,Hkv", [(2, 2), (8, 2)])
 def test_very_long_contexts_and_gaps_in_the_row_space(H, Hkv):
     """A 40000-token decode sequence (20 key partitions), a chunk on a 20000-token prefix, and query rows laid
