@@ -197,7 +197,7 @@ typedef struct {
   int32_t mfma_min_keys;      /* the softmax weights of query rows that see fewer keys than this are not rounded to
                                  bf16 as the matrix-core kernels do (with a handful of keys one weight's rounding
                                  shows in the output): such rows run on the vector kernel, which keeps them in
-                                 fp32, or as units that split them into two bf16 parts; 0 = built-in 64,
+                                 fp32, or as units that split them into three bf16 parts (24 bits); 0 = built-in 64,
                                  1 = no such routing, at most 64                              */
   int32_t reserved[1];        /* must be 0                                                   */
 } ic_tuning;

@@ -3,10 +3,11 @@
 // of a workgroup.  As row items these rows cost a workgroup per (row, head), each a chain of dependent loads (item,
 // block table, keys) around a few hundred multiply-adds: 4 fresh chunks of a 40-head pool are 10080 of them, 240 us.
 // Here a (sequence, head) is ONE unit: its keys are staged in LDS once, 16 rows per wave on the matrix cores.
-//   - The weights keep 16 bits of significand on the way into the PV product: p = hi + lo, both bf16, one MFMA each
-//     (2^-17 relative error, against 2^-9 of the one rounding the tile bodies make; with a handful of keys a single
-//     weight's rounding shows in the result).  The normaliser is the fp32 sum of the unrounded weights, the maximum
-//     the row's own.
+//   - The weights keep their 24 bits of significand on the way into the PV product: p = hi + mid + lo, all bf16, one MFMA
+//     each (against the one rounding, 2^-9, that the tile bodies make; with a handful of keys a single weight's
+//     rounding shows in the result).  With two parts (16 bits) 0.17 % of the results were not the bf16 value nearest to the
+//     exact one, with three 0.01 %, as on the vector kernel.  The normaliser is the fp32 sum of the weights, the
+//     maximum the row's own.
 //   - A product of a zero weight and an infinite value is NaN on the matrix core, also for keys the row does not
 //     see.  If a wave's result is not finite it is computed again key by key on the vector ALU, over the row's own
 //     keys only.
@@ -111,7 +112,7 @@ __device__ __forceinline__ void few_body(const AttnParams& p, const FewItem& f, 
   m = __builtin_fmaxf(m, __shfl_xor(m, 16));
   m = __builtin_fmaxf(m, __shfl_xor(m, 32));
   float l = 0.f;
-  bf16x8 hi[2], lo[2];
+  bf16x8 hi[2], mid[2], lo[2];
 #pragma unroll
   for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -119,8 +120,11 @@ __device__ __forceinline__ void few_body(const AttnParams& p, const FewItem& f, 
       s[u][i] = __builtin_amdgcn_exp2f(s[u][i] - m);
       l += s[u][i];
       const __bf16 h = (__bf16)s[u][i];
+      const float r1 = s[u][i] - (float)h;  // exact, and so is what is left after mid
+      const __bf16 d = (__bf16)r1;
       hi[u >> 1][4 * (u & 1) + i] = h;
-      lo[u >> 1][4 * (u & 1) + i] = (__bf16)(s[u][i] - (float)h);
+      mid[u >> 1][4 * (u & 1) + i] = d;
+      lo[u >> 1][4 * (u & 1) + i] = (__bf16)(r1 - (float)d);
     }
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
@@ -135,6 +139,7 @@ __device__ __forceinline__ void few_body(const AttnParams& p, const FewItem& f, 
     for (int h = 0; h < 2; ++h) {
       const bf16x8 a = tile16::read_vt16<D>(vs, 16 * dt, h, lane);
       acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, hi[h], acc[dt], 0, 0, 0);
+      acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, mid[h], acc[dt], 0, 0, 0);
       acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, lo[h], acc[dt], 0, 0, 0);
     }
 #pragma unroll

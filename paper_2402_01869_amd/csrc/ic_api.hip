@@ -24,7 +24,7 @@ constexpr int kUnsplitWorkgroups = 1024;  // tile workgroups (4 per CU) from whi
 // The weights of rows that see fewer keys than this are not rounded to bf16.  The matrix-core kernels round them
 // before the PV product; with a handful of keys a single weight's rounding (2^-9 relative) shows in the
 // output, with dozens the roundings average out.  The vector path keeps the weights in fp32, the
-// few-key units split them into two bf16 parts.
+// few-key units split them into three bf16 parts.
 constexpr int kShareKeys = 8192;  // sequences at least this long keep their tile items side by side
 constexpr int kMfmaMinKeys = 64;
 constexpr int kExpectedCus = 256;        // the planner runs without a device; the launches use the device's own count
