@@ -316,8 +316,10 @@ int ic_check_ids(const ic_pool_cfg* cfg, const int32_t* host_ids, int32_t n, int
  *
  * A swapper serves L pools of ONE shape (the L layers of a model; a multi-layer cache is L pools).
  * Swaps run on two streams of default priority, one per direction (swap-out and swap-in run beside each
- * other), which all swappers of a process share per device; each direction of a swapper has a staging
- * buffer of max_blocks * kv_block_bytes() bytes, carved from the caller's dev_staging.
+ * other), which all swappers of a process share per device (a process gets few hardware queues, on which streams
+ * of their own would meet all the same): a swap also follows the swaps that other swappers queued in its
+ * direction before, and so what those wait for.  Each direction of a swapper has a staging buffer of
+ * max_blocks * kv_block_bytes() bytes, carved from the caller's dev_staging.
  * Per layer l and list position i, with blk = kv_block_bytes():
  *   kv_swap_out_layers:  host[l * layer_stride + i * blk ..+blk) <- pool_l[host_ids[i]]
  *   kv_swap_in_layers:   pool_l[host_ids[i]] <- host[l * layer_stride + i * blk ..+blk)   (ids distinct)
@@ -328,7 +330,7 @@ int ic_check_ids(const ic_pool_cfg* cfg, const int32_t* host_ids, int32_t n, int
  * pass the stream that wrote (swap-out) or last read (swap-in) the listed blocks.
  * Order later work with ic_swapper_wait_layer (a stream waits until layer l of the latest call in
  * that direction is through: for swap-in the layer's blocks are then readable, for swap-out they
- * may be reused), ic_swapper_sync_layer or ic_swapper_sync (the host waits).
+ * may be reused), ic_swapper_sync_layer or ic_swapper_sync (the host waits for this swapper's swaps).
  * One host thread drives a swapper.  Byte-exact.  n = 0 succeeds and does nothing.
  * ------------------------------------------------------------------------------------------ */
 typedef struct ic_swapper ic_swapper;
@@ -336,7 +338,7 @@ typedef struct ic_swapper ic_swapper;
 typedef struct {
   int32_t num_layers; /* L >= 1                                                        */
   int32_t max_blocks; /* most blocks one call may move per layer, >= 1                 */
-  int32_t num_stages; /* staging buffers, 2..8 (one per direction is in use)           */
+  int32_t num_stages; /* staging buffers of dev_staging, 2..8; more than 2, one per direction, are not used */
   int32_t reserved;   /* must be 0                                                     */
 } ic_swapper_cfg;
 

@@ -83,6 +83,7 @@ struct ic_swapper {
   int next_ids = 0;
   std::vector<hipEvent_t> done[2];
   std::vector<uint8_t> done_set[2];
+  bool open[2] = {false, false};  // a call that failed half-way left work without its last done event
 };
 
 namespace {
@@ -221,8 +222,14 @@ int ic_swapper_create(const ic_swapper_cfg* cfg, ic_pool* const* layer_pools, vo
 int ic_swapper_sync(ic_swapper* sw) {
   if (!sw) return IC_ENULL;
   if (!sw->live) return IC_OK;
-  if (hipStreamSynchronize(sw->s_out) != hipSuccess) return IC_EHIP;
-  if (hipStreamSynchronize(sw->s_in) != hipSuccess) return IC_EHIP;
+  // This swapper's own work ends with the last layer of its latest call in each direction; the streams may hold others'.
+  for (int d = 0; d < 2; ++d) {
+    if (sw->open[d]) {
+      if (hipStreamSynchronize(d == IC_SWAP_OUT ? sw->s_out : sw->s_in) != hipSuccess) return IC_EHIP;
+    } else if (sw->done_set[d].back()) {
+      if (hipEventSynchronize(sw->done[d].back()) != hipSuccess) return IC_EHIP;
+    }
+  }
   return IC_OK;
 }
 
@@ -256,6 +263,7 @@ int kv_swap_out_layers(ic_swapper* sw, const int32_t* host_ids, int32_t n, void*
   IdSlot* slot = nullptr;
   if ((rc = upload_ids(sw, st, host_ids, n, &dev_ids, &slot)) != IC_OK) return rc;
   char* const buf = sw->staging + (size_t)IC_SWAP_OUT * sw->stage_bytes;
+  sw->open[IC_SWAP_OUT] = true;
   for (int l = 0; l < sw->cfg.num_layers; ++l) {
     if (launch_pack(sw->views[l].base, buf, dev_ids, n, sw->block_bytes, st) != hipSuccess) return IC_EHIP;
     if (link_copy((char*)pinned_host_dst + (size_t)l * layer_stride_bytes, buf, sw->block_bytes, n,
@@ -264,6 +272,7 @@ int kv_swap_out_layers(ic_swapper* sw, const int32_t* host_ids, int32_t n, void*
     if (hipEventRecord(sw->done[IC_SWAP_OUT][l], st) != hipSuccess) return IC_EHIP;
     sw->done_set[IC_SWAP_OUT][l] = 1;
   }
+  sw->open[IC_SWAP_OUT] = false;
   if (hipEventRecord(slot->ev, st) != hipSuccess) return IC_EHIP;
   slot->pending = true;
   return IC_OK;
@@ -283,6 +292,7 @@ int kv_swap_in_layers(ic_swapper* sw, const int32_t* host_ids, int32_t n, const 
   IdSlot* slot = nullptr;
   if ((rc = upload_ids(sw, st, host_ids, n, &dev_ids, &slot)) != IC_OK) return rc;
   char* const buf = sw->staging + (size_t)IC_SWAP_IN * sw->stage_bytes;
+  sw->open[IC_SWAP_IN] = true;
   for (int l = 0; l < sw->cfg.num_layers; ++l) {
     if (link_copy(buf, (const char*)pinned_host_src + (size_t)l * layer_stride_bytes, sw->block_bytes, n,
                   hipMemcpyHostToDevice, st) != hipSuccess)
@@ -291,6 +301,7 @@ int kv_swap_in_layers(ic_swapper* sw, const int32_t* host_ids, int32_t n, const 
     if (hipEventRecord(sw->done[IC_SWAP_IN][l], st) != hipSuccess) return IC_EHIP;
     sw->done_set[IC_SWAP_IN][l] = 1;
   }
+  sw->open[IC_SWAP_IN] = false;
   if (hipEventRecord(slot->ev, st) != hipSuccess) return IC_EHIP;
   slot->pending = true;
   return IC_OK;

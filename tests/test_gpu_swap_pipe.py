@@ -281,3 +281,33 @@ def test_two_swappers_share_the_streams_and_keep_apart():
     for _, out, back in bufs:
         out.close()
         back.close()
+
+
+def test_sync_waits_for_the_swapper_s_own_swaps_only():
+    """One swapper's swap stands behind a stream that is busy for some 50 ms; another swapper, idle or through with its own
+    swaps, is in sync at once."""
+    a, b = (Layers(2, 64, 4, 64, 8, 2, seed=s) for s in (1, 2))
+    ids = np.arange(6, dtype=np.int32)
+    pins = [B.PinnedBuffer(2 * 6 * ly.bb) for ly in (a, b)]
+    b.sw.sync()                                       # never used
+    a.sw.swap_out(ids, pins[0].ptr, 6 * a.bb)
+    a.sw.sync()                                       # everything is created before the clock counts
+    busy, through = torch.cuda.Stream(), torch.cuda.Event()
+    for used in (False, True):
+        if used:
+            b.sw.swap_out(ids, pins[1].ptr, 6 * b.bb)
+            b.sw.swap_in(ids + 8, pins[1].ptr, 6 * b.bb)
+            torch.cuda.synchronize()
+        with torch.cuda.stream(busy):
+            torch.cuda._sleep(120_000_000)
+        through.record(busy)
+        a.sw.swap_out(ids, pins[0].ptr, 6 * a.bb, busy.cuda_stream)
+        a.sw.swap_in(ids + 8, pins[0].ptr, 6 * a.bb, busy.cuda_stream)
+        b.sw.sync()
+        assert not through.query(), "waited for the other swapper"
+        a.sw.sync()
+        assert through.query()
+    assert np.array_equal(pins[0].array.reshape(2, -1), oracle.swap_out_layers(a.host, ids))
+    for ly, pin in zip((a, b), pins):
+        ly.close()
+        pin.close()
