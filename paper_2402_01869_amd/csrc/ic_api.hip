@@ -489,9 +489,12 @@ int split_units(const ic_pool* pool, const PlanSizes& ps) {
   return ps.decode_as_group ? pool->cfg.num_kv_heads : pool->cfg.num_heads;
 }
 
-// compact: no split that only buys time and no few-key units, for a caller whose workspace is too small for the plan that
-// paged_attn_mixed_workspace_bytes sizes (one allocated for another batch, say): the least this batch can run in.
-void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, bool compact = false) {
+// How much workspace a plan may take.  kFull is what paged_attn_mixed_workspace_bytes sizes; the others are for a caller whose
+// workspace is smaller (one allocated for another batch, say): no split that only buys time, and, the least a batch
+// can run in, no few-key units either.
+enum Room { kFull = 0, kUnsplit = 1, kLeast = 2 };
+
+void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, Room room = kFull) {
   std::memset(&ps, 0, sizeof ps);
   // Grouped-query attention: the G = H / Hkv query heads of a group read the same keys.  When G is a
   // power of two up to 32, a tile workgroup takes all of them (G rows per query row), so keys are
@@ -520,13 +523,13 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, bool
   // Without tile items the few-key units would be a launch of their own (4-5 us); up to two rounds of one-row items on
   // the vector kernel take no longer.  Measured: 4 chunks of 2 rows from position 0 + 1 decode row, 16 heads, two
   // layers: 30 us as row items, 36 as units.
-  ps.few_as_units = !compact && !ps.spans_as_rows && (tiles > 0 || few * pool->cfg.num_heads > 2 * kExpectedCus);
+  ps.few_as_units = room != kLeast && !ps.spans_as_rows && (tiles > 0 || few * pool->cfg.num_heads > 2 * kExpectedCus);
   if (t.span_part_tokens == 0) {
     const int64_t head_groups = pool->cfg.num_heads >> ps.tile_g_shift;
     double row_us = 0.0;
     for (int s = 0; s < d->num_seqs; ++s)
       if (d->q_len[s] == 1) row_us += d->ctx_len[s] * (4.0 * pool->cfg.head_dim * pool->cfg.num_kv_heads / 5.5e6);
-    ps.span_part = compact || ps.spans_as_rows || tiles * head_groups >= kUnsplitWorkgroups ? kWholeSpan : choose_span_part(pool, d, ps, row_us);
+    ps.span_part = room != kFull || ps.spans_as_rows || tiles * head_groups >= kUnsplitWorkgroups ? kWholeSpan : choose_span_part(pool, d, ps, row_us);
   }
   // Side by side: tile items or few-key units beside rows of a kernel that has a slim build, unless one after the other is
   // expected to take 4 % less, or not 2 % more where the rows are split (their last partitions merge them there), or because
@@ -535,7 +538,7 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, bool
   {
     const double tiles_time = tile_load_us(pool, d, ps);
     const RowLoad whole = row_load(pool, d, ps, ps.row_part);
-    const bool choose = t.decode_part_tokens == 0 && !compact;
+    const bool choose = t.decode_part_tokens == 0 && room == kFull;
     const int part_alone = choose ? choose_row_part(pool, d, ps) : ps.row_part;
     ps.side_by_side = (tiles_time > 0.0 || (ps.few_as_units && few > 0)) && !t.serial_spans && whole.items > 0 &&
                       (ps.decode_as_group ? whole.group && ps.slim_group : true);
@@ -610,6 +613,15 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, bool
   ps.off_part_o = o;  o = align_up(o + sizeof(float) * (size_t)in.partial_slots * H * D, 256);
   ps.off_part_ml = o; o = align_up(o + sizeof(float) * (size_t)in.partial_slots * H * 2, 256);
   ps.total_bytes = o;
+}
+
+// The plan for a workspace of so many bytes.
+int plan_within(const ic_pool* pool, const ic_batch_desc* d, size_t bytes, PlanSizes& ps) {
+  for (const Room room : {kFull, kUnsplit, kLeast}) {
+    plan_sizes(pool, d, ps, room);
+    if (bytes >= ps.total_bytes) return IC_OK;
+  }
+  return IC_ESIZE;
 }
 
 // The kernels that run a plan, and how.
@@ -1167,9 +1179,7 @@ int paged_attn_mixed(ic_pool* pool, const ic_batch_desc* desc, const void* dev_q
     if (rc != IC_OK) return rc;
     if (misaligned(dev_q) || misaligned(dev_out) || ((uintptr_t)dev_workspace & 255u)) return IC_EALIGN;
     PlanSizes ps;
-    plan_sizes(pool, desc, ps);
-    if (workspace_bytes < ps.total_bytes) plan_sizes(pool, desc, ps, true);
-    if (workspace_bytes < ps.total_bytes) return IC_ESIZE;
+    if ((rc = plan_within(pool, desc, workspace_bytes, ps)) != IC_OK) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
     char* ws = (char*)dev_workspace;
     if ((rc = upload_plan(pool, desc, ps, ws, st)) != IC_OK) return rc;
@@ -1185,9 +1195,7 @@ int paged_attn_plan_create(ic_pool* pool, const ic_batch_desc* desc, void* dev_w
   if (rc != IC_OK) return rc;
   if ((uintptr_t)dev_workspace & 255u) return IC_EALIGN;
   std::unique_ptr<ic_plan> pl(new ic_plan());
-  plan_sizes(pool, desc, pl->ps);
-  if (workspace_bytes < pl->ps.total_bytes) plan_sizes(pool, desc, pl->ps, true);
-  if (workspace_bytes < pl->ps.total_bytes) return IC_ESIZE;
+  if ((rc = plan_within(pool, desc, workspace_bytes, pl->ps)) != IC_OK) return rc;
   pl->cfg = pool->cfg;
   pl->tune = pool->tune;
   pl->scale = desc->scale;

@@ -233,7 +233,8 @@ def test_rows_merged_by_their_last_partition(H, Hkv, D, ctx):
                                                (4, 4, 64, [2600, 300], [40, 300])])
 @pytest.mark.gpu
 def test_a_workspace_without_room_for_the_split_runs_whole_rows(H, Hkv, D, ctx, q_len):
-    """A workspace large enough for whole rows and tiles (allocated for another batch, say) is accepted."""
+    """A workspace large enough for whole rows and tiles (allocated for another batch, say) is accepted, and few-key rows stay
+    units of the tile kernel as long as their few bytes fit too."""
     import torch
     import oracle
     from gpu_common import from_dev_bits, make_pool, max_abs_err, to_dev_bits
@@ -247,18 +248,22 @@ def test_a_workspace_without_room_for_the_split_runs_whole_rows(H, Hkv, D, ctx, 
     whole = pool.workspace_bytes(desc)
     if max(ctx) <= 4096:
         assert pool.plan_query(desc)["partial_slots"] == 0
+    few = pool.plan_launches(desc)["n_few_items"]
     pool.set_tuning()
-    assert whole < full
+    assert whole < full and few == (1 if q_len == [40, 300] else 0)
     q, ws = to_dev_bits(q_bits), torch.empty(full, dtype=torch.uint8, device="cuda:0")
-    for planned in (False, True):
+    for planned, room in ((False, whole), (True, whole), (False, whole - 256 * few), (True, whole - 256 * few)):
+        pool.prof_begin(16)
         out = torch.full(tuple(q_bits.shape), 0x7FFF, dtype=torch.int16, device="cuda:0")
         if planned:
-            plan = pool.plan_create(desc, ws.data_ptr(), whole)
+            plan = pool.plan_create(desc, ws.data_ptr(), room)
             pool.paged_attn_planned(plan, q.data_ptr(), out.data_ptr())
         else:
-            pool.paged_attn_mixed(desc, q.data_ptr(), out.data_ptr(), ws.data_ptr(), whole)
+            pool.paged_attn_mixed(desc, q.data_ptr(), out.data_ptr(), ws.data_ptr(), room)
         torch.cuda.synchronize()
         assert max_abs_err(from_dev_bits(out), want) <= 1e-2
+        if few:      # no decode rows here: the row kernel runs for few-key rows that are not units
+            assert pool.prof_end()["row"]["launches"] == (0 if room == whole else 1)
     plan.close()
     assert pool.paged_attn_mixed(desc, q.data_ptr(), out.data_ptr(), ws.data_ptr(), 1024, check=False) == B.IC_ESIZE
     pool.close()
