@@ -487,7 +487,7 @@ def attention_kernel_names(pool, desc, acfg):
     beside = bool(how["side_by_side"])
     row = {B.IC_LAUNCH_SLIM: "row_persist_slim_kernel", B.IC_LAUNCH_PER_ITEM: "row_attn_kernel"}.get(how["row_launch"], "row_persist_kernel")
     tile = f"tile_attn_kernel<{D}>" if how["tile_launch"] == B.IC_LAUNCH_PER_ITEM else f"tile_persist_kernel<{D}, {'true' if beside else 'false'}>"
-    group = "group_slim_kernel" if how["group_launch"] == B.IC_LAUNCH_SLIM else f"group_attn_kernel<{D}>"
+    group = "group_slim_kernel" if how["group_launch"] == B.IC_LAUNCH_SLIM else f"group_attn_kernel<{D}, {'true' if how['n_split_units'] else 'false'}>"
     return {"row": f"{row}<{D}>", "group": group, "tile": tile, "merge": f"merge_kernel<{D}>",
             "side_by_side": beside, "beside_tile": group if how["group_launch"] else f"{row}<{D}>"}
 

@@ -147,7 +147,8 @@ __device__ __forceinline__ void group_step(const uint16_t* ks, const uint16_t* v
   }
 }
 
-template <int D>
+// kMerge: split rows are merged by their last partition (s_last: an int of LDS), else by the merge kernel.
+template <int D, bool kMerge>
 __device__ __forceinline__ void group_body(const AttnParams& p, const RowItem& it, int kvh, uint16_t* lds, int* s_last) {
   using G = TG<D>;
   const int H = p.num_heads, Hk = p.num_kv_heads, Gq = p.group;  // Gq <= 32 query heads per K/V head
@@ -235,17 +236,21 @@ __device__ __forceinline__ void group_body(const AttnParams& p, const RowItem& i
       p.out[((int64_t)it.qrow * H + hq) * D + d] = __builtin_bit_cast(uint16_t, o);
     } else {
       const int64_t ps = (int64_t)it.slot * H + hq;
-      mergep::store_shared(&p.part_o[ps * D + d], O);
+      mergep::store_partial<kMerge>(&p.part_o[ps * D + d], O);
       if (d == 0) {
-        mergep::store_shared(&p.part_ml[ps * 2], M);
-        mergep::store_shared(&p.part_ml[ps * 2 + 1], L);
+        mergep::store_partial<kMerge>(&p.part_ml[ps * 2], M);
+        mergep::store_partial<kMerge>(&p.part_ml[ps * 2 + 1], L);
       }
     }
   }
-  if (it.slot >= 0 && p.split_units > 0) mergep::finish_split<D, 4>(p, it.slot, kvh, kvh * Gq, Gq, s_last);
+  if constexpr (kMerge) {
+    if (it.slot >= 0) mergep::finish_split<D, 4>(p, it.slot, kvh, kvh * Gq, Gq, s_last);
+  }
 }
 
-template <int D>
+// Two builds, because the end that merges takes registers: at head_dim 256, where the kernel spills some as it is, rows
+// that are not split took 2 % longer in a kernel that had it (256 rows of 2000 keys, 4 heads over 2: 222.9 -> 218.6 us a call).
+template <int D, bool kMerge>
 __global__ __launch_bounds__(64 * kGroupWaves, (D <= 128 ? 2 : 1)) void group_attn_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[group_lds_bytes<D>() / 2];
   __shared__ int s_last;
@@ -254,7 +259,7 @@ __global__ __launch_bounds__(64 * kGroupWaves, (D <= 128 ? 2 : 1)) void group_at
   const int item_idx = wg / Hk;
   const int kvh = wg - item_idx * Hk;
   const RowItem it = p.row_items[p.group_first + item_idx];
-  group_body<D>(p, it, kvh, lds, &s_last);
+  group_body<D, kMerge>(p, it, kvh, lds, &s_last);
 }
 
 }  // namespace
@@ -266,12 +271,18 @@ hipError_t launch_group_kernel(const AttnParams& p, int head_dim, hipStream_t st
   const uint64_t grid = (uint64_t)n_items * (uint64_t)p.num_kv_heads;
   if (grid > 0x7fffffffull) return hipErrorInvalidValue;
   const dim3 g((uint32_t)grid), b(64 * kGroupWaves);
+#define IC_GROUP_CASE(DD)                                                                                  \
+  case DD:                                                                                                 \
+    if (p.split_units > 0) hipLaunchKernelGGL((group_attn_kernel<DD, true>), g, b, 0, st, p);                \
+    else hipLaunchKernelGGL((group_attn_kernel<DD, false>), g, b, 0, st, p);                                 \
+    break;
   switch (head_dim) {
-    case 64: hipLaunchKernelGGL(group_attn_kernel<64>, g, b, 0, st, p); break;
-    case 128: hipLaunchKernelGGL(group_attn_kernel<128>, g, b, 0, st, p); break;
-    case 256: hipLaunchKernelGGL(group_attn_kernel<256>, g, b, 0, st, p); break;
+    IC_GROUP_CASE(64)
+    IC_GROUP_CASE(128)
+    IC_GROUP_CASE(256)
     default: return hipErrorInvalidValue;
   }
+#undef IC_GROUP_CASE
   return hipGetLastError();
 }
 

@@ -78,7 +78,8 @@ __global__ __launch_bounds__(Impl<D>::kThreads, 2) void tile_attn_kernel(AttnPar
 // kBeside only names the build (side by side with a row or group kernel, or on its own), so that a kernel trace
 // tells the two uses apart; the code is the same.
 // amdgpu_num_vgpr: on this target vector and accumulation registers share one file and the compiler doubles the
-// figure it is given, so 104 caps the kernel at 208 registers (launch bounds alone would allow 256).
+// figure it is given, so 104 caps the kernel at 208 registers (launch bounds alone would allow 256).  At head_dim 256 three
+// 64-bit addresses then go to scratch, stored and loaded once a work item, outside the key loop.
 template <int D, bool kBeside>
 __global__ __launch_bounds__(Impl<D>::kThreads, 2) __attribute__((amdgpu_num_vgpr(104))) void tile_persist_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[Impl<D>::kLdsBytes / 2];

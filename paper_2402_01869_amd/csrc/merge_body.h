@@ -18,6 +18,12 @@ typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 __device__ __forceinline__ void store_shared(float* a, float v) {
   __hip_atomic_store(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// A partial result for another workgroup of this launch (kShared), or for the merge kernel behind it.
+template <bool kShared>
+__device__ __forceinline__ void store_partial(float* a, float v) {
+  if constexpr (kShared) store_shared(a, v);
+  else *a = v;
+}
 __device__ __forceinline__ f32x2 load_shared(const float* a) {
   return __builtin_bit_cast(f32x2, __hip_atomic_load((const uint64_t*)a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }

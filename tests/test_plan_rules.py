@@ -175,6 +175,32 @@ def test_few_items_and_split_slots_of_the_image(H, Hkv, D):
     assert seen_units and seen_split
 
 
+def test_whole_rows_of_the_group_kernel_do_not_pay_for_the_merging_end():
+    """The build that runs rows which are not split spills no more than the kernel alone does (its key loop included); the end
+    that merges is in a build of its own."""
+    import os
+    import re
+    import shutil
+    import subprocess
+    import tempfile
+    if not shutil.which("hipcc"):
+        pytest.skip("hipcc not on PATH")
+    src = os.path.join(os.path.dirname(os.path.abspath(B.__file__)), "csrc", "attn_group.hip")
+    with tempfile.TemporaryDirectory() as tmp:
+        r = subprocess.run(["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+                            "-packed-fp32-ops", "-Rpass-analysis=kernel-resource-usage", "-c", src, "-o", os.path.join(tmp, "g.o")],
+                           capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    scratch, name = {}, None
+    for line in r.stderr.splitlines():
+        m = re.search(r"Function Name: \S*group_attn_kernelI(\S+?)EEv", line)
+        name = m.group(1) if m else None if "Function Name" in line else name
+        m = re.search(r"ScratchSize \[bytes/lane\]: (\d+)", line)
+        if m and name:
+            scratch[name] = int(m.group(1))
+    assert scratch["Li64ELb0"] == scratch["Li128ELb0"] == 0 and scratch["Li256ELb0"] <= 124, scratch
+
+
 def test_the_benchmark_names_the_kernels_that_run():
     """The report's kernel names follow the planner's launches, not the tuning alone."""
     import types
