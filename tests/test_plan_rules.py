@@ -193,7 +193,7 @@ def test_whole_rows_of_the_group_kernel_do_not_pay_for_the_merging_end():
     assert r.returncode == 0, r.stderr[-2000:]
     scratch, name = {}, None
     for line in r.stderr.splitlines():
-        m = re.search(r"Function Name: \S*group_attn_kernelI(\S+?)EEv", line)
+        m = re.search(r"Function Name: \S*group_attn_kernelI(\S+?)EEEv", line)
         name = m.group(1) if m else None if "Function Name" in line else name
         m = re.search(r"ScratchSize \[bytes/lane\]: (\d+)", line)
         if m and name:
