@@ -253,12 +253,14 @@ struct LaunchRates {
   double tile_flops;  // per us, all CUs: 64-key steps of tile workgroups
   double row_many;    // K/V bytes per us of a persistent row workgroup among many,
   double row_one;     // ... of the longest item's, beside a tile workgroup,
+  double row_rate;    // ... of all of them: one slim workgroup per CU (alone at head_dim 64 there are two: 32 heads, 224 rows of
+                      // 3000 keys 1051 us beside one short chunk, 789 after it)
   double row_alone;   // ... of a workgroup of the stand-alone launches on a CU of its own
   double pair_us;     // fork, join and upload
 };
 const LaunchRates& launch_rates(int head_dim, bool group) {
-  static const LaunchRates rates[4] = {{1.11e9, 40e3, 39e3, 22e3, 29.0}, {1.29e9, 92e3, 41e3, 38e3, 26.0},
-                                       {1.15e9, 100e3, 38e3, 50e3, 35.5}, {1.44e9, 28e3, 64e3, 38e3, 32.0}};
+  static const LaunchRates rates[4] = {{1.11e9, 40e3, 39e3, 5.2e6, 22e3, 29.0}, {1.29e9, 92e3, 41e3, 6.2e6, 38e3, 26.0},
+                                       {1.15e9, 100e3, 38e3, 6.1e6, 50e3, 35.5}, {1.44e9, 28e3, 64e3, 6.05e6, 38e3, 32.0}};
   return rates[group ? 3 : head_dim == 64 ? 0 : head_dim == 128 ? 1 : 2];
 }
 
@@ -272,17 +274,20 @@ double tiles_us(const LaunchRates& rate, int head_dim, int64_t items, int64_t st
 
 // Side by side the rows come from the queue of one workgroup per CU, 2.7 us an item; up to two rounds of long ones run one
 // after the other.  The shorter of the two kernels costs the longer one 0.4 of its own time.
-double side_by_side_us(const LaunchRates& rate, double tiles, const RowLoad& r) {
+double queued_rows_us(const LaunchRates& rate, const RowLoad& r) {
   const int64_t rounds = (r.long_items + kExpectedCus - 1) / kExpectedCus;
-  const double rows = std::max({r.bytes / 6.35e6, (r.items * 2.7 + r.bytes / rate.row_many) / kExpectedCus,
-                                (rounds <= 2 ? rounds : 1) * (r.longest / rate.row_one + 2.7)});
+  return std::max({r.bytes / rate.row_rate, (r.items * 2.7 + r.bytes / rate.row_many) / kExpectedCus,
+                   (rounds <= 2 ? rounds : 1) * (r.longest / rate.row_one + 2.7)});
+}
+double side_by_side_us(const LaunchRates& rate, double tiles, const RowLoad& r) {
+  const double rows = queued_rows_us(rate, r);
   return rate.pair_us + std::max(tiles, rows) + 0.4 * std::min(tiles, rows);
 }
 
 // One after the other the rows run at the memory's rate, or as long as the longest item takes.  Few-key units cost less than
 // behind tile items that share the CUs.
 double serial_us(const LaunchRates& rate, double tiles, const RowLoad& r, bool few_units) {
-  return (few_units ? 17.5 : 24.5) + tiles + std::max(r.bytes / 6.15e6, r.longest / rate.row_alone);
+  return (few_units ? 17.5 : 24.5) + tiles + std::max(r.bytes / 6.2e6, r.longest / rate.row_alone);
 }
 
 // Keys per decode work item when the caller leaves the choice to the library.  Whole rows (up to kDefaultRowPart keys)
@@ -374,8 +379,10 @@ RowLoad row_load(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& p
   return load;
 }
 
-// Its tile items.
-double tile_load_us(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& ps) {
+// Its tile items; *alone: without rows beside them.  From six rounds on the persistent tile kernel, whose queues keep the tiles
+// of a sequence on one L2, is the faster one at head_dim 256 too, where it only runs side by side (one row of 100 keys, 8 chunks
+// of 2048 on 2048 keys: 1087 us side by side, 1171 one after the other; 8 of 1024 on 512: 220, 212).
+double tile_load_us(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& ps, double* alone) {
   int64_t items = 0, steps = 0, most = 0;
   for (int s = 0; s < d->num_seqs; ++s) {
     const int c = d->ctx_len[s], n = d->q_len[s], part = n == 1 ? ps.row_part : ps.span_part;
@@ -389,7 +396,9 @@ double tile_load_us(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes
     }
   }
   const int64_t n_th = pool->cfg.num_heads >> ps.tile_g_shift;
-  return tiles_us(launch_rates(pool->cfg.head_dim, ps.decode_as_group), pool->cfg.head_dim, items * n_th, steps * n_th, most);
+  const double t = tiles_us(launch_rates(pool->cfg.head_dim, ps.decode_as_group), pool->cfg.head_dim, items * n_th, steps * n_th, most);
+  *alone = pool->cfg.head_dim > 128 && items * n_th >= 6 * kExpectedCus ? 1.07 * t : t;
+  return t;
 }
 
 // Keys per decode work item beside tile items that are expected to take tiles_time.  While whole rows give fewer items than
@@ -532,11 +541,13 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, Room
     ps.span_part = room != kFull || ps.spans_as_rows || tiles * head_groups >= kUnsplitWorkgroups ? kWholeSpan : choose_span_part(pool, d, ps, row_us);
   }
   // Side by side: tile items or few-key units beside rows of a kernel that has a slim build, unless one after the other is
-  // expected to take 4 % less, or not 2 % more where the rows are split (their last partitions merge them there), or because
-  // the caller asks for persistent row workgroups.  The decode rows' partition goes with the launch.
+  // expected to take less by 4 % or a fifth of the shorter kernel (where the rows are split: not 2 % more, their last
+  // partitions merge them there), or because the caller asks for persistent row workgroups.  The decode rows' partition
+  // goes with the launch.
   ps.slim_group = pool->cfg.head_dim == 128 && G <= 16;
   {
-    const double tiles_time = tile_load_us(pool, d, ps);
+    double tiles_alone = 0.0;
+    const double tiles_time = tile_load_us(pool, d, ps, &tiles_alone);
     const RowLoad whole = row_load(pool, d, ps, ps.row_part);
     const bool choose = t.decode_part_tokens == 0 && room == kFull;
     const int part_alone = choose ? choose_row_part(pool, d, ps) : ps.row_part;
@@ -546,8 +557,11 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, Room
       const LaunchRates& rate = launch_rates(pool->cfg.head_dim, ps.decode_as_group);
       double beside = side_by_side_us(rate, tiles_time, whole);
       const int part_beside = choose ? choose_row_part_beside(pool, d, ps, tiles_time, &beside) : ps.row_part;
-      const double serial = serial_us(rate, tiles_time, row_load(pool, d, ps, part_alone), ps.few_as_units && few > 0);
-      ps.side_by_side = t.row_launch >= 2 || t.row_slots > 0 || beside < (part_beside < ps.row_part ? 0.98 : 1.04) * serial;
+      const double serial = serial_us(rate, tiles_alone, row_load(pool, d, ps, part_alone), ps.few_as_units && few > 0);
+      // what can be hidden at all is the shorter kernel
+      const double hidden = std::min(tiles_time, queued_rows_us(rate, row_load(pool, d, ps, part_beside)));
+      const double slack = part_beside < ps.row_part ? -0.02 * serial : std::min(0.04 * serial, 0.2 * hidden);
+      ps.side_by_side = t.row_launch >= 2 || t.row_slots > 0 || beside < serial + slack;
       ps.row_part = ps.side_by_side ? part_beside : part_alone;
     } else {
       ps.row_part = part_alone;

@@ -89,6 +89,19 @@ def test_batches_run_side_by_side_where_that_is_faster(H, Hkv, D, n, keys, n_spa
     assert bool(_plan(H, Hkv, D, [40] + ctx, [1] + q_len)["side_by_side"]) == pair
 
 
+@pytest.mark.parametrize("H,Hkv,D,n,keys,n_span,span,prefix,pair", [
+    # one kind of work is most of the call; measured side by side / one after the other, us
+    (64, 8, 128, 196, 15062, 12, 71, 2, False),      # 1878 / 1808 a layer
+    (32, 32, 64, 224, 3000, 1, 256, 500, False),     # 1051 / 800
+    (32, 32, 64, 56, 12000, 2, 400, 500, False),     # 1023 / 794
+    (16, 16, 256, 1, 100, 8, 2048, 2048, True),      # 1087 / 1171
+    (16, 16, 256, 1, 100, 8, 2048, 4096, True),      # 1782 / 1890
+    (16, 16, 256, 1, 100, 4, 1024, 2048, False),     # 229 / 220
+])
+def test_batches_of_mostly_one_kind(H, Hkv, D, n, keys, n_span, span, prefix, pair):
+    assert bool(_plan(H, Hkv, D, [keys] * n + [prefix + span] * n_span, [1] * n + [span] * n_span)["side_by_side"]) == pair
+
+
 @pytest.mark.parametrize("H,Hkv,D,n,keys,n_span,prefix,split", [
     # measured side by side with whole rows / in items of 1024 keys, us
     (40, 40, 128, 4, 4000, 4, 2500, False),      # the tiles lead
