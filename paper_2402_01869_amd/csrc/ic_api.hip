@@ -184,8 +184,9 @@ struct PlanSizes {
   ic_plan_info info;
   int row_part, span_part, tile_rows;  // tile_rows: QUERY rows per tile item
   int min_keys;                        // rows that see fewer keys are vector row items whatever their kind
-  int vec_items;                       // row items [0, vec_items) keep fp32 weights, the rest run on the group kernel
+  int vec_items;                       // row items [0, vec_items) do not round their weights to bf16, the rest run on the group kernel
   int few_runs, few_rows;              // ... of which the last few_rows are the rows of few_runs few-key units (tile kernels)
+                                       // and the others the vector kernel's
   int tile_g_shift;                    // log2 of the query heads one tile workgroup serves
   bool spans_as_rows;
   bool few_as_units;                   // few-key rows of spans go to the tile kernels' few-key body
@@ -314,7 +315,7 @@ int choose_row_part(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes
   // Decode rows as one-row tiles are not what this model is about; and where spans run row by row, their rows take the
   // partition too, in numbers that fill the chip whole.
   if (ps.decode_as_tiles || (spans && ps.spans_as_rows)) return kDefaultRowPart;
-  const int64_t slots = group && !spans ? 2 * kExpectedCus : kExpectedCus;  // two group workgroups per CU; beside a tile workgroup one
+  const int64_t slots = group && !spans ? 2 * kExpectedCus : kExpectedCus;  // two group workgroups per CU; behind tile workgroups fewer at first
   const int64_t enough = 2 * slots;
   int64_t items = 0, keys = 0;
   int longest = 0;
@@ -442,8 +443,7 @@ double tile_step_us(int head_dim) {
 // it is looked at only when whole tiles give fewer than four rounds, and pays where one round is not full or the longest
 // tiles run alone at the end.  An item costs two steps besides its keys.  row_us: time of the row items, beside which
 // shorter spans gain nothing.  Measured: one 512-row chunk on 2500 keys, 64 heads over 8 K/V heads (128 whole tiles):
-// 98 ->
-// 62 us + 9 us of merge; 3 chunks of 67 rows on 8900 keys, 16 heads over 2 K/V heads: call 176 -> 34 us.
+// 98 -> 62 us + 9 us of merge; 3 chunks of 67 rows on 8900 keys, 16 heads over 2 K/V heads: call 176 -> 34 us.
 int choose_span_part(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& ps, double row_us) {
   const int H = pool->cfg.num_heads, D = pool->cfg.head_dim;
   const int64_t n_th = H >> ps.tile_g_shift;
@@ -490,7 +490,7 @@ int choose_span_part(const ic_pool* pool, const ic_batch_desc* d, const PlanSize
 // vector kernel (in a pool whose decode rows are the group kernel's, the vector kernel only has rows too short to
 // split).  0: the merge kernel merges them.  A partition's end takes 2-3 us longer that way (its stores have to reach
 // memory, then a counter), which overlaps only where several workgroups share a CU: on the launches of one workgroup
-// per item, which are the ones choose_row_part splits for.  From the queue of a persistent kernel it adds up: 44 rows
+// per item, which rows that choose_row_part splits run on.  Rows split beside tile items come from a queue.  From the queue of a persistent kernel it adds up: 44 rows
 // of 600..10200 keys, 40 heads, in 4096-key items 729 us a layer against 710 with the merge kernel.
 int split_units(const ic_pool* pool, const PlanSizes& ps) {
   const ic_tuning& t = pool->tune;
