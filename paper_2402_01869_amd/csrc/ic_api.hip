@@ -247,6 +247,7 @@ struct RowLoad {
   double bytes = 0.0, longest = 0.0;  // K/V bytes they read, of the longest item
   int64_t long_items = 0;             // items of at least 3/4 of the longest
   bool group = false;                 // some are the group kernel's
+  bool split = false;                 // some are parts of a row
 };
 
 // What differs between head_dim 64, 128, 256 and the group kernel's pools.
@@ -367,6 +368,7 @@ RowLoad row_load(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& p
       const bool group = rt.rest_group && rt.n_few == 0;
       const int64_t units = group ? pool->cfg.num_kv_heads : pool->cfg.num_heads;
       load.group = load.group || group;
+      load.split = load.split || c > part;
       load.items += (c + part - 1) / part * units;
       load.bytes += key_bytes * c * units;
       load.long_items += (c / part + (4 * (int64_t)(c % part) >= 3 * (int64_t)longest)) * units;
@@ -402,31 +404,34 @@ double tile_load_us(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes
   return t;
 }
 
+// The merge launch of rows that are split, where the spans need none anyway.
+double merge_launch_us(const PlanSizes& ps, const RowLoad& rows) { return rows.split && ps.span_part == kWholeSpan ? 5.0 : 0.0; }
+
 // Keys per decode work item beside tile items that are expected to take tiles_time.  While whole rows give fewer items than
 // CUs the finer partition wins ties, because one long item slows the tile workgroup on its CU and the next CU has none; from
-// then on it has to be expected to save 1.5 %.  A merge launch, where the spans need none, costs 5 us.  Measured, whole rows /
-// 1024 keys an item: 40 heads, 3 rows of 4000 keys and 2 chunks of 512 on 2000 116 / 94, 7 such rows and 3 chunks on 1500 159 /
-// 132, 16 heads of 256 dims, 6 and 2 161 / 113; where the tiles lead, 40 heads, 5 and 4 chunks on 2500 200 / 204.
-int choose_row_part_beside(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& ps, double tiles_time, double* us) {
-  static const int parts[] = {kDefaultRowPart, 2048, 1024, 768, 512, 384};
+// then on it has to be expected to save 1.5 %.  Measured, whole rows / 1024 keys an item: 40 heads, 3 rows of 4000 keys and
+// 2 chunks of 512 on 2000 116 / 94, 7 such rows and 3 chunks on 1500 159 / 132, 16 heads of 256 dims, 6 and 2 161 / 113; where
+// the tiles lead, 40 heads, 5 and 4 chunks on 2500 200 / 204.
+// rows: the load of whole rows, replaced by that of the choice.
+int choose_row_part_beside(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& ps, double tiles_time, RowLoad& rows) {
+  static const int parts[] = {2048, 1024, 768, 512, 384};
   const LaunchRates& rate = launch_rates(pool->cfg.head_dim, ps.decode_as_group);
-  const double merge = ps.span_part == kWholeSpan ? 5.0 : 0.0;
-  int best = kDefaultRowPart, longest = 0;
+  int best = ps.row_part, longest = 0;
   for (int s = 0; s < d->num_seqs; ++s)
     if (d->q_len[s] == 1) longest = std::max(longest, d->ctx_len[s]);
-  int64_t items = 0;
-  double least = 0.0;
+  double least = side_by_side_us(rate, tiles_time, rows) + merge_launch_us(ps, rows);
+  int64_t tried = rows.items;
   for (const int part : parts) {
-    if (part >= longest && part != kDefaultRowPart) continue;  // no other plan than whole rows
-    const RowLoad rows = row_load(pool, d, ps, part);
-    const double t = side_by_side_us(rate, tiles_time, rows) + (longest > part ? merge : 0.0);
-    if (least == 0.0 || t < (items < kExpectedCus ? 1.02 : 0.985) * least) {
+    if (ps.decode_as_tiles || tried >= 4 * kExpectedCus) break;  // rounds enough: a finer partition only adds items
+    if (part >= longest) continue;                               // no other plan than whole rows
+    const RowLoad finer = row_load(pool, d, ps, part);
+    const double t = side_by_side_us(rate, tiles_time, finer) + merge_launch_us(ps, finer);
+    if (t < (rows.items < kExpectedCus ? 1.02 : 0.985) * least) {
       best = part;
-      items = rows.items;
-      *us = t;
-      least = least == 0.0 ? t : std::min(least, t);
+      rows = finer;
+      least = std::min(least, t);
     }
-    if (ps.decode_as_tiles || rows.items >= 4 * kExpectedCus) break;  // rounds enough: a finer partition only adds items
+    tried = finer.items;
   }
   return best;
 }
@@ -546,22 +551,22 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, Room
   // goes with the launch.
   ps.slim_group = pool->cfg.head_dim == 128 && G <= 16;
   {
-    double tiles_alone = 0.0;
-    const double tiles_time = tile_load_us(pool, d, ps, &tiles_alone);
-    const RowLoad whole = row_load(pool, d, ps, ps.row_part);
-    const bool choose = t.decode_part_tokens == 0 && room == kFull;
+    const bool choose = t.decode_part_tokens == 0 && room == kFull, few_units = ps.few_as_units && few > 0;
     const int part_alone = choose ? choose_row_part(pool, d, ps) : ps.row_part;
-    ps.side_by_side = (tiles_time > 0.0 || (ps.few_as_units && few > 0)) && !t.serial_spans && whole.items > 0 &&
-                      (ps.decode_as_group ? whole.group && ps.slim_group : true);
-    if (ps.side_by_side) {
-      const LaunchRates& rate = launch_rates(pool->cfg.head_dim, ps.decode_as_group);
-      double beside = side_by_side_us(rate, tiles_time, whole);
-      const int part_beside = choose ? choose_row_part_beside(pool, d, ps, tiles_time, &beside) : ps.row_part;
-      const double serial = serial_us(rate, tiles_alone, row_load(pool, d, ps, part_alone), ps.few_as_units && few > 0);
-      // what can be hidden at all is the shorter kernel
-      const double hidden = std::min(tiles_time, queued_rows_us(rate, row_load(pool, d, ps, part_beside)));
-      const double slack = part_beside < ps.row_part ? -0.02 * serial : std::min(0.04 * serial, 0.2 * hidden);
-      ps.side_by_side = t.row_launch >= 2 || t.row_slots > 0 || beside < serial + slack;
+    double tiles_alone = 0.0;
+    const double tiles_time = t.serial_spans ? 0.0 : tile_load_us(pool, d, ps, &tiles_alone);
+    if (tiles_time > 0.0 || (few_units && !t.serial_spans)) {
+      RowLoad rows = row_load(pool, d, ps, ps.row_part);
+      ps.side_by_side = rows.items > 0 && (ps.decode_as_group ? rows.group && ps.slim_group : true);
+      const RowLoad alone = !ps.side_by_side || part_alone == ps.row_part ? rows : row_load(pool, d, ps, part_alone);
+      const int part_beside = ps.side_by_side && choose ? choose_row_part_beside(pool, d, ps, tiles_time, rows) : ps.row_part;
+      if (ps.side_by_side && t.row_launch < 2 && t.row_slots == 0) {
+        const LaunchRates& rate = launch_rates(pool->cfg.head_dim, ps.decode_as_group);
+        const double serial = serial_us(rate, tiles_alone, alone, few_units);
+        const double hidden = std::min(tiles_time, queued_rows_us(rate, rows));  // all that can be: the shorter kernel
+        const double slack = part_beside < ps.row_part ? -0.02 * serial : std::min(0.04 * serial, 0.2 * hidden);
+        ps.side_by_side = side_by_side_us(rate, tiles_time, rows) + merge_launch_us(ps, rows) < serial + slack;
+      }
       ps.row_part = ps.side_by_side ? part_beside : part_alone;
     } else {
       ps.row_part = part_alone;
