@@ -236,10 +236,10 @@ __device__ __forceinline__ void group_body(const AttnParams& p, const RowItem& i
       p.out[((int64_t)it.qrow * H + hq) * D + d] = __builtin_bit_cast(uint16_t, o);
     } else {
       const int64_t ps = (int64_t)it.slot * H + hq;
-      mergep::store_partial<kMerge>(&p.part_o[ps * D + d], O);
+      mergep::store_shared(&p.part_o[ps * D + d], O);
       if (d == 0) {
-        mergep::store_partial<kMerge>(&p.part_ml[ps * 2], M);
-        mergep::store_partial<kMerge>(&p.part_ml[ps * 2 + 1], L);
+        mergep::store_shared(&p.part_ml[ps * 2], M);
+        mergep::store_shared(&p.part_ml[ps * 2 + 1], L);
       }
     }
   }

@@ -257,10 +257,10 @@ __device__ __forceinline__ void row_body(const AttnParams& p, const RowItem& it,
       p.out[((int64_t)it.qrow * H + head) * D + d] = (uint16_t)f32_to_bf16(O / L);
     } else {
       const int64_t ps = (int64_t)it.slot * H + head;
-      mergep::store_partial<kMerge>(&p.part_o[ps * D + d], O);
+      mergep::store_shared(&p.part_o[ps * D + d], O);
       if (d == 0) {
-        mergep::store_partial<kMerge>(&p.part_ml[ps * 2], M);
-        mergep::store_partial<kMerge>(&p.part_ml[ps * 2 + 1], L);
+        mergep::store_shared(&p.part_ml[ps * 2], M);
+        mergep::store_shared(&p.part_ml[ps * 2 + 1], L);
       }
     }
   }
