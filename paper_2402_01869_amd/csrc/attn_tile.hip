@@ -1,9 +1,10 @@
-// Tile kernels: recomputation spans on the matrix cores.  head_dim <= 128: 32 query rows per wave (tile_body.h);
+// Tile kernels: recomputation spans on the matrix cores.  head_dim <= 128: 32 query rows per wave (tile32_body.h);
 // head_dim 256: 16 rows per wave (tile16_body.h).  Either way a workgroup is 8 waves, two per SIMD.  The rows of a span
 // that see fewer than 64 keys are units of their own (few_body.h), handed out after the tile items.
 #include <algorithm>
 
 #include "few_body.h"
+#include "tile32_body.h"
 
 namespace ic {
 
@@ -14,11 +15,11 @@ using namespace tilep;
 // What a workgroup of the tile kernels is for head_dim D.
 template <int D, bool k16 = (D > 128)>
 struct Impl {
-  static constexpr int kThreads = TW<D>::kThreads;
-  static constexpr int kLdsBytes = tile_lds_bytes<D>();
+  static constexpr int kThreads = tile32::G32<D>::kThreads;
+  static constexpr int kLdsBytes = std::max(tile32::tile32_lds_bytes<D>(), fewp::few_lds_bytes<D>());
   template <bool kAlone>
   static __device__ __forceinline__ void body(const AttnParams& p, const TileItem& it, int th, uint16_t* lds) {
-    tile_body<D>(p, it, th, lds);
+    tile32::tile32_body<D>(p, it, th, lds);
   }
 };
 template <int D>
@@ -51,7 +52,7 @@ __device__ __forceinline__ void run_few(const AttnParams& p, uint32_t unit, uint
 
 template <int D>
 __global__ __launch_bounds__(Impl<D>::kThreads, 2) void tile_attn_kernel(AttnParams p) {
-  __shared__ __attribute__((aligned(16))) uint16_t lds[Impl<D>::kLdsBytes / 2];
+  __shared__ __attribute__((aligned(1024))) uint16_t lds[Impl<D>::kLdsBytes / 2];
   const int n_th = p.num_heads >> p.tile_g_shift;  // head groups, each served by one workgroup per item
   const uint32_t wg = blockIdx.x;
   const uint32_t n_tile = (uint32_t)p.n_tile_items * (uint32_t)n_th;
@@ -71,8 +72,8 @@ __global__ __launch_bounds__(Impl<D>::kThreads, 2) void tile_attn_kernel(AttnPar
 // (L2 domains) by block index, so XCD x = index % 8 owns the tile items of the heads h = x (mod 8),
 // in head-major order: the query tiles of one (sequence, head), which read the same keys, run on
 // one L2 at the same time, and each span's keys are fetched from HBM about once.
-// Register budget: at most 216 per lane for head_dim <= 128, 208 for head_dim 256 (checked by the test-suite
-// from the compiler's resource report).  Two waves of this kernel and one of the slim row kernel (80, head_dim
+// Register budget: at most 208 per lane, vector and accumulation registers together (checked by the test-suite
+// from the compiler's resource report and listing).  Two waves of this kernel and one of the slim row kernel (80, head_dim
 // 256: 96) or of the slim group kernel (96) fill the 512 of a SIMD, which is what lets one workgroup of each
 // share a CU.
 // kBeside only names the build (side by side with a row or group kernel, or on its own), so that a kernel trace
@@ -82,7 +83,7 @@ __global__ __launch_bounds__(Impl<D>::kThreads, 2) void tile_attn_kernel(AttnPar
 // 64-bit addresses then go to scratch, stored and loaded once a work item, outside the key loop.
 template <int D, bool kBeside>
 __global__ __launch_bounds__(Impl<D>::kThreads, 2) __attribute__((amdgpu_num_vgpr(104))) void tile_persist_kernel(AttnParams p) {
-  __shared__ __attribute__((aligned(16))) uint16_t lds[Impl<D>::kLdsBytes / 2];
+  __shared__ __attribute__((aligned(1024))) uint16_t lds[Impl<D>::kLdsBytes / 2];
   __shared__ int s_next;
   if (p.tile_first) __builtin_amdgcn_s_setprio(3);
   const int H = p.num_heads >> p.tile_g_shift;               // head groups
