@@ -13,22 +13,20 @@ namespace {
 using namespace tilep;
 
 // What a workgroup of the tile kernels is for head_dim D.
-template <int D, bool k16 = (D > 128)>
+template <int D>
 struct Impl {
   static constexpr int kThreads = tile32::G32<D>::kThreads;
   static constexpr int kLdsBytes = std::max(tile32::tile32_lds_bytes<D>(), fewp::few_lds_bytes<D>());
-  template <bool kAlone>
   static __device__ __forceinline__ void body(const AttnParams& p, const TileItem& it, int th, uint16_t* lds) {
     tile32::tile32_body<D>(p, it, th, lds);
   }
 };
-template <int D>
-struct Impl<D, true> {
-  static constexpr int kThreads = tile16::G16<D>::kThreads;
-  static constexpr int kLdsBytes = tile16::tile16_lds_bytes<D>();
-  template <bool kAlone>  // a kernel with its SIMDs to itself has registers for the pinned operand prefetch
+template <>
+struct Impl<tile16::kDim> {
+  static constexpr int kThreads = tile16::kThreads;
+  static constexpr int kLdsBytes = std::max(tile16::kLdsBytes, fewp::few_lds_bytes<tile16::kDim>());
   static __device__ __forceinline__ void body(const AttnParams& p, const TileItem& it, int th, uint16_t* lds) {
-    tile16::tile16_body<D, kAlone>(p, it, th, lds);
+    tile16::tile16_body(p, it, th, lds);
   }
 };
 
@@ -63,7 +61,7 @@ __global__ __launch_bounds__(Impl<D>::kThreads, 2) void tile_attn_kernel(AttnPar
   const int item_idx = wg / n_th;
   const int th = wg - item_idx * n_th;
   const TileItem it = p.tile_items[item_idx];
-  Impl<D>::template body<true>(p, it, th, lds);
+  Impl<D>::body(p, it, th, lds);
 }
 
 // Persistent launch of the same body, for running beside the row kernel: `slots` workgroups (one
@@ -79,8 +77,7 @@ __global__ __launch_bounds__(Impl<D>::kThreads, 2) void tile_attn_kernel(AttnPar
 // kBeside only names the build (side by side with a row or group kernel, or on its own), so that a kernel trace
 // tells the two uses apart; the code is the same.
 // amdgpu_num_vgpr: on this target vector and accumulation registers share one file and the compiler doubles the
-// figure it is given, so 104 caps the kernel at 208 registers (launch bounds alone would allow 256).  At head_dim 256 three
-// 64-bit addresses then go to scratch, stored and loaded once a work item, outside the key loop.
+// figure it is given, so 104 caps the kernel at 208 registers (launch bounds alone would allow 256).
 template <int D, bool kBeside>
 __global__ __launch_bounds__(Impl<D>::kThreads, 2) __attribute__((amdgpu_num_vgpr(104))) void tile_persist_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds[Impl<D>::kLdsBytes / 2];
@@ -110,7 +107,7 @@ __global__ __launch_bounds__(Impl<D>::kThreads, 2) __attribute__((amdgpu_num_vgp
       th = idx - item * (uint32_t)H;
     }
     const TileItem it = p.tile_items[item];
-    Impl<D>::template body<false>(p, it, (int)th, lds);
+    Impl<D>::body(p, it, (int)th, lds);
     idx = next();
   }
   // (a loop of its own: values of one body kept in registers across the other would not fit)

@@ -666,8 +666,9 @@ PlanLaunches plan_launches(const ic_pool* pool, const PlanSizes& ps) {
   // head_dim <= 128: the persistent tile launch also when no other kernel runs beside it.  Its per-XCD queues keep the
   // query tiles of one (sequence, head) on one L2: on 2048-row chunks the spans then fetch 2.6 x instead of 6.9 x
   // their keys from HBM and finish 7 % sooner (9.66 against 10.41 ms); shorter chunks and grouped pools: no change.
-  // head_dim 256: one workgroup per work item; the persistent build is held to 208 registers for the sake of
-  // its neighbour and is 19 % slower alone (0.197 against 0.166 ms on the GPT-J-shaped chunks).
+  // head_dim 256: one workgroup per work item.  Neither is the better one throughout: 8 chunks of 512 rows on 512..2048 keys, 16
+  // heads, 124 us either way, 4 chunks of 200..400 on 1000..6000, 16 heads over 4, 118 us against 124, 8 of 2048 on 8192 2.58
+  // against 2.53 ms.
   how.tile = !tiles ? IC_LAUNCH_NONE : how.side_by_side || D <= 128 ? IC_LAUNCH_PERSISTENT : IC_LAUNCH_PER_ITEM;
   // row_launch = 3: the side-by-side builds, alone
   how.group = !groups ? IC_LAUNCH_NONE : how.side_by_side || (t.row_launch == 3 && ps.slim_group) ? IC_LAUNCH_SLIM : IC_LAUNCH_PER_ITEM;

@@ -1,84 +1,47 @@
-// Tile path for head_dim 256: the work item, staging, online softmax and epilogue of tile_body.h (recomputation
-// chunks, Section 4.2, on the matrix cores), with 16 query rows per wave instead of 32.
+// Tile path for head_dim 256: the work item, steps and schedule of tile32_body.h (recomputation chunks, Section 4.2, on the
+// matrix cores), with 16 query rows per wave instead of 32.
 //
-// Why: 32 rows x 256 dims of fp32 accumulators (128 registers) plus the wave's Q^T (64) leave no room for a second
+// Why 16: 32 rows x 256 dims of fp32 accumulators (128 registers) plus the wave's Q^T (64) leave no room for a second
 // wave on a SIMD, and a lone wave has nothing to hide its LDS and memory waits behind.  With 16 rows per wave
-// (v_mfma_f32_16x16x32_bf16) a wave holds 64 accumulator and 32 Q^T registers, a workgroup is 8 waves of 16 rows
-// (the same 128-row tile), and two waves share every SIMD.  The price is LDS traffic: every K and V operand read now
-// feeds half as many multiply-adds.
+// (v_mfma_f32_16x16x32_bf16, 16 cycles) a wave holds 64 accumulator and 32 Q^T registers, a workgroup is 8 waves of 16 rows
+// (128 rows), and two waves share every SIMD.  The price is LDS traffic: every K and V operand read now
+// feeds half as many multiply-adds, 1 KiB per MFMA, which is what LDS delivers (256 bytes a cycle and CU) when all four SIMDs multiply.
 //   - S^T = K Q^T per 16-key subtile: A = K[16 keys][32 dims] from LDS (lane: key = lane % 16, dims 8 (lane / 16) ..+7),
 //     B = Q^T from registers; result: lane holds query column lane % 16, keys 4 (lane / 16) ..+3 of the subtile.
-//   - O^T += V^T P^T per 32 keys (two subtiles) and 16 dims: the two subtiles' weights of a lane, rounded to bf16, ARE
-//     the B operand (slot j < 4 of lane group g <-> key 4 g + j of the first subtile, slot 4 + j <-> the same key of the
+//   - O^T += V^T P^T per 32 keys (two subtiles, one half of a tile) and 16 dims: the two subtiles' weights of a lane, rounded to
+//     bf16, ARE the B operand (slot j < 4 of lane group g <-> key 4 g + j of the first subtile, slot 4 + j <-> the same key of the
 //     second); the A operand comes from two LDS transpose loads in that key order.
+// What bounds it: at two waves a SIMD and an LDS operand per 16-cycle MFMA, LDS reads and issue; on N(0,1) data the power cap.
+// Before, a wave did the scores, the weights and the products of a 64-key tile one after the other, K and V went through 32
+// registers, the weights were summed by v_dot2 (which waits for the MFMAs in flight), and the matrix pipe was idle for 70 % of the
+// time.  Measured, before and now: 8 chunks of 2048 rows on 8192 keys, 16 heads, 3.15 -> 2.53 ms (786 -> 979 TFLOP/s;
+// all-zero data 2.84 -> 1.98 ms); 8 chunks of 512 on 512..2048, 146.6 -> 121.7 us, beside 64 decode rows the call 300 -> 293 us.
+// 512 threads, 208 registers: as many as the 32-row shape's kernel, so the same neighbours fit beside it.
 #pragma once
 
-#include "tile_body.h"
+#include "tile32_body.h"
 
 namespace ic {
 namespace tile16 {
 
 using namespace tilep;
+using tile32::barrier;
+using tile32::copy_region;
+using tile32::here;
+using tile32::pin;
+using tile32::unroll;
 
+// The 16-row shape with tiles staged as padded rows (the few-key units).
 template <int D>
 struct G16 {
-  static constexpr int kRows = 16;                        // query rows (x heads of a group) per wave
-  static constexpr int kWaves = tile_rows(D) / kRows;     // 8 for head_dim 256
-  static constexpr int kThreads = 64 * kWaves;
   // bf16 per LDS row of K and of V: rows shift by 8 of the 64 banks (32 bytes).  An operand read of K takes 16 bytes of
-  // 16 keys per quarter wave, a transpose read of V 32 bytes of 8 keys per half wave: both then cover all banks once
-  // (measured: with the 16-byte shift of tile_body.h the K reads of this layout are 5 % slower, with its 64-byte
-  // shift the V reads conflict two ways).
+  // 16 keys per quarter wave, a transpose read of V 32 bytes of 8 keys per half wave: both then cover all banks once.
   static constexpr int kKStride = D + 16;
   static constexpr int kVStride = D + 16;
   static constexpr int kChunks = D / 8;                   // 16-byte chunks per token row
-  static constexpr int kLoads = kTileK * kChunks / kThreads;  // K (and V) chunks per thread and tile
   static constexpr int kQSteps = D / 32;                  // MFMA k-steps of Q K^T
   static constexpr int kDTiles = D / 16;                  // 16-row tiles of O^T
-  static_assert(kThreads <= 1024, "workgroup size");
 };
-
-template <int D>
-struct Staging16 {
-  static_assert(kTileK * G16<D>::kChunks % G16<D>::kThreads == 0, "a tile must split evenly over the threads");
-  u32x4 k[G16<D>::kLoads];
-  u32x4 v[G16<D>::kLoads];
-};
-
-// Global -> registers for one 64-key tile: thread u takes 16-byte chunk u + kThreads j of the K tile and of the V
-// tile; a wave's 64 chunks of one load lie in one (block, head) tile and are consecutive: fully coalesced.
-template <int D>
-__device__ __forceinline__ void fetch_tile16(Staging16<D>& st, const char* pool, const int (&ids)[4], int head, int H,
-                                             int tid) {
-  using G = G16<D>;
-  constexpr int kTileBytes = kBlockSize * D * 2;
-  const int64_t blk_stride = (int64_t)2 * H * kTileBytes;
-#pragma unroll
-  for (int j = 0; j < G::kLoads; ++j) {
-    const int u = tid + G::kThreads * j;
-    const int tok = u / G::kChunks;  // 0..63
-    const int c = u % G::kChunks;
-    const int bsel = __builtin_amdgcn_readfirstlane(tok / kBlockSize);  // wave-uniform
-    const char* a = pool + (int64_t)head * kTileBytes + (int64_t)ids[bsel] * blk_stride + (tok % kBlockSize) * (D * 2) + c * 16;
-    st.k[j] = *(const u32x4*)a;
-    st.v[j] = *(const u32x4*)(a + (int64_t)H * kTileBytes);
-  }
-}
-
-// Registers -> LDS as [key][dim] rows (padded).  V of keys >= n_valid is zeroed (dead slots may hold NaN).
-template <int D>
-__device__ __forceinline__ void stage_tile16(const Staging16<D>& st, uint16_t* ks, uint16_t* vs, int tid, int n_valid) {
-  using G = G16<D>;
-#pragma unroll
-  for (int j = 0; j < G::kLoads; ++j) {
-    const int u = tid + G::kThreads * j;
-    const int tok = u / G::kChunks, c = u % G::kChunks;
-    *(u32x4*)(ks + tok * G::kKStride + c * 8) = st.k[j];
-    u32x4 v = st.v[j];
-    if (tok >= n_valid) v = (u32x4){0u, 0u, 0u, 0u};
-    *(u32x4*)(vs + tok * G::kVStride + c * 8) = v;
-  }
-}
 
 // A operand of O^T += V^T P^T for dims d0 .. d0 + 15 and the 32 keys of half h of the tile, in the key order of the
 // weights (see the head of this file).  The LDS transpose load (layout measured on gfx950): in a group of 16 lanes,
@@ -96,221 +59,391 @@ __device__ __forceinline__ bf16x8 read_vt16(const uint16_t* vs, int d0, int h, i
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// One 64-key tile for one wave.  mask is set only for tiles that straddle the wave's causal diagonal.
-// kPin: pin the order of operand reads and MFMAs written here (costs about ten registers; the build that shares its
-// SIMDs with another kernel cannot afford them).
-template <int D, bool kPin>
-__device__ __forceinline__ void wave_step16(const uint16_t* ks, const uint16_t* vs, const bf16x8 (&qreg)[G16<D>::kQSteps],
-                                            f32x4 (&acc_o)[G16<D>::kDTiles], float& m, float& l, int kt, int pos, int lane,
-                                            float sc, bool mask) {
-  using G = G16<D>;
-  const int col = lane & 15, g = lane >> 4;
-  f32x4 s[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) s[u] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  {
-    // The four 16-key subtiles advance together (four independent accumulators alternate in the matrix pipe), and the
-    // A operands of the next k-step are read from LDS before this step's MFMAs issue: the kernel is bound by LDS
-    // operand reads, and left to itself the compiler keeps only one or two of them in flight per wave.
-    const uint16_t* kp = ks + col * G::kKStride + 8 * g;
-    bf16x8 a[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) a[u] = *(const bf16x8*)(kp + 16 * u * G::kKStride);
-#pragma unroll
-    for (int t = 0; t < G::kQSteps; ++t) {
-      bf16x8 n[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) n[u] = t + 1 < G::kQSteps ? *(const bf16x8*)(kp + 16 * u * G::kKStride + 32 * (t + 1)) : a[u];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) s[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u], qreg[t], s[u], 0, 0, 0);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) a[u] = n[u];
-    }
-    // pin that order (0x100: LDS reads, 0x008: MFMAs): the scheduler otherwise moves every read next to its use
-    if constexpr (kPin) {
-      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-      for (int t = 0; t + 1 < G::kQSteps; ++t) {
-        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-    }
-  }
-  // this lane: query column col, keys kt + 16 u + 4 g + i
-  if (mask) {  // wave-uniform; the empty asm keeps this a branch instead of 16 always-on selects
-    asm volatile("" ::: "memory");
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) s[u][i] = kt + 16 * u + 4 * g + i > pos ? -__builtin_inff() : s[u][i];
-  }
-  float tmax = -__builtin_inff();
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) tmax = __builtin_fmaxf(tmax, s[u][i]);
-  tmax *= sc;
-  // Lazy reference maximum: a lane looks at its own 16 scores; the wave reduces across the four lanes of a column
-  // (and rescales) only when some score exceeds its column's reference by more than 2^kLazyLog2.
-  if (__builtin_amdgcn_ballot_w64(tmax > m + kLazyLog2) != 0) {
-    tmax = __builtin_fmaxf(tmax, __shfl_xor(tmax, 16));
-    tmax = __builtin_fmaxf(tmax, __shfl_xor(tmax, 32));
-    const float m_cand = __builtin_fmaxf(m, tmax);
-    const bool grew = m_cand > m + kLazyLog2;  // the same in the four lanes of a column
-    const float alpha = grew ? __builtin_amdgcn_exp2f(m - m_cand) : 1.0f;
-    m = grew ? m_cand : m;
-    l *= alpha;
-#pragma unroll
-    for (int dt = 0; dt < G::kDTiles; ++dt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc_o[dt][i] *= alpha;
-  }
-  // weights rounded to bf16 in pairs and summed as rounded: the normaliser counts what the matrix core multiplies
-  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-  bf16x8 pb[2];
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int i = 0; i < 4; i += 2) {
-      const bf16x2 pr = {(__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(s[u][i], sc, -m)),
-                         (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(s[u][i + 1], sc, -m))};
-      l = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, l, false);
-      pb[u >> 1][4 * (u & 1) + i] = pr[0];
-      pb[u >> 1][4 * (u & 1) + i + 1] = pr[1];
-    }
-  // O^T += V^T P^T: the 32-key half outer, so that the kDTiles independent accumulators alternate; operands are
-  // read four MFMAs ahead.
-  {
-    constexpr int kAhead = 4, kOps = 2 * G::kDTiles;
-    bf16x8 a[kAhead];
-#pragma unroll
-    for (int i = 0; i < kAhead; ++i) a[i] = read_vt16<D>(vs, 16 * (i % G::kDTiles), i / G::kDTiles, lane);
-#pragma unroll
-    for (int i = 0; i < kOps; ++i) {
-      const bf16x8 cur = a[i % kAhead];
-      if (i + kAhead < kOps) a[i % kAhead] = read_vt16<D>(vs, 16 * ((i + kAhead) % G::kDTiles), (i + kAhead) / G::kDTiles, lane);
-      acc_o[i % G::kDTiles] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur, pb[i / G::kDTiles], acc_o[i % G::kDTiles], 0, 0, 0);
-    }
-    if constexpr (kPin) {  // two transpose loads per operand
-      __builtin_amdgcn_sched_group_barrier(0x100, 2 * kAhead, 0);
-#pragma unroll
-      for (int i = 0; i < kOps; ++i) {
-        if (i + kAhead < kOps) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      }
-    }
-  }
-}
-
 template <int D>
 constexpr int tile16_buf_elems() {
   return kTileK * G16<D>::kKStride + kTileK * G16<D>::kVStride;
 }
-template <int D>
-constexpr int tile16_lds_bytes() {
-  return 2 * tile16_buf_elems<D>() * 2;  // two buffers of bf16
+// Staged tiles: as tile32_body.h's, 1 KiB regions of 8 keys x 64 dims, region (key / 8) * 4 + dim / 64, copied by one load of a wave
+// each.  Chunk c of key k sits at chunk c ^ spread(k) of the key's 128 bytes.  A transpose read of V takes two neighbouring chunks of 8
+// keys.  A K operand read, in one pass, takes chunk c of 8 keys and chunk c ^ 1 of the other 8 (lanes 0-3, 12-15 and 20-27, as measured:
+// with bit 0 of the spread depending on the key half of these passes conflict).  Either then covers all banks once.
+__device__ __forceinline__ int spread(int key) { return ((key >> 1) & 1) << 2 | ((key >> 2) & 1) << 1; }
+
+constexpr int kDim = 256, kRows = 16, kWaves = 8, kThreads = 64 * kWaves;  // query rows (x heads of a group) per wave
+constexpr int kTileBytes = kTileK * kDim * 2;               // one staged tile of K or of V
+constexpr int kRegions = kTileBytes / 1024 / kWaves;        // regions of a tile that one wave copies: keys 8 w .. 8 w + 7
+constexpr int kKeyGroup = 16 * kDim * 2;                    // bytes from 16 keys to the next 16
+constexpr int kQ = 2 * (kDim / 32), kP = kDim / 16;         // MFMAs of a half's scores (two subtiles) and of its products
+constexpr int kLdsBytes = 4 * kTileBytes;                   // two tiles of K, two of V
+static_assert(tile_rows(kDim) == kRows * kWaves && kRegions == kDim / 64, "a workgroup's rows, and a wave's keys");
+
+// Accumulation registers by number, all 104 of them, as in tile32_body.h: O^T of 16-dim tile dt, Q^T of k-step t, the normaliser, ones.
+constexpr int acc_o(int dt) { return 4 * dt; }
+constexpr int acc_q(int t) { return kDim / 4 + 4 * t; }
+constexpr int kAccL = kDim / 4 + kDim / 8, kAccOnes = kAccL + 4;
+
+// s (vector registers) = a * Q^T(0), or += a * Q^T(T)
+template <int T>
+__device__ __forceinline__ void mfma_qk(f32x4& s, const u32x4 a) {
+  constexpr int R = acc_q(T);
+  if constexpr (T == 0) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, a[%2:%3], 0" : "=&v"(s) : "v"(a), "n"(R), "n"(R + 3) : IC_ACC_104);
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, a[%2:%3], %0" : "+v"(s) : "v"(a), "n"(R), "n"(R + 3) : IC_ACC_104);
+}
+// O^T(DT) += v * p
+template <int DT>
+__device__ __forceinline__ void mfma_pv(const bf16x8 v, const bf16x8 p) {
+  constexpr int R = acc_o(DT);
+  asm volatile("v_mfma_f32_16x16x32_bf16 a[%2:%3], %0, %1, a[%2:%3]" ::"v"(v), "v"(p), "n"(R), "n"(R + 3) : IC_ACC_104);
+}
+// Normaliser += the weights of p, as rounded (a product with ones: every row of the result is the sum of a column's 32
+// weights).  kFirst: of a step, whose weights are summed by themselves before they join the running total.
+template <bool kFirst>
+__device__ __forceinline__ void normaliser(const bf16x8 p) {
+  if constexpr (kFirst) asm volatile("v_mfma_f32_16x16x32_bf16 a[%1:%2], a[%3:%4], %0, 0" ::"v"(p), "n"(kAccL), "n"(kAccL + 3), "n"(kAccOnes), "n"(kAccOnes + 3) : IC_ACC_104);
+  else asm volatile("v_mfma_f32_16x16x32_bf16 a[%1:%2], a[%3:%4], %0, a[%1:%2]" ::"v"(p), "n"(kAccL), "n"(kAccL + 3), "n"(kAccOnes), "n"(kAccOnes + 3) : IC_ACC_104);
 }
 
-// One TileItem x one group of (1 << p.tile_g_shift) query heads that share a K/V head, executed by a workgroup of
-// tile_rows(D) / 16 waves (see tile_body in tile_body.h for the row mapping).  lds: tile16_lds_bytes<D>() bytes.
-template <int D, bool kPin>
+// The 8 scores of a lane become weights in 12 operations of two instructions (the last kind one): kind 0 the exponents of pair j,
+// 1 their exponentials, 2 rounding to bf16.  K counts them in an order that keeps each a pair behind the one it needs.
+template <int K>
+__device__ __forceinline__ void weight_op(f32x4 (&s)[2], bf16x8& pw, float negm, float sc) {
+  constexpr int kind = K < 2 ? 0 : K == 2 ? 1 : K < 9 ? (K - 3) % 3 : K == 9 ? 1 : 2;
+  constexpr int j = K < 2 ? K : K == 2 ? 0 : K < 9 ? (K - 3) / 3 + 2 - kind : K == 9 ? 3 : K - 8;
+  constexpr int u = j / 2, i = 2 * (j % 2);
+  if constexpr (kind == 0) {
+    s[u][i] = __builtin_fmaf(s[u][i], sc, negm);
+    s[u][i + 1] = __builtin_fmaf(s[u][i + 1], sc, negm);
+  } else if constexpr (kind == 1) {
+    s[u][i] = __builtin_amdgcn_exp2f(s[u][i]);
+    s[u][i + 1] = __builtin_amdgcn_exp2f(s[u][i + 1]);
+  } else {
+    pw[2 * j] = (__bf16)s[u][i];
+    pw[2 * j + 1] = (__bf16)s[u][i + 1];
+  }
+}
+
+// One TileItem x one group of (1 << p.tile_g_shift) query heads that share a K/V head, executed by a workgroup of kWaves
+// waves (see tile32_body() for the row mapping and for the steps, which are the same).  lds: kLdsBytes, 1 KiB aligned.
 __device__ __forceinline__ void tile16_body(const AttnParams& p, const TileItem& it, int th, uint16_t* lds) {
-  using G = G16<D>;
+  constexpr int D = kDim, kS = kQ + kP, kR = kRegions;
+  typedef __attribute__((address_space(3))) const char lds_char;
+  typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
+  typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
   const int H = p.num_heads, Hk = p.num_kv_heads, gs = p.tile_g_shift;
   const int head0 = th << gs;
   const int kvh = head0 / p.group;
   const int n_rows_t = it.n_rows << gs;  // rows of the tile: query rows x heads of the group
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = here();
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int col = lane & 15, g = lane >> 4;
 
-  const int r = G::kRows * w + col;                  // row inside the tile
-  const int r_eff = min(r, n_rows_t - 1);            // dead rows mirror the last live one
-  const int pos = it.pos0 + (r_eff >> gs);           // last visible key of this lane's row
-  const int wave_pos_lo = it.pos0 + min((G::kRows * w) >> gs, it.n_rows - 1);
-  const int wave_pos_hi = it.pos0 + min((G::kRows * w + G::kRows - 1) >> gs, it.n_rows - 1);
-  bf16x8 qreg[G::kQSteps];
-  {
-    const int head = head0 + (r_eff & ((1 << gs) - 1));
-    const uint16_t* qp = p.q + ((int64_t)(it.qrow0 + (r_eff >> gs)) * H + head) * D + 8 * g;
-#pragma unroll
-    for (int t = 0; t < G::kQSteps; ++t) qreg[t] = *(const bf16x8*)(qp + 32 * t);
-  }
-  f32x4 acc_o[G::kDTiles];
-#pragma unroll
-  for (int dt = 0; dt < G::kDTiles; ++dt) acc_o[dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  float m = kNegBig, l = 0.f;
-
-  const char* pool = (const char*)p.pool;
-  typedef __attribute__((address_space(4))) const int32_t const_i32;
-  const_i32* bt = (const_i32*)(p.bt_flat + p.bt_off[it.seq]);  // wave-uniform, read-only: scalar loads
-  const int last_blk = (it.k_end - 1) / kBlockSize;
-  const int n_tiles = (it.k_end - it.k_begin + kTileK - 1) / kTileK;
+  // row of the tile (dead rows mirror the last live one), and the last key it sees
+  auto row_of = [&](int ln) { return min(kRows * w + (ln & 15), n_rows_t - 1); };
+  auto pos_of = [&](int ln) { return it.pos0 + (row_of(ln) >> gs); };
+  const int wave_pos_lo = it.pos0 + min((kRows * w) >> gs, it.n_rows - 1);
+  const int wave_pos_hi = it.pos0 + min((kRows * w + kRows - 1) >> gs, it.n_rows - 1);
   const float sc = p.scale_log2e;
-  auto tile_ids = [&](int t, int (&ids)[4]) {
-    const int b0 = (it.k_begin + t * kTileK) / kBlockSize;
+
+  // ---- keys and values: this wave copies keys 8 w .. 8 w + 7 of every tile, half of block w / 2 of the tile's four
+  typedef __attribute__((address_space(4))) const int32_t const_i32;
+  const_i32* bt = (const_i32*)(p.bt_flat + p.bt_off[it.seq]);
+  const int last_blk = (it.k_end - 1) / kBlockSize;   // last table entry this item may touch
+  const int n_tiles = (it.k_end - it.k_begin + kTileK - 1) / kTileK;
+  constexpr int kBlockBytes = kBlockSize * D * 2;     // one (K or V, head) tile of a block
+  const uint32_t blk_stride = 2u * (uint32_t)Hk * kBlockBytes;
+  const char* const kbase = (const char*)p.pool + (int64_t)kvh * kBlockBytes;
+  const int64_t vplane = (int64_t)Hk * kBlockBytes;
+  const int my_key = 8 * (w & 1) + (lane >> 3);       // inside the block
+  const uint32_t lane_off = (uint32_t)(my_key * (D * 2) + ((lane & 7) ^ spread(my_key)) * 16);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)lds;
+  const uint32_t my_lds = lds0 + (uint32_t)(kR * w) * 1024u;
+  constexpr int kVBuf = 2 * kTileBytes;               // the two buffers of V follow those of K
+  // Tiles past the item's end re-read its last block and are never used.
+  auto block_id = [&](int t) { return bt[min((it.k_begin + t * kTileK) / kBlockSize + w / 2, last_blk)]; };
+  auto copy_tile = [&](int id, int64_t plane, int buf) __attribute__((always_inline)) {
+    const char* b = kbase + plane + (uint64_t)(uint32_t)id * blk_stride;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ids[i] = bt[min(b0 + i, last_blk)];
+    for (int j = 0; j < kR; ++j) copy_region(b + 128 * j, lane_off, my_lds + (uint32_t)(buf + 1024 * j));
+  };
+  int id_u = block_id(0), id_1 = block_id(1), id_2 = block_id(2);  // blocks of tiles u, u + 1, u + 2
+  copy_tile(id_u, 0, 0);
+  copy_tile(id_1, 0, kTileBytes);
+  copy_tile(id_u, vplane, kVBuf);
+
+  // ---- this wave's Q^T, O^T = 0, normaliser = 0
+  {
+    const int r = row_of(lane);
+    const int head = head0 + (r & ((1 << gs) - 1));
+    const uint16_t* qp = p.q + ((int64_t)(it.qrow0 + (r >> gs)) * H + head) * D + 8 * g;
+    u32x4 q[D / 32];
+#pragma unroll
+    for (int t = 0; t < D / 32; ++t) q[t] = *(const u32x4*)(qp + 32 * t);
+    tile32::acc_mine<128>();
+    unroll<D / 4>([&](auto i) __attribute__((always_inline)) { tile32::acc_write<decltype(i)::value>(0u); });
+    unroll<D / 8>([&](auto i) __attribute__((always_inline)) {
+      constexpr int e = decltype(i)::value;
+      tile32::acc_write<acc_q(0) + e>(q[e / 4][e % 4]);
+    });
+    unroll<4>([&](auto i) __attribute__((always_inline)) {
+      tile32::acc_write<kAccL + decltype(i)::value>(0u);
+      tile32::acc_write<kAccOnes + decltype(i)::value>(0x3f803f80u);
+    });
+    tile32::acc_mine<128>();
+  }
+  float m = kNegBig;                    // reference of the weights, in log2 units
+  float l = 0.f;                        // normaliser of this lane's column, without the last step's sums
+  float top = -__builtin_inff();        // this lane's largest raw score in the half that is weighed next
+  f32x4 sa[2], sb[2];                   // scores of even and odd halves, two subtiles each
+  bf16x8 pa = {}, pb = {};              // weights of even and odd halves
+#pragma unroll
+  for (int u = 0; u < 2; ++u) sa[u] = sb[u] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+  // Operand reads.  K (MFMA i of a half: subtile i % 2, k-step i / 2): keys 16 (i % 2) + col, dims 32 (i / 2) + 8 g ..+7.
+  // V (transpose load, see read_vt16): dims 16 dt ..+15 of the 32 keys of half h.
+  lds_char* const lb = (lds_char*)lds;
+  lds_char* const k_row = lb + (col >> 3) * (kR * 1024) + (col & 7) * 128;
+  lds_char* k_at[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) k_at[c] = k_row + ((4 * c + g) ^ spread(col)) * 16;
+  auto read_k = [&](int i, int at) __attribute__((always_inline)) {
+    return *(lds_u32x4*)(k_at[(i >> 1) & 1] + at + (i & 1) * kKeyGroup + (i >> 2) * 1024);
+  };
+  const int vj = lane & 15, vk = 4 * g + (vj >> 2);
+  lds_char* v_at[4];  // [dt & 3]
+#pragma unroll
+  for (int o = 0; o < 4; ++o)
+    v_at[o] = lb + kVBuf + (vk >> 3) * (kR * 1024) + (vk & 7) * 128 + ((2 * o + ((vj >> 1) & 1)) ^ spread(vk)) * 16 + (vj & 1) * 8;
+  auto read_v = [&](int dt, int h, int at) __attribute__((always_inline)) {
+    lds_char* const a = v_at[dt & 3] + at + 2 * h * kKeyGroup + (dt >> 2) * 1024;
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)a);
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(a + kKeyGroup));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   };
 
-  // Pipeline as in tile_body.h with one register set: in step t every wave computes on LDS buffer t % 2, copies
-  // tile t + 1 from its registers into the other buffer, reloads the registers with tile t + 2; one barrier ends
-  // the step.  Fetches are unconditional: tiles past the item's end re-read its last block and are never staged.
-  constexpr int kBuf = tile16_buf_elems<D>();
-  Staging16<D> st;
-  int ids[4];
-  tile_ids(0, ids);
-  fetch_tile16<D>(st, pool, ids, kvh, Hk, tid);
-  stage_tile16<D>(st, lds, lds + kTileK * G::kKStride, tid, it.k_end - it.k_begin);
-  tile_ids(1, ids);
-  fetch_tile16<D>(st, pool, ids, kvh, Hk, tid);
-  tile_ids(2, ids);
-  __syncthreads();
-  // Waves w and w + 4 share a SIMD: one does its arithmetic first and its copy after, the other the reverse.
-  const bool copy_first = (w & 4) != 0;
-  for (int t = 0; t < n_tiles; ++t) {
-    const int kt = it.k_begin + t * kTileK;
-    const uint16_t* ks = lds + (t & 1) * kBuf;
-    const uint16_t* vs = ks + kTileK * G::kKStride;
-    uint16_t* nks = lds + ((t + 1) & 1) * kBuf;
-    auto copy = [&]() {
-      if (t + 1 < n_tiles) stage_tile16<D>(st, nks, nks + kTileK * G::kKStride, tid, it.k_end - (kt + kTileK));
+  const int n_half = wave_pos_hi < it.k_begin ? 0 : min(2 * n_tiles, (wave_pos_hi - it.k_begin) / 32 + 1);  // halves this wave sees
+  u32x4 kop[kQ];    // K operands; the first four are read at the end of the stage before
+  bf16x8 vop[kP];   // V operands
+  auto must_move = [&]() { return __builtin_amdgcn_ballot_w64(top * sc > m + kLazyLog2) != 0; };
+  auto move = [&]() __attribute__((always_inline)) {  // the factor of what has the reference before
+    float t = __builtin_fmaxf(top, tile32::from_lane(top, here() ^ 16));
+    t = __builtin_fmaxf(t, tile32::from_lane(t, here() ^ 32));
+    const float cand = __builtin_fmaxf(m, t * sc);
+    const bool grew = cand > m + kLazyLog2;  // the same in the four lanes of a column
+    const float alpha = grew ? __builtin_amdgcn_exp2f(m - cand) : 1.0f;
+    m = grew ? cand : m;
+    return alpha;
+  };
+  auto rescale = [&](float alpha) __attribute__((always_inline)) {
+    tile32::acc_settle<128>();
+    unroll<D / 16>([&](auto ci) __attribute__((always_inline)) {
+      constexpr int c = 4 * decltype(ci)::value;
+      float x[4];
+      unroll<4>([&](auto e) __attribute__((always_inline)) { x[decltype(e)::value] = tile32::acc_read<c + decltype(e)::value>(); });
+      unroll<4>([&](auto e) __attribute__((always_inline)) { tile32::acc_write<c + decltype(e)::value>(__builtin_bit_cast(uint32_t, x[decltype(e)::value] * alpha)); });
+    });
+    l *= alpha;
+    tile32::acc_write<kAccL>(__builtin_bit_cast(uint32_t, tile32::acc_read<kAccL>() * alpha));
+    tile32::acc_settle<128>();
+  };
+  auto sum_up = [&]() __attribute__((always_inline)) {  // a step's sums join the normaliser
+    tile32::acc_settle<128>();
+    l += tile32::acc_read<kAccL>();
+    tile32::acc_write<kAccL>(0u);  // the next normaliser() is a barrier away
+  };
+  auto next_ids = [&](int u) __attribute__((always_inline)) {
+    id_u = id_1;
+    id_1 = id_2;
+    id_2 = block_id(u + 3);
+  };
+  auto hide = [&](f32x4 (&s)[2], int k0) __attribute__((always_inline)) {  // scores of keys past the lane's row; returns the largest left
+    const int ln = here();
+    const int room = pos_of(ln) - k0 - 4 * (ln >> 4);
+    asm volatile("" ::: "memory");  // keeps the caller's condition a branch instead of always-on selects
+    float t = -__builtin_inff();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      s[i / 4][i % 4] = 16 * (i / 4) + (i % 4) > room ? -__builtin_inff() : s[i / 4][i % 4];
+      t = __builtin_fmaxf(t, s[i / 4][i % 4]);
+    }
+    return t;
+  };
+  auto largest = [&](const f32x4 (&s)[2]) __attribute__((always_inline)) {
+    float t = -__builtin_inff();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) t = __builtin_fmaxf(t, s[i / 4][i % 4]);
+    return t;
+  };
+  auto serial_step = [&](int u) __attribute__((always_inline)) {
+    const int par = (u & 1) * kTileBytes, other = par ^ kTileBytes;
+    const int kt = it.k_begin + u * kTileK;
+    const int n_valid = it.k_end - (kt - kTileK);
+    if (u >= n_tiles - 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no copy follows V of tile u - 1
+    if (n_valid < kTileK) {  // dead slots of that tile: zero (0 * NaN would poison the product)
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const int at = here();
+      if (8 * w + (at >> 3) >= n_valid) {
+#pragma unroll
+        for (int j = 0; j < kR; ++j)
+          *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(my_lds + (uint32_t)(kVBuf + other + 1024 * j) + 16 * at) = (u32x4){0u, 0u, 0u, 0u};
+      }
+    }
+    barrier<kR>();
+    const int vt = n_tiles == 2 ? u + 1 : u;  // (no third tile needs the wait for V of the second to be by count)
+    if (vt > 0 && vt < n_tiles) copy_tile(vt == u ? id_u : id_1, vplane, kVBuf + (vt & 1) * kTileBytes);
+    if (u > 0 && 2 * u - 2 < n_half) {
+      unroll<kP>([&](auto dt) __attribute__((always_inline)) { mfma_pv<decltype(dt)::value>(read_v(decltype(dt)::value, 0, other), pa); });
+      normaliser<false>(pa);
+      if (kt - 1 > wave_pos_lo) top = hide(sb, kt - 32);
+      if (must_move()) rescale(move());
+      unroll<12>([&](auto k) __attribute__((always_inline)) { weight_op<decltype(k)::value>(sb, pb, -m, sc); });
+      asm volatile("s_nop 3" : "+v"(pb));
+      unroll<kP>([&](auto dt) __attribute__((always_inline)) { mfma_pv<decltype(dt)::value>(read_v(decltype(dt)::value, 1, other), pb); });
+      normaliser<false>(pb);
+      sum_up();
+    }
+    if (u == n_tiles) return;
+    if (2 * u < n_half) {
+      unroll<kQ>([&](auto ii) __attribute__((always_inline)) {
+        constexpr int i = decltype(ii)::value;
+        mfma_qk<i / 2>(sa[i % 2], read_k(i, par));
+        mfma_qk<i / 2>(sb[i % 2], read_k(i, par + 2 * kKeyGroup));
+      });
+      asm volatile("s_nop 15" : "+v"(sa[0]), "+v"(sa[1]), "+v"(sb[0]), "+v"(sb[1]));
+      float first;
+      if (kt + kTileK - 1 > wave_pos_lo) {
+        first = hide(sa, kt);
+        top = hide(sb, kt + 32);
+      } else {
+        first = largest(sa);
+        top = largest(sb);
+      }
+      // Lazy reference, as in tile32_body.h; here from the largest of 64 scores.
+      const float second = top;
+      top = __builtin_fmaxf(top, first);
+      if (must_move()) {
+        const float alpha = move();
+        if (u > 0) rescale(alpha);  // (before, there is nothing to rescale)
+      }
+      top = second;
+      unroll<12>([&](auto k) __attribute__((always_inline)) { weight_op<decltype(k)::value>(sa, pa, -m, sc); });
+      asm volatile("s_nop 3" : "+v"(pa));
+    }
+    barrier<kR>();
+    if (u + 2 < n_tiles) copy_tile(id_2, 0, par);
+    next_ids(u);
+  };
+
+  // Operands are read four MFMAs ahead (an MFMA is half as long as the 32-row shape's).
+  auto fast_stage = [&](auto half_tag, auto par_tag, int u, f32x4 (&scur)[2], f32x4 (&snext)[2], bf16x8& pcur, bf16x8& pprev) __attribute__((always_inline)) {
+    constexpr int kHalf = decltype(half_tag)::value, kPar = decltype(par_tag)::value;
+    constexpr int kAt = kPar * kTileBytes + kHalf * 2 * kKeyGroup;
+    constexpr int kNextAt = kHalf == 0 ? kAt + 2 * kKeyGroup : (kPar ^ 1) * kTileBytes;
+    constexpr int kVAt = (kPar ^ 1) * kTileBytes;
+    const bool moved = must_move();
+    float alpha = 1.f;
+    if (__builtin_expect(moved, 0)) alpha = move();
+    const float negm = -m;
+    auto weights = [&](auto slot) __attribute__((always_inline)) {  // this slot's share of the 12 operations
+      constexpr int a = decltype(slot)::value * 12 / kS, b = (decltype(slot)::value + 1) * 12 / kS;
+      unroll<b - a>([&](auto k) __attribute__((always_inline)) { weight_op<a + decltype(k)::value>(scur, pcur, negm, sc); });
     };
-    if (copy_first) copy();
-    if (kt <= wave_pos_hi)  // otherwise every key of the tile is in this wave's future
-      wave_step16<D, kPin>(ks, vs, qreg, acc_o, m, l, kt, pos, lane, sc, kt + kTileK - 1 > wave_pos_lo);
-    if (!copy_first) copy();
-    fetch_tile16<D>(st, pool, ids, kvh, Hk, tid);
-    tile_ids(t + 3, ids);
-    __syncthreads();
+    auto operand_v = [&](auto vi) __attribute__((always_inline)) { vop[decltype(vi)::value] = read_v(decltype(vi)::value, kHalf, kVAt); };
+    pin();
+    unroll<kQ>([&](auto ii) __attribute__((always_inline)) {
+      constexpr int i = decltype(ii)::value;
+      if constexpr (i == kQ - 4) {
+        barrier<kR>();
+        pin();
+      }
+      if constexpr (i % 2 == 0) asm volatile("" ::"v"(kop[i]), "v"(kop[i + 1]));  // one wait for the two
+      mfma_qk<i / 2>(snext[i % 2], kop[i]);
+      if constexpr (i % 2 == 0 && i + 4 < kQ) {
+        kop[i + 4] = read_k(i + 4, kAt);
+        kop[i + 5] = read_k(i + 5, kAt);
+      }
+      if constexpr (i >= kQ - 4) operand_v(std::integral_constant<int, i - (kQ - 4)>{});
+      if constexpr (kHalf == 0 && i == kQ - 2) l += tile32::acc_read<kAccL>();  // the step before
+      weights(ii);
+      pin();
+    });
+    unroll<kP>([&](auto ii) __attribute__((always_inline)) {
+      constexpr int i = decltype(ii)::value;
+      if constexpr (i % 2 == 0) asm volatile("" ::"v"(vop[i]), "v"(vop[i + 1]));
+      mfma_pv<i>(vop[i], pprev);
+      if constexpr (i == kP - 1) normaliser<kHalf == 0>(pprev);
+      if constexpr (i % 2 == 0 && i + 4 < kP) {
+        operand_v(std::integral_constant<int, i + 4>{});
+        operand_v(std::integral_constant<int, i + 5>{});
+      }
+      if constexpr (i == 0 && kHalf == 0) copy_tile(id_u, vplane, kVBuf + kPar * kTileBytes);
+      if constexpr (i == 0 && kHalf == 1) {
+        copy_tile(id_2, 0, kPar * kTileBytes);
+        next_ids(u);
+      }
+      if constexpr (i >= kP - 4) kop[i - (kP - 4)] = read_k(i - (kP - 4), kNextAt);
+      weights(std::integral_constant<int, kQ + i>{});
+      constexpr int m0 = kP / 2;  // the largest score of half h + 1, four pairs over the last slots
+      if constexpr (i >= m0) {
+        if constexpr (i == m0) top = -__builtin_inff();
+#pragma unroll
+        for (int k = (i - m0) * 4 / (kP - m0); k < (i - m0 + 1) * 4 / (kP - m0); ++k) top = __builtin_fmaxf(__builtin_fmaxf(top, snext[k / 2][2 * (k % 2)]), snext[k / 2][2 * (k % 2) + 1]);
+      }
+      pin();
+    });
+    asm volatile("" : "+v"(pcur), "+v"(top));  // are worked out here, not in the next stage, where they are used
+    if (__builtin_expect(moved, 0)) rescale(alpha);  // the products so far have the old reference, those of half h the new one
+  };
+
+  // Steps 1 .. fast_end of this wave have three full parts in both stages, nothing to hide and a whole tile of V to publish.
+  const int fast_end = min(min((n_half - 2) >> 1, (wave_pos_lo - it.k_begin - 31) >> 6), (it.k_end - it.k_begin) >> 6);
+  constexpr std::integral_constant<int, 0> A{}, even{};
+  constexpr std::integral_constant<int, 1> B{}, odd{};
+  for (int u = 0; u <= n_tiles;) {
+    serial_step(u);
+    ++u;
+    if (u + 1 <= fast_end) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) kop[i] = read_k(i, kTileBytes);
+      do {
+        fast_stage(A, odd, u, sb, sa, pb, pa);
+        fast_stage(B, odd, u, sa, sb, pa, pb);
+        fast_stage(A, even, u + 1, sb, sa, pb, pa);
+        fast_stage(B, even, u + 1, sa, sb, pa, pb);
+        u += 2;
+      } while (u + 1 <= fast_end);
+    }
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // copies still in flight write LDS that the next item uses
 
   // ---- epilogue: lane holds O^T[d][col] for d = 16 dt + 4 g + i
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
-  if (r < n_rows_t) {
-    const int qr = r >> gs;
-    const int head = head0 + (r & ((1 << gs) - 1));
+  tile32::acc_settle<128>();
+  const float lsum = l + tile32::acc_read<kAccL>();
+  const int lane_e = here();
+  const int r_e = kRows * w + (lane_e & 15), d0 = 4 * (lane_e >> 4);
+  if (r_e < n_rows_t) {
+    const int qr = r_e >> gs;
+    const int head = head0 + (r_e & ((1 << gs) - 1));
     if (it.slot0 < 0) {
-      const float inv = 1.0f / l;
+      const float inv = 1.0f / lsum;
       uint16_t* op = p.out + ((int64_t)(it.qrow0 + qr) * H + head) * D;
-#pragma unroll
-      for (int dt = 0; dt < G::kDTiles; ++dt) {
+      unroll<kP>([&](auto ci) __attribute__((always_inline)) {
+        constexpr int c = decltype(ci)::value;
         bf16x4 o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (__bf16)(acc_o[dt][e] * inv);  // round to nearest even
-        *(bf16x4*)(op + 16 * dt + 4 * g) = o;
-      }
+        unroll<4>([&](auto e) __attribute__((always_inline)) { o[decltype(e)::value] = (__bf16)(tile32::acc_read<4 * c + decltype(e)::value>() * inv); });  // round to nearest even
+        *(bf16x4*)(op + 16 * c + d0) = o;
+      });
     } else {
       const int64_t ps = (int64_t)(it.slot0 + qr * it.nparts) * H + head;
       float* op = p.part_o + ps * D;
-#pragma unroll
-      for (int dt = 0; dt < G::kDTiles; ++dt) *(f32x4*)(op + 16 * dt + 4 * g) = acc_o[dt];
-      if (g == 0) {
+      unroll<kP>([&](auto ci) __attribute__((always_inline)) {
+        constexpr int c = decltype(ci)::value;
+        f32x4 o;
+        unroll<4>([&](auto e) __attribute__((always_inline)) { o[decltype(e)::value] = tile32::acc_read<4 * c + decltype(e)::value>(); });
+        *(f32x4*)(op + 16 * c + d0) = o;
+      });
+      if (d0 == 0) {
         p.part_ml[ps * 2] = m;
-        p.part_ml[ps * 2 + 1] = l;
+        p.part_ml[ps * 2 + 1] = lsum;
       }
     }
   }

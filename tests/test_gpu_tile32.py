@@ -1,4 +1,4 @@
-"""The 32-row tile body (head_dim 64 and 128): its first, last and middle tiles are different code, the reference of the
+"""The tile bodies (32 rows per wave, head_dim 256: 16): their first, last and middle tiles are different code, the reference of the
 softmax moves in each of them, and dead slots of the last tile are zeroed in LDS.  Against the fp64 oracle."""
 import numpy as np
 import pytest
@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 PREFIXES = (0, 1, 31, 63, 64, 65, 127, 128, 190, 192, 255, 256, 257, 320, 383, 449, 513, 640, 705)
 
 
-@pytest.mark.parametrize("H,Hkv,D,rows", [(2, 2, 64, 2), (2, 2, 128, 67), (16, 2, 64, 33), (8, 1, 128, 40), (9, 9, 128, 5), (1, 1, 64, 300)])
+@pytest.mark.parametrize("H,Hkv,D,rows", [(2, 2, 64, 2), (2, 2, 128, 67), (16, 2, 64, 33), (8, 1, 128, 40), (9, 9, 128, 5), (1, 1, 64, 300),
+                                           (2, 2, 256, 2), (3, 3, 256, 67), (8, 1, 256, 40), (1, 1, 256, 150)])
 @pytest.mark.parametrize("jumps", [(), (40, 97, 129, 200, 290, 350, 410, 480, 600)])
 def test_tiles_of_every_number_and_moving_references(H, Hkv, D, rows, jumps):
     """jumps: from each of these keys on the scores grow by some 12 in log2 units, more than the slack of 8, so that the

@@ -1,4 +1,4 @@
-"""What the compiler does not check for the 32-row tile body, whose accumulators are accumulation registers named by number and
+"""What the compiler does not check for the tile bodies, whose accumulators are accumulation registers named by number and
 whose score MFMAs are assembly: read from the kernels' assembly listing (hipcc cross-compiles; no GPU needed)."""
 import os
 import re
@@ -35,7 +35,7 @@ def listing(tmp_path_factory):
 
 
 @pytest.mark.parametrize("kernel", ["tile_persist_kernelILi{}ELb0E", "tile_persist_kernelILi{}ELb1E", "tile_attn_kernelILi{}E"])
-@pytest.mark.parametrize("D,own", [(64, 56), (128, 104)])
+@pytest.mark.parametrize("D,own", [(64, 56), (128, 104), (256, 104)])
 def test_accumulation_registers_and_wait_states_of_the_tile_body(listing, kernel, D, own):
     start = re.search(r"^\S*%s\S*:" % kernel.format(D), listing, re.M).start()
     text = listing[start:listing.index(".section", start)]
