@@ -34,6 +34,7 @@ constexpr int few_lds_bytes() {
 template <int D>
 __device__ __forceinline__ void few_body(const AttnParams& p, const FewItem& f, int pair, uint16_t* lds) {
   using G = tile16::G16<D>;
+  const int32_t offs = first_offsets(p);
   const int H = p.num_heads, Hk = p.num_kv_heads;
   int tid0 = threadIdx.x;
   asm volatile("" : "+v"(tid0));  // values derived from it are not kept in registers across the tile items before
@@ -57,7 +58,7 @@ __device__ __forceinline__ void few_body(const AttnParams& p, const FewItem& f, 
   uint16_t* vs = ks + kTileK * G::kKStride;
   {
     typedef __attribute__((address_space(4))) const int32_t const_i32;
-    const_i32* bt = (const_i32*)(p.bt_flat + p.bt_off[rows[0].seq]);
+    const_i32* bt = (const_i32*)(p.bt_flat + table_start(p, offs, rows[0].seq));
     constexpr int kTileBytes = kBlockSize * D * 2;
     constexpr int kLoads = kTileK * G::kChunks / 256;
     const char* base = (const char*)p.pool + (int64_t)kvh * kTileBytes;

@@ -99,6 +99,21 @@ struct AttnParams {
   int32_t* counters;       // 16 work-queue counters, zero when the kernel starts
 };
 
+// Where a sequence's ids begin, for the tile kernels' work items.  The offsets of the first 64 sequences are loaded one per lane (the
+// section is a multiple of 256 bytes) beside the work item instead of after it: item, offset, ids and keys are a chain of load
+// latencies, most of what a call on a few tiles takes (2 rows and 2 chunks of 32, 4 heads: 12.79 -> 12.66 us).  In
+// the row kernels it costs more than it gives (one row of 3000 keys, four layers: 70.6 -> 70.9 us).
+__device__ __forceinline__ int32_t first_offsets(const AttnParams& p) {
+  uint32_t lane = threadIdx.x & 63u;
+  asm volatile("" : "+v"(lane));  // worked out here: kept across the items of a persistent kernel it would take a register
+  return p.bt_off[lane];
+}
+__device__ __forceinline__ int32_t table_start(const AttnParams& p, int32_t first, int seq) {
+  typedef __attribute__((address_space(4))) const int32_t const_i32;
+  if (seq < 64) return __builtin_amdgcn_readlane(first, seq);
+  return ((const_i32*)p.bt_off)[seq];
+}
+
 // Work-queue counters of the persistent kernels (16 ints at the head of the descriptor image):
 //   [0..7] tile queue of each XCD, [9] shared tile queue, [8] row queue, [10] queue of the slim group kernel,
 //   [12] / [13] / [14] workgroups of the row / tile / slim group kernel that have left.

@@ -125,6 +125,7 @@ __device__ __forceinline__ void weight_op(f32x4 (&s)[2], bf16x8& pw, float negm,
 // One TileItem x one group of (1 << p.tile_g_shift) query heads that share a K/V head, executed by a workgroup of kWaves
 // waves (see tile32_body() for the row mapping and for the steps, which are the same).  lds: kLdsBytes, 1 KiB aligned.
 __device__ __forceinline__ void tile16_body(const AttnParams& p, const TileItem& it, int th, uint16_t* lds) {
+  const int32_t offs = first_offsets(p);
   constexpr int D = kDim, kS = kQ + kP, kR = kRegions;
   typedef __attribute__((address_space(3))) const char lds_char;
   typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
@@ -146,7 +147,7 @@ __device__ __forceinline__ void tile16_body(const AttnParams& p, const TileItem&
 
   // ---- keys and values: this wave copies keys 8 w .. 8 w + 7 of every tile, half of block w / 2 of the tile's four
   typedef __attribute__((address_space(4))) const int32_t const_i32;
-  const_i32* bt = (const_i32*)(p.bt_flat + p.bt_off[it.seq]);
+  const_i32* bt = (const_i32*)(p.bt_flat + table_start(p, offs, it.seq));
   const int last_blk = (it.k_end - 1) / kBlockSize;   // last table entry this item may touch
   const int n_tiles = (it.k_end - it.k_begin + kTileK - 1) / kTileK;
   constexpr int kBlockBytes = kBlockSize * D * 2;     // one (K or V, head) tile of a block
@@ -289,7 +290,7 @@ __device__ __forceinline__ void tile16_body(const AttnParams& p, const TileItem&
     }
     barrier<kR>();
     const int vt = n_tiles == 2 ? u + 1 : u;  // (no third tile needs the wait for V of the second to be by count)
-    if (vt > 0 && vt < n_tiles) copy_tile(vt == u ? id_u : id_1, vplane, kVBuf + (vt & 1) * kTileBytes);
+    if (vt > 0 && vt < n_tiles) copy_tile(vt == u ? id_u : id_1, vplane, __builtin_amdgcn_readfirstlane(kVBuf + (vt & 1) * kTileBytes));
     if (u > 0 && 2 * u - 2 < n_half) {
       unroll<kP>([&](auto dt) __attribute__((always_inline)) { mfma_pv<decltype(dt)::value>(read_v(decltype(dt)::value, 0, other), pa); });
       normaliser<false>(pa);
@@ -328,6 +329,9 @@ __device__ __forceinline__ void tile16_body(const AttnParams& p, const TileItem&
       unroll<12>([&](auto k) __attribute__((always_inline)) { weight_op<decltype(k)::value>(sa, pa, -m, sc); });
       asm volatile("s_nop 3" : "+v"(pa));
     }
+    // No tile to publish, and no copy into the buffer that this one leaves.  (From three tiles on the last step is some waves' fast one,
+    // which has the barrier; the waves of a workgroup must meet at the same ones.)
+    if (n_tiles <= 2 && u + 1 == n_tiles) return;
     barrier<kR>();
     if (u + 2 < n_tiles) copy_tile(id_2, 0, par);
     next_ids(u);

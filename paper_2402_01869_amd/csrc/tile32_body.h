@@ -206,6 +206,7 @@ template <int D>
 __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem& it, int th, uint16_t* lds) {
   using G = G32<D>;
   constexpr int kQ = G::kQSteps, kP = 2 * G::kDTiles, kS = kQ + kP, kR = G::kRegions;
+  const int32_t offs = first_offsets(p);
   typedef __attribute__((address_space(3))) const char lds_char;
   typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
   typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
@@ -230,7 +231,7 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
 
   // ---- keys and values: this wave copies keys 8 w .. 8 w + 7 of every tile, half of block w / 2 of the tile's four
   typedef __attribute__((address_space(4))) const int32_t const_i32;
-  const_i32* bt = (const_i32*)(p.bt_flat + p.bt_off[it.seq]);
+  const_i32* bt = (const_i32*)(p.bt_flat + table_start(p, offs, it.seq));
   const int last_blk = (it.k_end - 1) / kBlockSize;   // last table entry this item may touch
   const int n_tiles = (it.k_end - it.k_begin + kTileK - 1) / kTileK;
   constexpr int kBlockBytes = kBlockSize * D * 2;     // one (K or V, head) tile of a block
@@ -389,7 +390,7 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
     }
     barrier<kR>();
     const int vt = n_tiles == 2 ? u + 1 : u;  // (no third tile needs the wait for V of the second to be by count)
-    if (vt > 0 && vt < n_tiles) copy_tile(vt == u ? id_u : id_1, vplane, kVBuf + (vt & 1) * G::kTileBytes);
+    if (vt > 0 && vt < n_tiles) copy_tile(vt == u ? id_u : id_1, vplane, __builtin_amdgcn_readfirstlane(kVBuf + (vt & 1) * G::kTileBytes));
     if (u > 0 && 2 * u - 2 < n_half) {
       unroll<kP / 2>([&](auto dt) __attribute__((always_inline)) { mfma_pv<D, decltype(dt)::value>(read_v(decltype(dt)::value, 0, other), pa[0]); });
       unroll<kP / 2>([&](auto dt) __attribute__((always_inline)) { mfma_pv<D, decltype(dt)::value>(read_v(decltype(dt)::value, 1, other), pa[1]); });
@@ -435,6 +436,9 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
       unroll<24>([&](auto k) __attribute__((always_inline)) { weight_op<decltype(k)::value>(sa, pa, -m, sc); });
       asm volatile("s_nop 3" : "+v"(pa[0]), "+v"(pa[1]));
     }
+    // No tile to publish, and no copy into the buffer that this one leaves.  (From three tiles on the last step is some waves' fast one,
+    // which has the barrier; the waves of a workgroup must meet at the same ones.)
+    if (n_tiles <= 2 && u + 1 == n_tiles) return;
     barrier<kR>();
     if (u + 2 < n_tiles) copy_tile(id_2, 0, par);
     next_ids(u);
