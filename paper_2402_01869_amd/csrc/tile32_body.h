@@ -374,6 +374,19 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
     for (int i = 0; i < 16; ++i) t = __builtin_fmaxf(t, s[i]);
     return t;
   };
+  auto products = [&](auto half_tag, const bf16x8 (&pw)[2], int at) __attribute__((always_inline)) {  // operands four MFMAs ahead
+    constexpr int kStep = 2 * decltype(half_tag)::value;
+    bf16x8 v[kP];
+    auto operand = [&](auto vi) __attribute__((always_inline)) { v[decltype(vi)::value] = read_v(decltype(vi)::value % G::kDTiles, kStep + decltype(vi)::value / G::kDTiles, at); };
+    unroll<4>(operand);
+    pin();
+    unroll<kP>([&](auto ii) __attribute__((always_inline)) {
+      constexpr int i = decltype(ii)::value;
+      mfma_pv<D, i % G::kDTiles>(v[i], pw[i / G::kDTiles]);
+      if constexpr (i + 4 < kP) operand(std::integral_constant<int, i + 4>{});
+      pin();
+    });
+  };
   auto serial_step = [&](int u) __attribute__((always_inline)) {
     const int par = (u & 1) * G::kTileBytes, other = par ^ G::kTileBytes;
     const int kt = it.k_begin + u * kTileK;
@@ -392,25 +405,35 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
     const int vt = n_tiles == 2 ? u + 1 : u;  // (no third tile needs the wait for V of the second to be by count)
     if (vt > 0 && vt < n_tiles) copy_tile(vt == u ? id_u : id_1, vplane, __builtin_amdgcn_readfirstlane(kVBuf + (vt & 1) * G::kTileBytes));
     if (u > 0 && 2 * u - 2 < n_half) {
-      unroll<kP / 2>([&](auto dt) __attribute__((always_inline)) { mfma_pv<D, decltype(dt)::value>(read_v(decltype(dt)::value, 0, other), pa[0]); });
-      unroll<kP / 2>([&](auto dt) __attribute__((always_inline)) { mfma_pv<D, decltype(dt)::value>(read_v(decltype(dt)::value, 1, other), pa[1]); });
+      products(std::integral_constant<int, 0>{}, pa, other);
       normaliser<D, false>(pa[0]);
       normaliser<D, false>(pa[1]);
       if (kt - 1 > wave_pos_lo) top = hide(sb, kt - 32);
       if (must_move()) rescale(move());
       unroll<24>([&](auto k) __attribute__((always_inline)) { weight_op<decltype(k)::value>(sb, pb, -m, sc); });
       asm volatile("s_nop 3" : "+v"(pb[0]), "+v"(pb[1]));
-      unroll<kP / 2>([&](auto dt) __attribute__((always_inline)) { mfma_pv<D, decltype(dt)::value>(read_v(decltype(dt)::value, 2, other), pb[0]); });
-      unroll<kP / 2>([&](auto dt) __attribute__((always_inline)) { mfma_pv<D, decltype(dt)::value>(read_v(decltype(dt)::value, 3, other), pb[1]); });
+      products(std::integral_constant<int, 1>{}, pb, other);
       normaliser<D, false>(pb[0]);
       normaliser<D, false>(pb[1]);
       sum_up();
     }
     if (u == n_tiles) return;
     if (2 * u < n_half) {
-      unroll<kQ>([&](auto s) __attribute__((always_inline)) {
-        mfma_qk<D, decltype(s)::value>(sa, read_k(decltype(s)::value, par));
-        mfma_qk<D, decltype(s)::value>(sb, read_k(decltype(s)::value, par + 2 * G::kKeyGroup));
+      u32x4 ka[kQ], kb[kQ];  // operands three k-steps ahead: left to itself the compiler reads each right before its use
+      unroll<3>([&](auto si) __attribute__((always_inline)) {
+        ka[decltype(si)::value] = read_k(decltype(si)::value, par);
+        kb[decltype(si)::value] = read_k(decltype(si)::value, par + 2 * G::kKeyGroup);
+      });
+      pin();
+      unroll<kQ>([&](auto si) __attribute__((always_inline)) {
+        constexpr int s = decltype(si)::value;
+        mfma_qk<D, s>(sa, ka[s]);
+        mfma_qk<D, s>(sb, kb[s]);
+        if constexpr (s + 3 < kQ) {
+          ka[s + 3] = read_k(s + 3, par);
+          kb[s + 3] = read_k(s + 3, par + 2 * G::kKeyGroup);
+        }
+        pin();
       });
       asm volatile("s_nop 15\n\ts_nop 3" : "+v"(sa), "+v"(sb));
       float first;
