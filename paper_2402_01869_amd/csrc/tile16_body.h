@@ -274,6 +274,19 @@ __device__ __forceinline__ void tile16_body(const AttnParams& p, const TileItem&
     for (int i = 0; i < 8; ++i) t = __builtin_fmaxf(t, s[i / 4][i % 4]);
     return t;
   };
+  auto products = [&](auto half_tag, const bf16x8& pw, int at) __attribute__((always_inline)) {  // operands four MFMAs ahead
+    constexpr int kHalf = decltype(half_tag)::value;
+    bf16x8 v[kP];
+    auto operand = [&](auto vi) __attribute__((always_inline)) { v[decltype(vi)::value] = read_v(decltype(vi)::value, kHalf, at); };
+    unroll<4>(operand);
+    pin();
+    unroll<kP>([&](auto ii) __attribute__((always_inline)) {
+      constexpr int i = decltype(ii)::value;
+      mfma_pv<i>(v[i], pw);
+      if constexpr (i + 4 < kP) operand(std::integral_constant<int, i + 4>{});
+      pin();
+    });
+  };
   auto serial_step = [&](int u) __attribute__((always_inline)) {
     const int par = (u & 1) * kTileBytes, other = par ^ kTileBytes;
     const int kt = it.k_begin + u * kTileK;
@@ -292,22 +305,33 @@ __device__ __forceinline__ void tile16_body(const AttnParams& p, const TileItem&
     const int vt = n_tiles == 2 ? u + 1 : u;  // (no third tile needs the wait for V of the second to be by count)
     if (vt > 0 && vt < n_tiles) copy_tile(vt == u ? id_u : id_1, vplane, __builtin_amdgcn_readfirstlane(kVBuf + (vt & 1) * kTileBytes));
     if (u > 0 && 2 * u - 2 < n_half) {
-      unroll<kP>([&](auto dt) __attribute__((always_inline)) { mfma_pv<decltype(dt)::value>(read_v(decltype(dt)::value, 0, other), pa); });
+      products(std::integral_constant<int, 0>{}, pa, other);
       normaliser<false>(pa);
       if (kt - 1 > wave_pos_lo) top = hide(sb, kt - 32);
       if (must_move()) rescale(move());
       unroll<12>([&](auto k) __attribute__((always_inline)) { weight_op<decltype(k)::value>(sb, pb, -m, sc); });
       asm volatile("s_nop 3" : "+v"(pb));
-      unroll<kP>([&](auto dt) __attribute__((always_inline)) { mfma_pv<decltype(dt)::value>(read_v(decltype(dt)::value, 1, other), pb); });
+      products(std::integral_constant<int, 1>{}, pb, other);
       normaliser<false>(pb);
       sum_up();
     }
     if (u == n_tiles) return;
     if (2 * u < n_half) {
+      u32x4 ka[kQ], kb[kQ];
+      unroll<3>([&](auto ii) __attribute__((always_inline)) {
+        ka[decltype(ii)::value] = read_k(decltype(ii)::value, par);
+        kb[decltype(ii)::value] = read_k(decltype(ii)::value, par + 2 * kKeyGroup);
+      });
+      pin();
       unroll<kQ>([&](auto ii) __attribute__((always_inline)) {
         constexpr int i = decltype(ii)::value;
-        mfma_qk<i / 2>(sa[i % 2], read_k(i, par));
-        mfma_qk<i / 2>(sb[i % 2], read_k(i, par + 2 * kKeyGroup));
+        mfma_qk<i / 2>(sa[i % 2], ka[i]);
+        mfma_qk<i / 2>(sb[i % 2], kb[i]);
+        if constexpr (i + 3 < kQ) {
+          ka[i + 3] = read_k(i + 3, par);
+          kb[i + 3] = read_k(i + 3, par + 2 * kKeyGroup);
+        }
+        pin();
       });
       asm volatile("s_nop 15" : "+v"(sa[0]), "+v"(sa[1]), "+v"(sb[0]), "+v"(sb[1]));
       float first;
