@@ -118,8 +118,11 @@ __device__ __forceinline__ void mfma_pv(const bf16x8 v, const bf16x8 p) {
 // 16x16x32 its four groups of 16 lanes are four groups of 8 keys, of which the even ones hold columns 0..15 and the odd ones
 // columns 16..31.  A row of the A operand that is 1 for the even (odd) groups and 0 for the others gives the sums of one half of
 // the columns: even result rows columns 0..15, odd rows columns 16..31, so every lane gets both in its first two results.
-// 16 cycles of the matrix pipe for 16 keys, and no vector instruction.  kFirst: of a step (64 keys), whose weights are summed by
-// themselves before they join the running total: that is then rounded once a step.
+// 0 times a weight of the other half is 0 because every weight is finite (see move()).
+// 16 cycles of the matrix pipe for 16 keys, and no vector instruction.  (Without zeros: the two operands of a half regrouped by columns with
+// v_permlane16_swap_b32, or the 4x4x4 shape, in which a lane gets the sum of its own weights, cost the grouped and the
+// long-context call 1 to 3 %.)  kFirst: of a step (64 keys), whose weights are summed by themselves before they join the running
+// total: that is then rounded once a step.
 template <int D, bool kFirst>
 __device__ __forceinline__ void normaliser(const bf16x8 p) {
   constexpr int L = acc_l<D>(), A = acc_ones<D>();
@@ -158,6 +161,7 @@ __device__ __forceinline__ float from_lane(float v, int lane) {
   return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(lane << 2, __builtin_bit_cast(int, v)));
 }
 __device__ __forceinline__ float other_half(float v) { return from_lane(v, here() ^ 32); }
+__device__ __forceinline__ float largest_of(float a, float b) { return __builtin_elementwise_maximum(a, b); }  // NaN if one of them is
 
 // Nothing of the compiler's own is in the accumulation registers from here on.
 template <int D>
@@ -320,12 +324,23 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
   const int n_half = wave_pos_hi < it.k_begin ? 0 : min(2 * n_tiles, (wave_pos_hi - it.k_begin) / 32 + 1);  // halves this wave sees
   u32x4 kop[kQ];    // K operands; the first two are read at the end of the stage before
   bf16x8 vop[kP];   // V operands
-  auto must_move = [&]() { return __builtin_amdgcn_ballot_w64(top * sc > m + kLazyLog2) != 0; };
-  auto move = [&]() __attribute__((always_inline)) {  // the factor of what has the reference before
-    const float cand = __builtin_fmaxf(m, __builtin_fmaxf(top, other_half(top)) * sc);
-    const bool grew = cand > m + kLazyLog2;  // the same in both lanes of a column
-    const float alpha = grew ? __builtin_amdgcn_exp2f(m - cand) : 1.0f;
+  auto must_move = [&]() { return __builtin_amdgcn_ballot_w64(!(top * sc <= m + kLazyLog2)) != 0; };
+  // The factor of what has the reference before; s: the scores that are weighed next.  A column whose largest score is NaN or
+  // overflows (a NaN or an infinity in its query row, or in a key that it sees) has no result: its factor is NaN, once, which its sums
+  // and its normaliser keep, and these scores become -inf.  So no weight is ever NaN or infinite, and none gets into
+  // another column's normaliser.
+  auto move = [&](f32x16& s) __attribute__((always_inline)) {
+    const float cand = largest_of(m, largest_of(top, other_half(top)) * sc);
+    const bool bad = !(cand < __builtin_inff());  // the same in both lanes of a column
+    const bool grew = cand > m + kLazyLog2 && !bad;
+    float alpha = grew ? __builtin_amdgcn_exp2f(m - cand) : 1.0f;
     m = grew ? cand : m;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) != 0, 0)) {
+      const float l0 = l[0], l1 = l[1], own = here() & 16 ? l1 : l0;
+      if (bad && own == own) alpha = __builtin_nanf("");
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] = bad ? -__builtin_inff() : s[i];
+    }
     return alpha;
   };
   auto rescale = [&](float alpha) __attribute__((always_inline)) {
@@ -364,14 +379,14 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       s[i] = 8 * (i / 4) + (i % 4) > room ? -__builtin_inff() : s[i];
-      t = __builtin_fmaxf(t, s[i]);
+      t = largest_of(t, s[i]);
     }
     return t;
   };
   auto largest = [&](const f32x16& s) __attribute__((always_inline)) {
     float t = -__builtin_inff();
 #pragma unroll
-    for (int i = 0; i < 16; ++i) t = __builtin_fmaxf(t, s[i]);
+    for (int i = 0; i < 16; ++i) t = largest_of(t, s[i]);
     return t;
   };
   auto products = [&](auto half_tag, const bf16x8 (&pw)[2], int at) __attribute__((always_inline)) {  // operands four MFMAs ahead
@@ -409,7 +424,7 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
       normaliser<D, false>(pa[0]);
       normaliser<D, false>(pa[1]);
       if (kt - 1 > wave_pos_lo) top = hide(sb, kt - 32);
-      if (must_move()) rescale(move());
+      if (must_move()) rescale(move(sb));
       unroll<24>([&](auto k) __attribute__((always_inline)) { weight_op<decltype(k)::value>(sb, pb, -m, sc); });
       asm volatile("s_nop 3" : "+v"(pb[0]), "+v"(pb[1]));
       products(std::integral_constant<int, 1>{}, pb, other);
@@ -450,10 +465,10 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
       // Here it is the largest of 64 scores: the weight of a row's largest score is then more often exactly 1, the one weight that
       // rounding does not touch (chunks of 300..1500 rows from position 0: relative error 1.908e-3, with 32 scores 1.923e-3).
       const float second = top;
-      top = __builtin_fmaxf(top, first);
+      top = largest_of(top, first);
       if (must_move()) {
-        const float alpha = move();
-        if (u > 0) rescale(alpha);  // (before, there is nothing to rescale)
+        const float alpha = move(sa);
+        if (u > 0 || __builtin_amdgcn_ballot_w64(alpha != alpha) != 0) rescale(alpha);  // (at first there is nothing to rescale)
       }
       top = second;
       unroll<24>([&](auto k) __attribute__((always_inline)) { weight_op<decltype(k)::value>(sa, pa, -m, sc); });
@@ -472,9 +487,12 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
     constexpr int kAt = kPar * G::kTileBytes + kHalf * 2 * G::kKeyGroup;
     constexpr int kNextAt = kHalf == 0 ? kAt + 2 * G::kKeyGroup : (kPar ^ 1) * G::kTileBytes;
     constexpr int kVAt = (kPar ^ 1) * G::kTileBytes, kVStep = 2 * kHalf;
-    const bool moved = must_move();
+    bool moved = must_move();
     float alpha = 1.f;
-    if (__builtin_expect(moved, 0)) alpha = move();
+    if (__builtin_expect(moved, 0)) {
+      alpha = move(scur);
+      moved = __builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0;
+    }
     const float negm = -m;
     auto weights = [&](auto slot) __attribute__((always_inline)) {  // this slot's share of the 24 operations
       constexpr int a = decltype(slot)::value * 24 / kS, b = (decltype(slot)::value + 1) * 24 / kS;
@@ -522,7 +540,7 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
       if constexpr (i >= m0) {
         if constexpr (i == m0) top = -__builtin_inff();
 #pragma unroll
-        for (int k = (i - m0) * 8 / (kP - m0); k < (i - m0 + 1) * 8 / (kP - m0); ++k) top = __builtin_fmaxf(__builtin_fmaxf(top, snext[2 * k]), snext[2 * k + 1]);
+        for (int k = (i - m0) * 8 / (kP - m0); k < (i - m0 + 1) * 8 / (kP - m0); ++k) top = largest_of(largest_of(top, snext[2 * k]), snext[2 * k + 1]);
       }
       pin();
     });
