@@ -145,6 +145,14 @@ __device__ __forceinline__ void tile16_body(const AttnParams& p, const TileItem&
   const int wave_pos_hi = it.pos0 + min((kRows * w + kRows - 1) >> gs, it.n_rows - 1);
   const float sc = p.scale_log2e;
 
+  // ---- this wave's Q^T, beside the block ids and before the first copy (see tile32_body.h)
+  const int r = row_of(lane);
+  const int head = head0 + (r & ((1 << gs) - 1));
+  const uint16_t* qp = p.q + ((int64_t)(it.qrow0 + (r >> gs)) * H + head) * D + 8 * g;
+  u32x4 q[D / 32];
+#pragma unroll
+  for (int t = 0; t < D / 32; ++t) q[t] = *(const u32x4*)(qp + 32 * t);
+
   // ---- keys and values: this wave copies keys 8 w .. 8 w + 7 of every tile, half of block w / 2 of the tile's four
   typedef __attribute__((address_space(4))) const int32_t const_i32;
   const_i32* bt = (const_i32*)(p.bt_flat + table_start(p, offs, it.seq));
@@ -167,18 +175,14 @@ __device__ __forceinline__ void tile16_body(const AttnParams& p, const TileItem&
     for (int j = 0; j < kR; ++j) copy_region(b + 128 * j, lane_off, my_lds + (uint32_t)(buf + 1024 * j));
   };
   int id_u = block_id(0), id_1 = block_id(1), id_2 = block_id(2);  // blocks of tiles u, u + 1, u + 2
+#pragma unroll
+  for (int s = 0; s < D / 32; ++s) asm volatile("" ::"v"(q[s]));  // waits
   copy_tile(id_u, 0, 0);
-  copy_tile(id_1, 0, kTileBytes);
+  if (n_tiles > 1) copy_tile(id_1, 0, kTileBytes);
   copy_tile(id_u, vplane, kVBuf);
 
-  // ---- this wave's Q^T, O^T = 0, normaliser = 0
+  // ---- Q^T, O^T = 0, normaliser = 0
   {
-    const int r = row_of(lane);
-    const int head = head0 + (r & ((1 << gs) - 1));
-    const uint16_t* qp = p.q + ((int64_t)(it.qrow0 + (r >> gs)) * H + head) * D + 8 * g;
-    u32x4 q[D / 32];
-#pragma unroll
-    for (int t = 0; t < D / 32; ++t) q[t] = *(const u32x4*)(qp + 32 * t);
     tile32::acc_mine<128>();
     unroll<D / 4>([&](auto i) __attribute__((always_inline)) { tile32::acc_write<decltype(i)::value>(0u); });
     unroll<D / 8>([&](auto i) __attribute__((always_inline)) {
@@ -291,7 +295,7 @@ __device__ __forceinline__ void tile16_body(const AttnParams& p, const TileItem&
     const int par = (u & 1) * kTileBytes, other = par ^ kTileBytes;
     const int kt = it.k_begin + u * kTileK;
     const int n_valid = it.k_end - (kt - kTileK);
-    if (u >= n_tiles - 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no copy follows V of tile u - 1
+    if (u >= n_tiles - 1 && u > 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no copy follows V of tile u - 1
     if (n_valid < kTileK) {  // dead slots of that tile: zero (0 * NaN would poison the product)
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       const int at = here();
@@ -301,7 +305,8 @@ __device__ __forceinline__ void tile16_body(const AttnParams& p, const TileItem&
           *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(my_lds + (uint32_t)(kVBuf + other + 1024 * j) + 16 * at) = (u32x4){0u, 0u, 0u, 0u};
       }
     }
-    barrier<kR>();
+    if (u == 0 && n_tiles > 1) barrier<2 * kR>();  // K of the second tile and V of the first may be on their way
+    else barrier<kR>();
     const int vt = n_tiles == 2 ? u + 1 : u;  // (no third tile needs the wait for V of the second to be by count)
     if (vt > 0 && vt < n_tiles) copy_tile(vt == u ? id_u : id_1, vplane, __builtin_amdgcn_readfirstlane(kVBuf + (vt & 1) * kTileBytes));
     if (u > 0 && 2 * u - 2 < n_half) {

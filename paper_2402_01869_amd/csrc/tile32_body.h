@@ -233,6 +233,17 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
   const int wave_pos_hi = it.pos0 + min((32 * w + 31) >> gs, it.n_rows - 1);   // largest limit in the wave
   const float sc = p.scale_log2e;
 
+  // ---- this wave's Q^T, asked for beside the block ids and there before the first copy: loads return in order, and the compiler, which
+  // does not know of the copies, waits for every load in flight.  Behind the copies the first scores waited for K of a second
+  // tile and V of the first (2 rows and 2 chunks of 32, 4 heads of 64: 12.75 us a call, now 12.5; one 512-row chunk on 2500 keys, 64
+  // heads over 8, two layers: 126.2, 124.5).  A call on a single tile copies no second one.
+  const int r = row_of(lane);
+  const int head = head0 + (r & ((1 << gs) - 1));
+  const uint16_t* qp = p.q + ((int64_t)(it.qrow0 + (r >> gs)) * H + head) * D + 8 * hl;
+  u32x4 q[kQ];
+#pragma unroll
+  for (int s = 0; s < kQ; ++s) q[s] = *(const u32x4*)(qp + 16 * s);
+
   // ---- keys and values: this wave copies keys 8 w .. 8 w + 7 of every tile, half of block w / 2 of the tile's four
   typedef __attribute__((address_space(4))) const int32_t const_i32;
   const_i32* bt = (const_i32*)(p.bt_flat + table_start(p, offs, it.seq));
@@ -255,18 +266,14 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
     for (int j = 0; j < kR; ++j) copy_region(b + 128 * j, lane_off, my_lds + (uint32_t)(buf + 1024 * j));
   };
   int id_u = block_id(0), id_1 = block_id(1), id_2 = block_id(2);  // blocks of tiles u, u + 1, u + 2
+#pragma unroll
+  for (int s = 0; s < kQ; ++s) asm volatile("" ::"v"(q[s]));  // waits
   copy_tile(id_u, 0, 0);
-  copy_tile(id_1, 0, G::kTileBytes);
+  if (n_tiles > 1) copy_tile(id_1, 0, G::kTileBytes);
   copy_tile(id_u, vplane, kVBuf);
 
-  // ---- this wave's Q^T, O^T = 0, normaliser = 0
+  // ---- Q^T, O^T = 0, normaliser = 0
   {
-    const int r = row_of(lane);
-    const int head = head0 + (r & ((1 << gs) - 1));
-    const uint16_t* qp = p.q + ((int64_t)(it.qrow0 + (r >> gs)) * H + head) * D + 8 * hl;
-    u32x4 q[kQ];
-#pragma unroll
-    for (int s = 0; s < kQ; ++s) q[s] = *(const u32x4*)(qp + 16 * s);
     acc_mine<D>();
     unroll<D / 2>([&](auto i) __attribute__((always_inline)) { acc_write<decltype(i)::value>(0u); });
     unroll<4 * kQ>([&](auto i) __attribute__((always_inline)) {
@@ -311,9 +318,9 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   };
 
-  // ---- Steps.  Step u has two barriers.  Barrier A publishes V of tile u - 1 and frees the buffer of tile u - 2, into which V of
-  // tile u is copied then; barrier B publishes K of tile u + 1 and frees the buffer of tile u for K of tile u + 2.  So every copy
-  // has a whole step to arrive, and a wave waits for all but the last tile's worth (kR) it has issued.
+  // ---- Steps.  Step u has two barriers.  Barrier A publishes V of tile u - 1 (the first one K of tile 0) and frees the buffer of tile
+  // u - 2, into which V of tile u is copied then; barrier B publishes K of tile u + 1 and frees the buffer of tile u for K of tile
+  // u + 2.  So every copy has a whole step to arrive, and a wave waits for all but the last tile's worth (kR) it has issued.
   // Between them a wave does one of two things, whatever the others do:
   //   serial  A(u); products of tile u - 1, second half of its weights first; scores of tile u, weights of its first half; B(u)
   //   fast    scores of half 2 u | A(u) | weights of half 2 u - 1 | O += P(2 u - 2);  scores of half 2 u + 1 | B(u) | weights of half 2 u | O += P(2 u - 1),
@@ -406,7 +413,7 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
     const int par = (u & 1) * G::kTileBytes, other = par ^ G::kTileBytes;
     const int kt = it.k_begin + u * kTileK;
     const int n_valid = it.k_end - (kt - kTileK);
-    if (u >= n_tiles - 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no copy follows V of tile u - 1
+    if (u >= n_tiles - 1 && u > 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no copy follows V of tile u - 1
     if (n_valid < kTileK) {  // dead slots of that tile: zero (0 * NaN would poison the product)
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       const int at = here();
@@ -416,7 +423,8 @@ __device__ __forceinline__ void tile32_body(const AttnParams& p, const TileItem&
           *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(my_lds + (uint32_t)(kVBuf + other + 1024 * j) + 16 * at) = (u32x4){0u, 0u, 0u, 0u};
       }
     }
-    barrier<kR>();
+    if (u == 0 && n_tiles > 1) barrier<2 * kR>();  // K of the second tile and V of the first may be on their way
+    else barrier<kR>();
     const int vt = n_tiles == 2 ? u + 1 : u;  // (no third tile needs the wait for V of the second to be by count)
     if (vt > 0 && vt < n_tiles) copy_tile(vt == u ? id_u : id_1, vplane, __builtin_amdgcn_readfirstlane(kVBuf + (vt & 1) * G::kTileBytes));
     if (u > 0 && 2 * u - 2 < n_half) {
