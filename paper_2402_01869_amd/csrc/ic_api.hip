@@ -242,6 +242,11 @@ SeqRoute route(const PlanSizes& ps, int c, int n) {
 // 9600 keys, 1 to 22 chunks, the rows whole and in partitions of 384 to 2048 keys; rms 7 %).  What these times choose took 1.6 %
 // longer in the mean than the best of what was measured for the batch (at most 17 %); whole rows always side by side 16 % (up
 // to 3.5 times: thousands of rows of 40 keys), and one after the other below a threshold on the shorter kernel's time 6 %.
+// Measured again with the tile kernels that run their products and weights as one stream: with tile_flops of head_dim 128 and 256
+// as now (before: 1.29 and 1.15) these times are 10 % off (rms, before 12) and choose 1.8 % more than the best (before 1.9; head_dim
+// 256 2.3, before 2.8).  At head_dim 64 and for grouped pools the rates that fit best, 1.27 and 1.55, chose no better.  With
+// these rates and those of tile_step_us() as now, 81 batches of 969 got another plan, which takes 4 % less time in the
+// mean (16 % less to 9 % more).
 struct RowLoad {
   int64_t items = 0;                  // work items x (query heads on the vector kernel, K/V heads on the group kernel)
   double bytes = 0.0, longest = 0.0;  // K/V bytes they read, of the longest item
@@ -261,8 +266,8 @@ struct LaunchRates {
   double pair_us;     // fork, join and upload
 };
 const LaunchRates& launch_rates(int head_dim, bool group) {
-  static const LaunchRates rates[4] = {{1.11e9, 40e3, 39e3, 5.2e6, 22e3, 29.0}, {1.29e9, 92e3, 41e3, 6.2e6, 38e3, 26.0},
-                                       {1.15e9, 100e3, 38e3, 6.1e6, 50e3, 35.5}, {1.44e9, 28e3, 64e3, 6.05e6, 38e3, 32.0}};
+  static const LaunchRates rates[4] = {{1.11e9, 40e3, 39e3, 5.2e6, 22e3, 29.0}, {1.42e9, 92e3, 41e3, 6.2e6, 38e3, 26.0},
+                                       {1.45e9, 100e3, 38e3, 6.1e6, 50e3, 35.5}, {1.44e9, 28e3, 64e3, 6.05e6, 38e3, 32.0}};
   return rates[group ? 3 : head_dim == 64 ? 0 : head_dim == 128 ? 1 : 2];
 }
 
@@ -383,8 +388,9 @@ RowLoad row_load(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& p
 }
 
 // Its tile items; *alone: without rows beside them.  From six rounds on the persistent tile kernel, whose queues keep the tiles
-// of a sequence on one L2, is the faster one at head_dim 256 too, where it only runs side by side (one row of 100 keys, 8 chunks
-// of 2048 on 2048 keys: 1087 us side by side, 1171 one after the other; 8 of 1024 on 512: 220, 212).
+// of a sequence on one L2, is the faster one at head_dim 256 too, where it only runs side by side (one row of 100 keys, 16 heads, 8
+// chunks of 2048 on 2048 keys: 899 us side by side, 996 one after the other; 16 of 1024 on 3000: 1147, 1423; 8 of 2048 on 8192: 2553,
+// 2615; with four rounds 8 of 1024 on 512: 193, 190).
 double tile_load_us(const ic_pool* pool, const ic_batch_desc* d, const PlanSizes& ps, double* alone) {
   int64_t items = 0, steps = 0, most = 0;
   for (int s = 0; s < d->num_seqs; ++s) {
@@ -436,10 +442,11 @@ int choose_row_part_beside(const ic_pool* pool, const ic_batch_desc* d, const Pl
   return best;
 }
 
-// Time of one 64-key step of a tile workgroup at the rate all 256 reach together (0.9 PFLOP/s, head_dim 256: 0.5); it
-// takes the same time however many of the tile's rows are live.
+// Time of one 64-key step of a tile workgroup among 256 (1.0 PFLOP/s, head_dim 256: 0.85); it takes the same time however many of
+// the tile's rows are live.  Of 77 batches of chunks, each measured in up to 12 partitions, the ones chosen with it take 0.9 % longer
+// than the best in the mean and 14 % at most (with the 0.9 and 0.5 of the tile kernels before: 1.15 %, 18 %).
 double tile_step_us(int head_dim) {
-  return 4.0 * tile_rows(head_dim) * 64 * head_dim / ((head_dim > 128 ? 0.5e9 : 0.9e9) / kExpectedCus);
+  return 4.0 * tile_rows(head_dim) * 64 * head_dim / ((head_dim > 128 ? 0.85e9 : 1.0e9) / kExpectedCus);
 }
 
 // Keys per span work item when the caller leaves the choice to the library: the partition expected to end soonest.
@@ -667,8 +674,8 @@ PlanLaunches plan_launches(const ic_pool* pool, const PlanSizes& ps) {
   // query tiles of one (sequence, head) on one L2: on 2048-row chunks the spans then fetch 2.6 x instead of 6.9 x
   // their keys from HBM and finish 7 % sooner (9.66 against 10.41 ms); shorter chunks and grouped pools: no change.
   // head_dim 256: one workgroup per work item.  Neither is the better one throughout: 8 chunks of 512 rows on 512..2048 keys, 16
-  // heads, 124 us either way, 4 chunks of 200..400 on 1000..6000, 16 heads over 4, 118 us against 124, 8 of 2048 on 8192 2.58
-  // against 2.53 ms.
+  // heads, 124 us either way, 4 chunks of 200..400 on 1000..6000, 16 heads over 4, 118 us against 124 (persistent), 8 of 2048 on
+  // 8192 2.58 ms against 2.53 and, with one short row beside the chunks, 16 of 1024 on 3000 1.42 ms against 1.15.
   how.tile = !tiles ? IC_LAUNCH_NONE : how.side_by_side || D <= 128 ? IC_LAUNCH_PERSISTENT : IC_LAUNCH_PER_ITEM;
   // row_launch = 3: the side-by-side builds, alone
   how.group = !groups ? IC_LAUNCH_NONE : how.side_by_side || (t.row_launch == 3 && ps.slim_group) ? IC_LAUNCH_SLIM : IC_LAUNCH_PER_ITEM;

@@ -118,6 +118,19 @@ def test_rows_beside_tiles_are_split_where_that_ends_sooner(H, Hkv, D, n, keys, 
     assert (plan["row_items"][:, 4] >= 0).any() == split
 
 
+@pytest.mark.parametrize("H,Hkv,D,n,keys,n_span,span,prefix,pair,split", [
+    # plans that follow from the rates of the tile kernels as they are; measured this way / as planned with the rates of the
+    # kernels before them, us
+    (16, 16, 256, 1, 8000, 3, 90, 3000, False, True),    # 70.5 / 81.2 side by side
+    (16, 16, 256, 86, 350, 2, 512, 1500, True, False),   # 113 / 125 with the chunks split
+    (64, 8, 128, 72, 1500, 1, 512, 1500, True, False),   # 109 / 129 with the chunks split
+])
+def test_plans_follow_the_rates_of_the_tile_kernels(H, Hkv, D, n, keys, n_span, span, prefix, pair, split):
+    plan = _plan(H, Hkv, D, [keys] * n + [prefix + span] * n_span, [1] * n + [span] * n_span)
+    assert bool(plan["side_by_side"]) == pair
+    assert (plan["span_part_tokens"] < prefix + span) == split
+
+
 @pytest.mark.parametrize("H,Hkv,ctx,q_len,kernel", [
     (40, 40, [3000, 16384], [1, 2048], 1),     # 2048 span rows row by row
     (64, 8, [3000, 700], [1, 100], 1),
