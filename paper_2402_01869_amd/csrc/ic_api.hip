@@ -195,7 +195,7 @@ struct PlanSizes {
   bool slim_group;                     // the group kernel has a slim build for the shape
   bool side_by_side;                   // the tile kernel beside the slim row or group kernel, on two streams
   bool row_per_item;                   // the vector kernel's items are short, or split by choose_row_part: one workgroup each, no queue
-  bool tile_leads;                     // the tile items are expected to take longer than the row items
+  bool tile_leads;                     // side by side: the tile kernel is the one on the caller's stream
   size_t off_ctr, off_bt_off, off_bt_flat, off_row, off_tile, off_few, off_merge, off_row_dst, off_slot_merge, off_arrived, image_bytes;
   int row_slots, row_merges;           // partial slots and merge items of split decode rows: the first of each
   size_t off_part_o, off_part_ml, total_bytes;
@@ -264,10 +264,11 @@ struct LaunchRates {
                       // 3000 keys 1051 us beside one short chunk, 789 after it)
   double row_alone;   // ... of a workgroup of the stand-alone launches on a CU of its own
   double pair_us;     // fork, join and upload
+  double lead;        // the tile kernel leads while the rows' time (queued_rows_us) is below so much of its own (see tile_leads)
 };
 const LaunchRates& launch_rates(int head_dim, bool group) {
-  static const LaunchRates rates[4] = {{1.11e9, 40e3, 39e3, 5.2e6, 22e3, 29.0}, {1.42e9, 92e3, 41e3, 6.2e6, 38e3, 26.0},
-                                       {1.45e9, 100e3, 38e3, 6.1e6, 50e3, 35.5}, {1.44e9, 28e3, 64e3, 6.05e6, 38e3, 32.0}};
+  static const LaunchRates rates[4] = {{1.11e9, 40e3, 39e3, 5.2e6, 22e3, 29.0, 0.65}, {1.42e9, 92e3, 41e3, 6.2e6, 38e3, 26.0, 1.0},
+                                       {1.45e9, 100e3, 38e3, 6.1e6, 50e3, 35.5, 0.95}, {1.44e9, 28e3, 64e3, 6.05e6, 38e3, 32.0, 1.5}};
   return rates[group ? 3 : head_dim == 64 ? 0 : head_dim == 128 ? 1 : 2];
 }
 
@@ -575,13 +576,20 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, Room
         ps.side_by_side = side_by_side_us(rate, tiles_time, rows) + merge_launch_us(ps, rows) < serial + slack;
       }
       ps.row_part = ps.side_by_side ? part_beside : part_alone;
+      // Which of the two kernels goes on the caller's stream, with issue priority if it is the tile kernel; the other one goes
+      // through the fork and join of the second stream.  The line is where the calls take the same time either way, between
+      // these ratios of the rows' time to the tiles' (tile kernel first / rows first, us, well off the line): 40 heads of
+      // 128, 0.95 and 1.1 (8 chunks of 512 on 2000 and 15 rows of 2500 keys 278 / 303, 29 rows 377 / 362); 32 heads of 64,
+      // 0.6 and 0.7 (11 rows 128 / 135, 25 rows 182 / 154); 16 heads of 256, 0.8 and 1.2 (15 rows 234 / 247, 25 rows 288 /
+      // 280); 64 heads over 8 and 16 over 4 and 2, 1.2 to 2 (199 rows of 2500 504 / 551, 85 of 9000 697 / 694, 110 855 / 829).
+      ps.tile_leads = queued_rows_us(launch_rates(pool->cfg.head_dim, ps.decode_as_group), rows) <
+                      launch_rates(pool->cfg.head_dim, ps.decode_as_group).lead * tiles_time;
     } else {
       ps.row_part = part_alone;
     }
   }
   ic_plan_info& in = ps.info;
-  double tile_pairs = 0, row_keys = 0;  // (query row, key) pairs of the tile items; keys of the row items
-  double vec_keys = 0;                  // ... of those on the vector kernel
+  double vec_keys = 0;  // of the row items on the vector kernel
   for (int s = 0; s < d->num_seqs; ++s) {
     const int c = d->ctx_len[s], n = d->q_len[s];
     in.table_entries += (c + kBlockSize - 1) / kBlockSize;
@@ -596,10 +604,7 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, Room
       const int klen = c - n + i + 1;
       const int parts = (klen + ps.row_part - 1) / ps.row_part;
       in.row_items += parts;
-      if (!rt.few_unit) {
-        row_keys += klen;
-        if (i < rt.n_few || !rt.rest_group) vec_keys += klen;
-      }
+      if (!rt.few_unit && (i < rt.n_few || !rt.rest_group)) vec_keys += klen;
       if (i < rt.n_few || !rt.rest_group) ps.vec_items += parts;
       if (parts > 1) { in.partial_slots += parts; in.merge_rows += 1; ps.row_slots += parts; ps.row_merges += 1; }
     }
@@ -610,16 +615,11 @@ void plan_sizes(const ic_pool* pool, const ic_batch_desc* d, PlanSizes& ps, Room
         const int klen = c - n + r0 + nr;  // keys visible to the tile's last row
         const int parts = (klen + part - 1) / part;
         in.tile_items += parts;
-        tile_pairs += (double)nr * (klen - 0.5 * nr);
         if (parts > 1) { in.partial_slots += parts * nr; in.merge_rows += nr; }
       }
     }
   }
   const int H = pool->cfg.num_heads, D = pool->cfg.head_dim;
-  // Which of the two kernels of a side-by-side launch ends last, from the rates they reach there (tile kernel
-  // 0.9 PFLOP/s at 4 D flop per pair and head, row kernels 5.5 TB/s at 4 D bytes per key and K/V head): that one
-  // goes on the caller's stream, the other through the fork and join of the second stream.  (head_dim 256: 0.5 PFLOP/s.)
-  ps.tile_leads = tile_pairs * H * (4.0 * D / (D > 128 ? 0.5e15 : 0.9e15)) > row_keys * pool->cfg.num_kv_heads * (4.0 * D / 5.5e12);
   const int n_vec = ps.vec_items - ps.few_rows;
   const bool short_rows = n_vec > 0 && vec_keys * (4.0 * D) < n_vec * kShortItemBytes;
   ps.row_per_item = short_rows || (t.decode_part_tokens == 0 && ps.row_part < kDefaultRowPart);
@@ -1133,7 +1133,7 @@ static int launch_attention(ic_pool* pool, const PlanSizes& ps, float scale, con
     if (hipStreamWaitEvent(pool->side, pool->ev_fork, 0) != hipSuccess) return IC_EHIP;
     // From here on the side stream may hold work that writes dev_out and the workspace: whatever fails
     // below, the caller's stream is still made to wait for it (or, failing that, the host does).
-    // The kernel expected to end last runs on the caller's stream, where nothing but the upload is in front of it;
+    // The kernel that leads runs on the caller's stream, where nothing but the upload is in front of it;
     // the other one pays the two cross-stream waits (some 10 us each).  A tile kernel that leads also asks for
     // issue priority: what it loses to its neighbour's waves is lost to the call (measured on the 70B-shaped
     // batch: tile kernel 0.455 instead of 0.492 ms, group kernel 0.24 instead of 0.21 ms, call 0.50 instead of 0.53).
