@@ -145,8 +145,9 @@ def listing(tmp_path_factory):
         return f.read()
 
 
-@pytest.mark.parametrize("kernel", ["tile_persist_kernelILi{}ELb0E", "tile_persist_kernelILi{}ELb1E", "tile_attn_kernelILi{}E"])
-@pytest.mark.parametrize("D,own", [(64, 56), (128, 104), (256, 104)])
+@pytest.mark.parametrize("kernel,D,own", [(k, D, own) for D, own in ((64, 56), (128, 104), (256, 104))
+                                          for k in ("tile_persist_kernelILi{}ELb0E", "tile_persist_kernelILi{}ELb1E")]
+                         + [("tile_attn_kernelILi{}E", 256, 104)])      # the builds that a plan can launch
 def test_accumulation_registers_and_wait_states_of_the_tile_body(listing, kernel, D, own):
     start = re.search(r"^\S*%s\S*:" % kernel.format(D), listing, re.M).start()
     text = listing[start:listing.index(".section", start)]
