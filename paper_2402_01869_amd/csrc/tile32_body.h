@@ -171,10 +171,14 @@ __device__ __forceinline__ void acc_mine() {
 }
 
 // One 16-byte piece per lane, 1 KiB per wave, from base + offset of the lane to LDS byte address lds_at + 16 * lane.  As assembly,
-// because the compiler would make every LDS read wait for all such copies in flight; barrier() waits for them by count.
+// because the compiler would make every LDS read wait for all such copies in flight; barrier() waits for them by count.  (clang warns
+// that m0 is a reserved register, once a use; what it would put there of its own it has to know to be overwritten.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void copy_region(const char* base, uint32_t lane_off, uint32_t lds_at) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_at), "v"(lane_off), "s"(base) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // Every wave's LDS reads before are done, and so are its copies but the last kPending.
 template <int kPending>
 __device__ __forceinline__ void barrier() {
