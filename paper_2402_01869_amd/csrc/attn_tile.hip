@@ -48,8 +48,8 @@ __device__ __forceinline__ void run_few(const AttnParams& p, uint32_t unit, uint
   fewp::few_body<D>(p, p.few_items[f], (int)(unit - f * pairs), lds);
 }
 
-// One workgroup per work item: head_dim 256 where the tiles run alone.  (At head_dim 64 and 128 the persistent launch is at least as
-// fast there: 2048-row chunks 7 % faster, shorter ones and grouped pools the same.)
+// One workgroup per work item: head_dim 256 where the tiles run alone.  (At head_dim 64 and 128 the persistent launch is as fast there
+// or faster: 16 chunks of 2048 rows on 16384 keys, 32 heads of 128, 8.49 against 9.06 ms, 8 chunks of 512 the same.)
 template <int D>
 __global__ __launch_bounds__(Impl<D>::kThreads, 2) void tile_attn_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds[Impl<D>::kLdsBytes / 2];

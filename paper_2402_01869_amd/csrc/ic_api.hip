@@ -671,8 +671,8 @@ PlanLaunches plan_launches(const ic_pool* pool, const PlanSizes& ps) {
   PlanLaunches how;
   how.side_by_side = ps.side_by_side;
   // head_dim <= 128: the persistent tile launch also when no other kernel runs beside it.  Its per-XCD queues keep the
-  // query tiles of one (sequence, head) on one L2: on 2048-row chunks the spans then fetch 2.6 x instead of 6.9 x
-  // their keys from HBM and finish 7 % sooner (9.66 against 10.41 ms); shorter chunks and grouped pools: no change.
+  // query tiles of one (sequence, head) on one L2: 16 chunks of 2048 rows on 16384 keys, 32 heads of 128, then fetch 2.2 x instead
+  // of 6.5 x their keys from HBM and take 8.49 instead of 9.06 ms; 8 chunks of 512, 40 heads or 64 over 8, the same either way.
   // head_dim 256: one workgroup per work item.  Neither is the better one throughout: 8 chunks of 512 rows on 512..2048 keys, 16
   // heads, 124 us either way, 4 chunks of 200..400 on 1000..6000, 16 heads over 4, 118 us against 124 (persistent), 8 of 2048 on
   // 8192 2.58 ms against 2.53 and, with one short row beside the chunks, 16 of 1024 on 3000 1.42 ms against 1.15.
@@ -1134,9 +1134,10 @@ static int launch_attention(ic_pool* pool, const PlanSizes& ps, float scale, con
     // From here on the side stream may hold work that writes dev_out and the workspace: whatever fails
     // below, the caller's stream is still made to wait for it (or, failing that, the host does).
     // The kernel that leads runs on the caller's stream, where nothing but the upload is in front of it;
-    // the other one pays the two cross-stream waits (some 10 us each).  A tile kernel that leads also asks for
-    // issue priority: what it loses to its neighbour's waves is lost to the call (measured on the 70B-shaped
-    // batch: tile kernel 0.455 instead of 0.492 ms, group kernel 0.24 instead of 0.21 ms, call 0.50 instead of 0.53).
+    // the other one pays the two cross-stream waits (some 10 us each).  Measured on 128 decode rows and 8 chunks of 512, 64 heads over
+    // 8: tile kernel first 0.437 ms a call, rows first 0.495; 256 rows and 16 chunks of 2048 on 16384, 32 heads: 9.32 against
+    // 9.52 ms.  A tile kernel that leads also asks for issue priority: what it loses to its neighbour's waves is lost to the
+    // call (the same calls without: 0.441 and 9.35 ms, hardly more than runs differ).
     const bool tile_main = ps.tile_leads;
     hipStream_t s_tile = tile_main ? st : pool->side, s_rows = tile_main ? pool->side : st;
     p.tile_first = tile_main;
