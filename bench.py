@@ -23,13 +23,13 @@ HBM_PEAK_GBPS = 8000.0        # MI355X HBM3E, vendor figure
 # command, scaled by the pack kernel's known 640 000 KiB (FETCH_SIZE x 2.0, WRITE_SIZE x 1.0 on this GPU);
 # figures and commands in the profiles/ file named next to each.  Only valid for the default launch plan of
 # these workloads; the JSON line says where the figure comes from (`traffic_source`).
-MEASURED_TRAFFIC = {"mixed_13b/row": ((2837482 * 2.0 + 1968) * 1024, "profiles/row_and_tile_persist_kernels_mixed_13b.md"),
+MEASURED_TRAFFIC = {"mixed_13b/row": ((2816595 * 2.0 + 1448) * 1024, "profiles/row_and_tile_persist_kernels_mixed_13b.md"),
                     "gptj_decode/row": ((660150 * 2.0 + 560) * 1024, "profiles/row_persist_kernel_gptj_decode.md"),
-                    "gptj_mixed/tile": ((154356 * 2.0 + 34851) * 1024, "profiles/tile_and_row_kernels_gptj_mixed.md"),
-                    "gptj_mixed/row": ((635748 * 2.0 + 560) * 1024, "profiles/tile_and_row_kernels_gptj_mixed.md"),
-                    "gqa_70b/group": ((542050 * 2.0 + 5424) * 1024, "profiles/group_and_tile_kernels_gqa_70b.md"),
-                    "gqa_70b/tile": ((124557 * 2.0 + 65610) * 1024, "profiles/group_and_tile_kernels_gqa_70b.md"),
-                    "long_ctx/tile": ((6047503 * 2.0 + 262353) * 1024, "profiles/tile_persist_kernel_long_ctx.md")}
+                    "gptj_mixed/tile": ((156760 * 2.0 + 32824) * 1024, "profiles/tile_and_row_kernels_gptj_mixed.md"),
+                    "gptj_mixed/row": ((635491 * 2.0 + 552) * 1024, "profiles/tile_and_row_kernels_gptj_mixed.md"),
+                    "gqa_70b/group": ((544853 * 2.0 + 5416) * 1024, "profiles/group_and_tile_kernels_gqa_70b.md"),
+                    "gqa_70b/tile": ((123847 * 2.0 + 65579) * 1024, "profiles/group_and_tile_kernels_gqa_70b.md"),
+                    "long_ctx/tile": ((5353236 * 2.0 + 262731) * 1024, "profiles/tile_persist_kernel_long_ctx.md")}
 SWAP_LOOP, SWAP_REPS = 50, 7   # pack / unpack timing: launches per event pair, loops
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16, vendor figure
 
